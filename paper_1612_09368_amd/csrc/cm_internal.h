@@ -382,6 +382,13 @@ __device__ __forceinline__ int lane() { return (int)__lane_id(); }
 // lanes below this one
 __device__ __forceinline__ unsigned long long lanes_below() { return (1ull << lane()) - 1ull; }
 
+// A value that every lane of the wave holds, in a scalar register: what it
+// decides is then a scalar branch, and what it addresses a scalar base.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ int64_t uniform64(int64_t v) {
+    return (int64_t)(((uint64_t)(uint32_t)uniform((int)(v >> 32)) << 32) | (uint32_t)uniform((int)v));
+}
+
 __device__ __forceinline__ int gwave() {
     return (int)((blockIdx.x * blockDim.x + threadIdx.x) / WAVE);
 }
@@ -389,59 +396,88 @@ __device__ __forceinline__ int nwaves() { return (int)((gridDim.x * blockDim.x) 
 __device__ __forceinline__ int gtid() { return (int)(blockIdx.x * blockDim.x + threadIdx.x); }
 __device__ __forceinline__ int gthreads() { return (int)(gridDim.x * blockDim.x); }
 
-__device__ __forceinline__ int wave_sum(int v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+// Inclusive scans over the wave by DPP moves (row shifts, then row
+// broadcasts); every lane of the wave must call them.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp0(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false); }
+__device__ __forceinline__ int wave_incl_add(int v) {
+    v += dpp0<0x111, 0xf>(v);  // row_shr:1
+    v += dpp0<0x112, 0xf>(v);
+    v += dpp0<0x114, 0xf>(v);
+    v += dpp0<0x118, 0xf>(v);  // row_shr:8
+    v += dpp0<0x142, 0xa>(v);  // row_bcast:15 into rows 1, 3
+    v += dpp0<0x143, 0xc>(v);  // row_bcast:31 into rows 2, 3
     return v;
 }
+__device__ __forceinline__ int imax(int x, int y) { return x > y ? x : y; }
+__device__ __forceinline__ int wave_incl_max(int v) {  // v >= 0
+    v = imax(v, dpp0<0x111, 0xf>(v));
+    v = imax(v, dpp0<0x112, 0xf>(v));
+    v = imax(v, dpp0<0x114, 0xf>(v));
+    v = imax(v, dpp0<0x118, 0xf>(v));
+    v = imax(v, dpp0<0x142, 0xa>(v));
+    v = imax(v, dpp0<0x143, 0xc>(v));
+    return v;
+}
+__device__ __forceinline__ int wave_sum(int v) {
+    return __builtin_amdgcn_readlane(wave_incl_add(v), WAVE - 1);
+}
 
-// Phase clock: global thread 0 reads the device wall clock before a phase
-// and adds the elapsed ticks after the barrier that ends it -- in its
-// workgroup's LDS, since a read-modify-write of the control block there
-// would be a memory round trip right after each barrier on the wave every
-// other one then waits for; ph_flush adds the sums to the control block at
-// the end of a batch or launch.
+// Phase clock: one thread reads the device wall clock before a phase and
+// adds the elapsed ticks after the barrier that ends it, in its workgroup's
+// LDS (a read-modify-write of the control block there would be a memory round
+// trip per step); ph_flush adds the sums to the control block at the end of a
+// batch or launch.  The clock thread is the last workgroup's: small steps
+// hand their items to the first waves, and the clock reads and sums of a step
+// (about 1 us) on workgroup 0's first wave were waited for by every other one.
 // Slots after the phase ticks and counts: the cascade rounds and the grid
-// and local steps of the batch (kept there for the same reason).
+// and local steps of the batch (kept there for the same reason; local steps
+// are counted by workgroup 0, which runs them).
 constexpr int PH_ROUNDS = 2 * PH_SLOTS, PH_GSTEPS = 2 * PH_SLOTS + 1, PH_LSTEPS = 2 * PH_SLOTS + 2;
 constexpr int PH_WORDS = 2 * PH_SLOTS + 3;
 __device__ __forceinline__ unsigned long long *ph_lds() {
-    __shared__ unsigned long long acc[PH_WORDS];  // ticks, counts, steps (workgroup 0 only)
+    __shared__ unsigned long long acc[PH_WORDS];  // ticks, counts, steps
     return acc;
 }
+__device__ __forceinline__ bool clock_thread() { return threadIdx.x == 0 && blockIdx.x == gridDim.x - 1; }
 // At the start of a launch, before its first barrier (which orders the
-// clearing before thread 0's first use).
+// clearing before the first use).
 __device__ __forceinline__ void ph_init() {
-    if (blockIdx.x == 0 && threadIdx.x < PH_WORDS) ph_lds()[threadIdx.x] = 0ull;
+    if (threadIdx.x < PH_WORDS) ph_lds()[threadIdx.x] = 0ull;
 }
-// Count one event of slot i (PH_ROUNDS .. PH_LSTEPS); global thread 0 only.
+// Count one event of slot i (PH_ROUNDS .. PH_LSTEPS) by the calling thread,
+// without waiting for the sum.
 __device__ __forceinline__ void ph_count(int i) {
-    if (gtid() == 0) ph_lds()[i] += 1ull;
+    __hip_atomic_fetch_add(&ph_lds()[i], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 __device__ __forceinline__ unsigned long long ph_start() {
-    return gtid() == 0 ? (unsigned long long)wall_clock64() : 0ull;
+    return clock_thread() ? (unsigned long long)wall_clock64() : 0ull;
 }
 __device__ __forceinline__ void ph_stop(Ctl *, int slot, unsigned long long t0) {
-    if (gtid() == 0) {
+    if (clock_thread()) {
         unsigned long long *p = ph_lds();
         p[slot] += (unsigned long long)wall_clock64() - t0;
         p[PH_SLOTS + slot] += 1;
     }
 }
+// Adds the workgroup's sums to the control block (global thread 0's and the
+// clock thread's; the others hold none).
 __device__ __forceinline__ void ph_flush(Ctl *c) {
-    if (gtid() == 0) {
+    if (threadIdx.x == 0 && (blockIdx.x == 0 || blockIdx.x == gridDim.x - 1)) {
         unsigned long long *p = ph_lds();
         for (int i = 0; i < PH_SLOTS; ++i) {
             if (p[PH_SLOTS + i]) {
-                c->ph_ticks[i] += p[i];
-                c->ph_count[i] += p[PH_SLOTS + i];
+                atomicAdd(&c->ph_ticks[i], p[i]);
+                atomicAdd(&c->ph_count[i], p[PH_SLOTS + i]);
                 p[i] = 0ull;
                 p[PH_SLOTS + i] = 0ull;
             }
         }
-        c->st_rounds += p[PH_ROUNDS];
-        c->st_grid_steps += p[PH_GSTEPS];
-        c->st_local_steps += p[PH_LSTEPS];
-        p[PH_ROUNDS] = p[PH_GSTEPS] = p[PH_LSTEPS] = 0ull;
+        unsigned long long *dst[3] = {&c->st_rounds, &c->st_grid_steps, &c->st_local_steps};
+        for (int i = 0; i < 3; ++i) {
+            if (p[PH_ROUNDS + i]) atomicAdd(dst[i], p[PH_ROUNDS + i]);
+            p[PH_ROUNDS + i] = 0ull;
+        }
     }
 }
 
@@ -531,7 +567,7 @@ __device__ __forceinline__ uint32_t hash_key(unsigned long long k) {
 struct Team {
     int rank;
     int size;
-    __device__ __forceinline__ int wave() const { return rank / WAVE; }
+    __device__ __forceinline__ int wave() const { return uniform(rank / WAVE); }
     __device__ __forceinline__ int nwaves() const { return size / WAVE; }
     __device__ __forceinline__ bool lead() const { return rank == 0; }
 };

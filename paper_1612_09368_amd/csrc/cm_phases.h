@@ -42,7 +42,7 @@ __device__ __forceinline__ void flush_acc(Ctl *c, Acc &acc) {
 // Queue length as published by its tail, clamped to the buffer capacity
 // (a tail can pass the capacity only after an overflow, which aborts the batch).
 __device__ __forceinline__ int32_t qlen(const int32_t *tail, int32_t cap) {
-    int32_t n = ld_rlx(tail);
+    const int32_t n = uniform(ld_rlx(tail));
     return n < cap ? n : cap;
 }
 
@@ -62,10 +62,10 @@ __device__ __forceinline__ Snap take_snap(const Ctl *c) {
     const int32_t *w = reinterpret_cast<const int32_t *>(c);
     return Snap{lane() < SNAP_WORDS ? ld_rlx(w + lane()) : 0};
 }
-// The snapshot's value of field f (a word of the first 128 bytes of *c).
-// It reads another lane's register: every lane of the wave must call it.
+// The snapshot's value of field f (a word of the first 128 bytes of *c; the
+// same f in every lane), in a scalar register.
 __device__ __forceinline__ int32_t snap_word(const Snap &s, const Ctl *c, const int32_t *f) {
-    return __shfl(s.v, (int)(f - reinterpret_cast<const int32_t *>(c)));
+    return __builtin_amdgcn_readlane(s.v, uniform((int)(f - reinterpret_cast<const int32_t *>(c))));
 }
 __device__ __forceinline__ int32_t sqlen(const Snap &s, const Ctl *c, const int32_t *tail, int32_t cap) {
     const int32_t n = snap_word(s, c, tail);
@@ -1056,7 +1056,7 @@ __device__ __forceinline__ void expand_async(const KArgs &a, const Iter &it, Acc
     Ctl *c = a.ctl;
     const DevGraph &g = a.g;
     const int32_t ep = it.ep;
-    ph_count(PH_ROUNDS);
+    if (gtid() == 0) ph_count(PH_ROUNDS);
     auto claim = [&](int32_t w, int32_t k) -> bool {
         if (w < 0) return false;
         if (g.core[w] != k || g.mcd[w] <= k) return false;
@@ -1174,7 +1174,7 @@ __device__ __forceinline__ void expand_async(const KArgs &a, const Iter &it, Acc
 __device__ __forceinline__ void evict_async(const KArgs &a, const Iter &it, Acc &acc) {
     const DevGraph &g = a.g;
     const int32_t ep = it.ep;
-    ph_count(PH_ROUNDS);
+    if (gtid() == 0) ph_count(PH_ROUNDS);
     auto hit = [&](int32_t w, int32_t k) -> bool {
         if (w < 0 || g.core[w] != k || ld_rlx(&g.stamp[w]) != ep) return false;
         // a counter already at or below k has crossed once: w is evicted
@@ -1222,7 +1222,7 @@ __device__ __forceinline__ void peel_async(const KArgs &a, const Iter &it, Acc &
     Ctl *c = a.ctl;
     const DevGraph &g = a.g;
     const int32_t ep = it.ep;
-    ph_count(PH_ROUNDS);
+    if (gtid() == 0) ph_count(PH_ROUNDS);
     auto body = [&](int32_t w, int32_t k) {
         bool first = false, fire = false;
         if (w >= 0 && g.core[w] == k && ld_rlx(&g.stamp[w]) != ep) {
@@ -1414,33 +1414,47 @@ __device__ __forceinline__ void expand_round(const KArgs &a, const Iter &it, int
     // neighbours it counted without visiting never matter; and an expanding
     // vertex has visited every level-k neighbour its CSD counted.  Peeling
     // the visited set therefore still leaves exactly the risers.
-    // Returns whether w supports a level-k vertex; *cl = w newly claimed.
-    // *lk = w is a level-k supporter (core k, SD > k): a candidate this
+    // Flags of an entry w: SUP = it supports a level-k vertex (CSD counts
+    // it); LK = it is a level-k supporter (core k, SD > k), a candidate this
     // iteration, so the only kind of neighbour whose counter an eviction of
-    // the scanned vertex lowers.
-    auto csd_claim = [&](int32_t w, int32_t k, bool &cl, bool &lk, bool *up = nullptr) -> bool {
-        cl = false;
-        lk = false;
-        if (w < 0) return false;
-        const int32_t cw = g.core[w];
-        if (up) *up = cw >= k;
-        if (cw > k) return true;
-        if (cw != k || g.mcd[w] <= k) return false;
-        lk = true;
-        // already claimed: skip the atomic.  A plain load may return an
-        // older stamp (then the atomic decides), never a later one.
-        if (g.stamp[w] != ep && atomicExch(&g.stamp[w], ep) != ep) {
-            g.cd[w] = 0;
-            if (a.t.sublists) g.slen[w] = 0;
-            cl = true;
+    // the scanned vertex lowers; CL = newly claimed; UP = core >= k.
+    enum : int32_t { SUP = 1, LK = 2, CL = 4, UP = 8 };
+    auto s1 = [&](Ent &e) __attribute__((always_inline)) {
+        e.a = -1;
+        if (e.w >= 0) e.a = g.core[e.w];
+    };
+    auto s2 = [&](Ent &e) __attribute__((always_inline)) {
+        e.b = -1;
+        e.c = ep;
+        if (e.w >= 0 && e.a == e.k) {
+            e.b = g.mcd[e.w];
+            e.c = g.stamp[e.w];
         }
-        return true;
+    };
+    // already claimed: skip the atomic.  A plain load may return an older
+    // stamp (then the atomic decides), never a later one.
+    auto s3 = [&](Ent &e) __attribute__((always_inline)) {
+        e.d = ep;
+        if (e.b > e.k && e.c != ep) e.d = atomicExch(&g.stamp[e.w], ep);
+    };
+    auto s4 = [&](Ent &e) __attribute__((always_inline)) {
+        int32_t f = 0;
+        if (e.w >= 0) {
+            if (e.a > e.k) f = SUP | UP;
+            else if (e.a == e.k) f = e.b > e.k ? SUP | LK | UP : UP;
+        }
+        if (e.d != ep) {
+            g.cd[e.w] = 0;
+            if (a.t.sublists) g.slen[e.w] = 0;
+            f |= CL;
+        }
+        e.a = f;
     };
     const bool sl = a.t.sublists != 0;
-    WaveBuf bq = wave_buf(0), be = wave_buf(1), bcand = wave_buf(2);
-    auto push_next = [&](int32_t w, bool p) {
-        push_vertex_wb(a, bq, a.q.fq[bn], &c->fq_tail[sn], a.q.fh[bn], &c->fh_tail[sn], w, p);
-    };
+    Pusher pq{wave_buf(0), wave_buf(3), a.q.fq[bn], &c->fq_tail[sn], a.q.fh[bn], &c->fh_tail[sn], g.len,
+              a.t.large_deg, a.t.chunk};
+    WaveBuf be = wave_buf(1), bcand = wave_buf(2);
+    auto push_next = [&](int32_t w, bool p) { push_deep(a, pq, w, p); };
     // an evicted vertex's walk is its supporter run (sublists) or its list
     auto push_evict = [&](int32_t v, bool p, int32_t nsup) {
         push_vertex_wb_len(a, be, a.q.eq[0], &c->eq_tail[0], a.q.eh[0], &c->eh_tail[0], v,
@@ -1455,49 +1469,14 @@ __device__ __forceinline__ void expand_round(const KArgs &a, const Iter &it, int
         expand_round_pruned(a, it, r, T, acc);
         return;
     }
-    // Lists of up to `large` slots: flattened walks of the wave's batch;
-    // longer root lists are counted chunk by chunk next round.
-    for_batches(T, a.q.fq[bc], nq, [&](int32_t v) {
-        const int32_t L = v >= 0 ? g.len[v] : 0;
-        const int32_t k = v >= 0 ? g.core[v] : 0;
-        const bool big = L > a.t.large_deg;
-        push_chunks(a, a.q.fh[bn], &c->fh_tail[sn], v, big ? nchunks(L, a.t.chunk) : 0);
-        const bool live = v >= 0 && !big;
-        int32_t pcd = 0, nlk = 0;  // CSD; supporters written to this lane's list
-        flat_walk_pos(g.nbr, g, v, live ? L : 0,
-                      [&](int32_t j, int32_t w, unsigned long long own, int64_t oj, int32_t lo) {
-            bool cl, lk;
-            const int32_t jj = j < 0 ? 0 : j;
-            const bool sup = csd_claim(j >= 0 ? w : -1, __shfl(k, jj), cl, lk);
-            pcd += __popcll(__ballot(sup) & own);
-            if (sl) {
-                // compacted after the owner's earlier supporters and those
-                // of the lanes before this one that read the same list
-                const unsigned long long lkm = __ballot(lk);
-                const int32_t before = __shfl(nlk, jj);
-                if (lk) g.sub[oj + before + __popcll(lkm & lanes_below() & ~((1ull << lo) - 1ull))] = w;
-                nlk += __popcll(lkm & own);
-            }
-            push_next(w, cl);
-        });
-        if (live) {
-            g.cd[v] = pcd;
-            if (sl) g.slen[v] = nlk;
-            acc.scanned += L;
-        }
-        push_cand(v, live);
-        push_evict(v, live && pcd <= k, nlk);
-    });
-
     // Long lists, chunk by chunk; the last chunk to finish has the CSD.
     const bool ul = a.t.uplists != 0;
-    for_chunks(T, a.q.fh[bc], nh, g, a.t.chunk, [&](int32_t v, int32_t lo, int32_t hi, int32_t nch) {
-        int32_t k = g.core[v];
+    // every chunk of v reads the same ubl (ub): it changes only when the last
+    // chunk of v (all others finished) completes a build
+    for_chunks(T, a.q.fh[bc], nh, g, g.len, a.t.chunk, ul ? g.ubl : nullptr,
+               [&](int32_t v, int32_t lo, int32_t hi, int32_t L, int32_t k, int64_t o, int32_t ub) {
+        const int32_t nch = nchunks(L, a.t.chunk);
         int32_t part = 0;
-        const int64_t o = g.off[v];
-        // every chunk of v reads the same ubl: it changes only when the last
-        // chunk of v (all others finished) completes a build
-        const int32_t ub = ul ? g.ubl[v] : -1;
         int32_t seen = 0;  // entries read (uniform)
         // the chunks of v append to one supporter run: slen[v] (zero since v
         // was claimed) hands out the slots.  A chunk collects its supporters
@@ -1508,42 +1487,38 @@ __device__ __forceinline__ void expand_round(const KArgs &a, const Iter &it, int
         int32_t *sbuf = lds_sup[threadIdx.x / WAVE];
         const bool bufok = a.t.chunk <= SUPBUF;
         int32_t ns = 0;  // supporters held in sbuf (uniform)
-        auto body = [&](int32_t w, bool *up) {
-            bool cl, lk;
-            if (csd_claim(w, k, cl, lk, up)) ++part;
+        const bool build = ul && ub < 0;  // whole chunk, writing this chunk's up-list
+        int32_t nup = 0;
+        int32_t *uw = build ? g.upl + o + lo : nullptr;
+        auto fin = [&](int32_t w, int32_t x) {
+            if (x & SUP) ++part;
             if (sl) {
-                const unsigned long long lkm = __ballot(lk);
+                const unsigned long long lkm = __ballot((x & LK) != 0);
                 if (lkm) {
                     if (bufok) {
-                        if (lk) sbuf[ns + __popcll(lkm & lanes_below())] = w;
+                        if (x & LK) sbuf[ns + __popcll(lkm & lanes_below())] = w;
                         ns += __popcll(lkm);
                     } else {
                         int32_t b = 0;
                         if (lane() == 0) b = atomicAdd(&g.slen[v], __popcll(lkm));
                         b = __shfl(b, 0);
-                        if (lk) g.sub[o + b + __popcll(lkm & lanes_below())] = w;
+                        if (x & LK) g.sub[o + b + __popcll(lkm & lanes_below())] = w;
                     }
                 }
             }
-            push_next(w, cl);
+            if (build) {
+                const unsigned long long um = __ballot((x & UP) != 0);
+                if (x & UP) uw[nup + __popcll(um & lanes_below())] = w;
+                nup += __popcll(um);
+            }
+            push_next(w, (x & CL) != 0);
         };
         if (ub >= 0) {
-            seen = walk_chunk_up(g, v, lo, hi, ub, [&](int32_t w) { body(w, nullptr); });
+            seen = walk_chunk_up(g, lo, hi, ub, k, o, s1, s2, s3, s4, fin);
         } else {
-            // whole chunk; with up-lists on, write this chunk's up-list
-            int32_t nup = 0;
-            int32_t *uw = ul ? g.upl + o + lo : nullptr;
             seen = hi - lo;
-            wave_walk(g, v, lo, hi, [&](int32_t w, int32_t) {
-                bool up = false;
-                body(w, &up);
-                if (ul) {
-                    const unsigned long long um = __ballot(up);
-                    if (up) uw[nup + __popcll(um & lanes_below())] = w;
-                    nup += __popcll(um);
-                }
-            });
-            if (ul && nup < hi - lo && lane() == 0) uw[nup] = -1;
+            wave_walk_st(g.nbr + o, lo, hi, k, s1, s2, s3, s4, fin);
+            if (build && nup < hi - lo && lane() == 0) uw[nup] = -1;
         }
         if (ns > 0) {
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // other lanes' LDS writes first
@@ -1570,7 +1545,7 @@ __device__ __forceinline__ void expand_round(const KArgs &a, const Iter &it, int
                 // every chunk added its supporters (and wrote its up-list)
                 // before counting itself done
                 if (sl) nsup = __hip_atomic_load(&g.slen[v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (ul && ub < 0) g.ubl[v] = g.len[v];
+                if (ul && ub < 0) g.ubl[v] = L;
             }
             tot = __shfl(tot, 0);
             nsup = __shfl(nsup, 0);
@@ -1578,7 +1553,39 @@ __device__ __forceinline__ void expand_round(const KArgs &a, const Iter &it, int
             push_evict(v, lane() == 0 && tot <= k, nsup);
         }
     });
-    wb_flush(bq, a.q.fq[bn], a.q.vcap, &c->fq_tail[sn], &c->overflow);
+    // Lists of up to `large` slots: flattened walks of the wave's batch, then
+    // of what the wave found; longer root lists are counted chunk by chunk
+    // next round.
+    for_batches_deep(T, a.q.fq[bc], nq, pq, [&](int32_t v, int32_t limit) {
+        const int32_t L = v >= 0 ? g.len[v] : 0;
+        const int32_t k = v >= 0 ? g.core[v] : 0;
+        const bool big = L > limit;
+        push_chunks(a, a.q.fh[bn], &c->fh_tail[sn], v, big ? nchunks(L, a.t.chunk) : 0);
+        const bool live = v >= 0 && !big;
+        int32_t pcd = 0, nlk = 0;  // CSD; supporters written to this lane's list
+        const int32_t walked = flat_walk_st(g.nbr, g, v, live ? L : 0, k, s1, s2, s3, s4,
+                     [&](int32_t j, int32_t w, int32_t x, unsigned long long own, int64_t oj, int32_t lo) {
+            pcd += __popcll(__ballot((x & SUP) != 0) & own);
+            if (sl) {
+                // compacted after the owner's earlier supporters and those
+                // of the lanes before this one that read the same list
+                const unsigned long long lkm = __ballot((x & LK) != 0);
+                const int32_t before = __shfl(nlk, j);
+                if (x & LK) g.sub[oj + before + __popcll(lkm & lanes_below() & ~((1ull << lo) - 1ull))] = w;
+                nlk += __popcll(lkm & own);
+            }
+            push_next(w, (x & CL) != 0);
+        });
+        if (live) {
+            g.cd[v] = pcd;
+            if (sl) g.slen[v] = nlk;
+            acc.scanned += L;
+        }
+        push_cand(v, live);
+        push_evict(v, live && pcd <= k, nlk);
+        return walked;
+    });
+    push_done(a, pq);
     wb_flush(be, a.q.eq[0], a.q.vcap, &c->eq_tail[0], &c->overflow);
     wb_flush(bcand, a.q.cand, a.q.vcap, &c->cand_count, &c->overflow);
 }
@@ -1598,71 +1605,60 @@ __device__ __forceinline__ void evict_round(const KArgs &a, const Iter &it, int 
         ph_count(PH_ROUNDS);
     }
     const int32_t ep = it.ep;
-    auto hit = [&](int32_t w, int32_t k) -> bool {
-        if (w < 0 || g.core[w] != k || g.stamp[w] != ep) return false;
-        // a counter already at or below k has crossed once: w is evicted.
-        // Counters only fall during eviction, so a plain load, which may
-        // return an older value, never skips a live counter.
-        if (g.cd[w] <= k) return false;
-        return atomicSub(&g.cd[w], 1) == k + 1;
-    };
-    WaveBuf bq = wave_buf(0);
-    auto push_next = [&](int32_t w, bool p) {
-        push_vertex_wb(a, bq, a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn], w, p);
-    };
-    if (a.t.sublists) {
-        // Only the evicted vertex's supporter run: every entry is a level-k
-        // candidate of this iteration (the expansion scanned the evicted
-        // vertex, as every candidate, before the first eviction round), so
-        // the counter decrement needs no core or stamp test.  A newly
-        // evicted vertex is queued by the length of its run.
-        auto hit_sup = [&](int32_t w, int32_t k) -> bool {
-            if (w < 0 || g.cd[w] <= k) return false;
-            return atomicSub(&g.cd[w], 1) == k + 1;
-        };
-        auto push_ev = [&](int32_t w, bool p) {
-            push_vertex_wb_len(a, bq, a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn], w,
-                               p ? g.slen[w] : 0, p, evict_large(a), evict_chunk(a));
-        };
-        for_batches(T, a.q.eq[bc], nq, [&](int32_t v) {
-            int32_t L = v >= 0 ? g.slen[v] : 0;
-            const int32_t len = v >= 0 ? g.len[v] : 0;
-            L = L < len ? L : len;  // never past the list, even on a count left from another iteration
-            const int32_t k = v >= 0 ? g.core[v] : 0;
-            acc.scanned += L;
-            flat_walk_pos(g.sub, g, v, L, [&](int32_t j, int32_t w, unsigned long long, int64_t, int32_t) {
-                push_ev(w, hit_sup(w, __shfl(k, j < 0 ? 0 : j)));
-            });
-        });
-        // long supporter runs, item by item
-        const int32_t ech = evict_chunk(a);
-        for (int32_t jx = T.wave(); jx < nh; jx += T.nwaves()) {
-            const int64_t item = a.q.eh[bc][jx];
-            const int32_t x = item_v(item);
-            int32_t L = g.slen[x];
-            const int32_t len = g.len[x];
-            L = L < len ? L : len;
-            const int32_t lo = item_c(item) * ech;
-            const int32_t hi = lo + ech < L ? lo + ech : L;
-            const int32_t k = g.core[x];
-            const int32_t *sp = g.sub + g.off[x];
-            if (lane() == 0 && hi > lo) acc.scanned += hi - lo;
-            for (int32_t s = lo; s < hi; s += WAVE) {
-                const int32_t i = s + lane();
-                const int32_t w = i < hi ? sp[i] : -1;
-                push_ev(w, hit_sup(w, k));
-            }
+    // an evicted vertex's walk: its supporter run (sublists) or its list
+    const bool sl = a.t.sublists != 0;
+    Pusher pq{wave_buf(0), wave_buf(3), a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn],
+              sl ? g.slen : g.len, sl ? evict_large(a) : a.t.large_deg, sl ? evict_chunk(a) : a.t.chunk};
+    const int32_t *arr = sl ? g.sub : g.nbr;
+    // Of a supporter run every entry is a level-k candidate of this iteration
+    // (the expansion scanned the evicted vertex, as every candidate, before
+    // the first eviction round), so the counter decrement needs no core or
+    // stamp test; of a whole list only such neighbours count.
+    auto s1 = [&](Ent &e) __attribute__((always_inline)) {
+        e.a = e.w >= 0 ? e.k : -1;
+        e.b = ep;
+        if (!sl && e.w >= 0) {
+            e.a = g.core[e.w];
+            e.b = g.stamp[e.w];
         }
-    } else {
-        acc.scanned += for_vertex_slots(T, a.q.eq[bc], nq, g, a.t.large_deg,
-                                    [&](int32_t w, int32_t k) { push_next(w, hit(w, k)); });
-        for_chunks(T, a.q.eh[bc], nh, g, a.t.chunk, [&](int32_t x, int32_t lo, int32_t hi, int32_t) {
-            int32_t k = g.core[x];
-            if (lane() == 0) acc.scanned += hi - lo;
-            wave_walk(g, x, lo, hi, [&](int32_t w, int32_t) { push_next(w, hit(w, k)); });
-        });
-    }
-    wb_flush(bq, a.q.eq[bn], a.q.vcap, &c->eq_tail[sn], &c->overflow);
+    };
+    auto s2 = [&](Ent &e) __attribute__((always_inline)) {
+        e.c = e.k;
+        if (e.a == e.k && e.b == ep) e.c = g.cd[e.w];
+    };
+    // A counter already at or below k has crossed once: w is evicted.
+    // Counters only fall during eviction, so a plain load, which may return
+    // an older value, never skips a live counter.
+    auto s3 = [&](Ent &e) __attribute__((always_inline)) {
+        e.d = e.k;
+        if (e.c > e.k) e.d = atomicSub(&g.cd[e.w], 1);
+    };
+    auto s4 = [&](Ent &e) __attribute__((always_inline)) { e.a = e.d == e.k + 1 ? 1 : 0; };
+    auto walk_len = [&](int32_t v) -> int32_t {
+        const int32_t len = g.len[v];
+        if (!sl) return len;
+        const int32_t L = g.slen[v];
+        return L < len ? L : len;  // never past the list, even on a count left from another iteration
+    };
+    // long walks, item by item (slen never passes the list: see walk_len)
+    for_chunks(T, a.q.eh[bc], nh, g, pq.lens, pq.chunk, sl ? g.len : nullptr,
+               [&](int32_t, int32_t lo, int32_t hi, int32_t, int32_t k, int64_t o, int32_t len) {
+        if (sl && hi > len) hi = len;
+        if (hi <= lo) return;
+        if (lane() == 0) acc.scanned += hi - lo;
+        wave_walk_st(arr + o, lo, hi, k, s1, s2, s3, s4,
+                     [&](int32_t w, int32_t f) { push_deep(a, pq, w, f != 0); });
+    });
+    for_batches_deep(T, a.q.eq[bc], nq, pq, [&](int32_t v, int32_t) {
+        const int32_t L = v >= 0 ? walk_len(v) : 0;
+        const int32_t k = v >= 0 ? g.core[v] : 0;
+        acc.scanned += L;
+        return flat_walk_st(arr, g, v, L, k, s1, s2, s3, s4,
+                            [&](int32_t, int32_t w, int32_t f, unsigned long long, int64_t, int32_t) {
+                                push_deep(a, pq, w, f != 0);
+                            });
+    });
+    push_done(a, pq);
 }
 
 // Peel cascade of the deletion (Algorithms 6-7) as rounds.  A peeled vertex
@@ -1682,34 +1678,58 @@ __device__ __forceinline__ void peel_round(const KArgs &a, const Iter &it, int r
         ph_count(PH_ROUNDS);
     }
     const int32_t ep = it.ep;
-    WaveBuf bq = wave_buf(0), bt = wave_buf(1), bchg = wave_buf(2);
-    // cw = core[w]: cores do not change during a peel round
-    auto body_c = [&](int32_t w, int32_t cw, int32_t k) {
-        bool first = false, fire = false;
-        if (w >= 0 && cw == k && g.stamp[w] != ep) {
-            int32_t old = atomicAdd(&g.dec[w], 1);
-            first = old == 0;
-            fire = g.mcd[w] - old - 1 == k - 1;
-            if (fire) g.stamp[w] = ep;
+    Pusher pq{wave_buf(0), wave_buf(3), a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn], g.len,
+              a.t.large_deg, a.t.chunk};
+    WaveBuf bt = wave_buf(1), bchg = wave_buf(2);
+    // cores and SD do not change during a peel round
+    auto s1 = [&](Ent &e) __attribute__((always_inline)) {
+        e.a = -1;
+        if (e.w >= 0) e.a = g.core[e.w];
+    };
+    auto s2 = [&](Ent &e) __attribute__((always_inline)) {
+        e.b = 0;
+        e.c = ep;
+        if (e.w >= 0 && e.a == e.k) {
+            e.b = g.mcd[e.w];
+            e.c = g.stamp[e.w];
         }
-        wb_push(bt, a.q.touched, a.q.vcap, &c->touched_count, w, first, &c->overflow);
-        push_vertex_wb(a, bq, a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn], w, fire);
+    };
+    auto s3 = [&](Ent &e) __attribute__((always_inline)) {
+        e.d = -1;
+        if (e.c != ep) e.d = atomicAdd(&g.dec[e.w], 1);
+    };
+    enum : int32_t { FIRST = 1, FIRE = 2 };
+    auto s4 = [&](Ent &e) __attribute__((always_inline)) {
+        const bool hit = e.d >= 0;
+        const bool fire = hit && e.b - e.d - 1 == e.k - 1;
+        if (fire) g.stamp[e.w] = ep;
+        e.a = (hit && e.d == 0 ? FIRST : 0) | (fire ? FIRE : 0);
+    };
+    auto fin = [&](int32_t w, int32_t f) {
+        if (__ballot(f != 0) == 0ull) return;
+        const bool fire = (f & FIRE) != 0;
+        wb_push(bt, a.q.touched, a.q.vcap, &c->touched_count, w, (f & FIRST) != 0, &c->overflow);
+        push_deep(a, pq, w, fire);
         push_vertex_wb(a, bchg, a.q.chg, &c->chg_count, a.q.chh, &c->chh_count, w, fire);
     };
-    auto body = [&](int32_t w, int32_t k) { body_c(w, w >= 0 ? g.core[w] : -1, k); };
-    acc.scanned += for_vertex_slots(T, a.q.eq[bc], nq, g, a.t.large_deg, body);
     // a long list with a valid up-list is read through it: the neighbours at
     // the peeled vertex's core are all in its up-set
-    for_chunks(T, a.q.eh[bc], nh, g, a.t.chunk, [&](int32_t x, int32_t lo, int32_t hi, int32_t) {
-        int32_t k = g.core[x];
-        const int32_t ub = a.t.uplists ? g.ubl[x] : -1;
+    for_chunks(T, a.q.eh[bc], nh, g, g.len, a.t.chunk, a.t.uplists ? g.ubl : nullptr,
+               [&](int32_t, int32_t lo, int32_t hi, int32_t, int32_t k, int64_t o, int32_t ub) {
         int32_t seen = hi - lo;
-        if (ub >= 0) seen = walk_chunk_up(g, x, lo, hi, ub, [&](int32_t w) { body(w, k); });
-        else wave_walk_pre(g, x, lo, hi, [&](int32_t w) { return g.core[w]; },
-                           [&](int32_t w, int32_t cw) { body_c(w, cw, k); });
+        if (ub >= 0) seen = walk_chunk_up(g, lo, hi, ub, k, o, s1, s2, s3, s4, fin);
+        else wave_walk_st(g.nbr + o, lo, hi, k, s1, s2, s3, s4, fin);
         if (lane() == 0) acc.scanned += seen;
     });
-    wb_flush(bq, a.q.eq[bn], a.q.vcap, &c->eq_tail[sn], &c->overflow);
+    for_batches_deep(T, a.q.eq[bc], nq, pq, [&](int32_t v, int32_t) {
+        const int32_t L = v >= 0 ? g.len[v] : 0;
+        const int32_t k = v >= 0 ? g.core[v] : 0;
+        acc.scanned += L;
+        return flat_walk_st(
+            g.nbr, g, v, L, k, s1, s2, s3, s4,
+            [&](int32_t, int32_t w, int32_t f, unsigned long long, int64_t, int32_t) { fin(w, f); });
+    });
+    push_done(a, pq);
     wb_flush(bt, a.q.touched, a.q.vcap, &c->touched_count, &c->overflow);
     wb_flush(bchg, a.q.chg, a.q.vcap, &c->chg_count, &c->overflow);
 }
@@ -1800,51 +1820,46 @@ __device__ __forceinline__ void mcd_phase(const KArgs &a, const Iter &it, const 
     }
     // Only a neighbour at the level the moved vertex crossed (its new core
     // on insertion, its new core + 1 on deletion) may need a delta, so the
-    // moved-this-iteration stamp is gathered for those alone.
-    auto nb_c = [&](int32_t w, int32_t cw, int32_t cv) -> int32_t {
-        if (w < 0) return 0;
-        if (cw == (ins ? cv : cv + 1) && g.chg[w] != ep) {
+    // moved-this-iteration stamp is gathered for those alone.  Cores do not
+    // change during this step.
+    auto s1 = [&](Ent &e) __attribute__((always_inline)) {
+        e.a = -1;
+        if (e.w >= 0) e.a = g.core[e.w];
+    };
+    auto s2 = [&](Ent &e) __attribute__((always_inline)) {
+        e.b = ep;
+        if (e.w >= 0 && e.a == (ins ? e.k : e.k + 1)) e.b = g.chg[e.w];
+    };
+    auto s3 = [&](Ent &e) __attribute__((always_inline)) {
+        if (e.b != ep) {
             if (ins) {
-                atomicAdd(&g.mcd[w], 1);
+                atomicAdd(&g.mcd[e.w], 1);
                 // the moved vertex rose to w's core: it joins w's up-set
-                if (a.t.uplists) g.ubl[w] = -1;
+                if (a.t.uplists) g.ubl[e.w] = -1;
             } else {
-                atomicSub(&g.mcd[w], 1);
+                atomicSub(&g.mcd[e.w], 1);
             }
         }
-        return cw >= cv ? 1 : 0;
     };
-    auto nb = [&](int32_t w, int32_t cv) -> int32_t { return w < 0 ? 0 : nb_c(w, g.core[w], cv); };
+    auto s4 = [&](Ent &e) __attribute__((always_inline)) { e.a = e.w >= 0 && e.a >= e.k ? 1 : 0; };
     const int32_t n = sqlen(it.sn, c, &c->chg_count, a.q.vcap);
     for_batches(T, a.q.chg, n, [&](int32_t v) {
+        // any length: a list not split into chunks when it was queued may be
+        // walked by one wave
         const int32_t L = v >= 0 ? g.len[v] : 0;
         const int32_t cv = v >= 0 ? g.core[v] : 0;
-        const bool big = L > a.t.large_deg;
         int32_t cnt = 0;
-        flat_walk(g, v, big ? 0 : L, [&](int32_t j, int32_t w, unsigned long long own) {
-            cnt += __popcll(__ballot(nb(w, __shfl(cv, j < 0 ? 0 : j)) != 0) & own);
-        });
-        if (v >= 0 && !big) { g.mcd[v] = cnt; acc.scanned += L; }
-        unsigned long long m = __ballot(big);
-        while (m) {
-            const int src = __ffsll((long long)m) - 1;
-            m &= m - 1ull;
-            const int32_t vv = __shfl(v, src);
-            const int32_t cvv = __shfl(cv, src);
-            const int32_t LL = __shfl(L, src);
-            int32_t tot = 0;
-            wave_walk(g, vv, 0, LL, [&](int32_t w, int32_t) { tot += nb(w, cvv); });
-            tot = wave_sum(tot);
-            if (lane() == 0) { g.mcd[vv] = tot; acc.scanned += LL; }
-        }
+        flat_walk_st(g.nbr, g, v, L, cv, s1, s2, s3, s4,
+                     [&](int32_t, int32_t, int32_t f, unsigned long long own, int64_t, int32_t) {
+                         cnt += __popcll(__ballot(f != 0) & own);
+                     });
+        if (v >= 0) { g.mcd[v] = cnt; acc.scanned += L; }
     });
     const int32_t nh = sqlen(it.sn, c, &c->chh_count, a.q.hcap);
-    for_chunks(T, a.q.chh, nh, g, a.t.chunk, [&](int32_t v, int32_t lo, int32_t hi, int32_t) {
-        int32_t cv = g.core[v];
+    for_chunks(T, a.q.chh, nh, g, g.len, a.t.chunk, nullptr,
+               [&](int32_t v, int32_t lo, int32_t hi, int32_t, int32_t k, int64_t o, int32_t) {
         int32_t cnt = 0;
-        // cores do not change during this step
-        wave_walk_pre(g, v, lo, hi, [&](int32_t w) { return g.core[w]; },
-                      [&](int32_t w, int32_t cw) { cnt += nb_c(w, cw, cv); });
+        wave_walk_st(g.nbr + o, lo, hi, k, s1, s2, s3, s4, [&](int32_t, int32_t f) { cnt += f; });
         cnt = wave_sum(cnt);
         if (lane() == 0) { atomicAdd(&g.mcd[v], cnt); acc.scanned += hi - lo; }
     });
@@ -2065,54 +2080,64 @@ __device__ __forceinline__ int run_iterations(const KArgs &a, int ins, int max_i
         if (it.n_r == 0 || bar_aborted(a.bar)) break;
         PC pc{S_CLAIM, 0};
         bool force = false;  // published by workgroup 0: run pc on the grid
+        // One loop runs the grid's steps and, in workgroup 0 alone, the
+        // chains of small ones: a single copy of the steps in the kernel.
+        bool chain = false;                 // inside workgroup 0's chain of local steps
+        unsigned long long t0 = 0, tl = 0;  // phase clock; start of the chain
         while (pc.step != S_DONE) {
-            int64_t work = step_work(a, it, pc);
-            if (force || !step_is_local(a, it, pc, work)) {
+            bool grid = false, fg = false;
+            if (!chain) {
+                t0 = ph_start();
+                grid = force || !step_is_local(a, it, pc, step_work(a, it, pc));
                 force = false;
-                const unsigned long long t0 = ph_start();
-                run_step(a, it, pc, grid_team(), acc);
-                ph_count(PH_GSTEPS);
+                if (!grid && blockIdx.x == 0) {
+                    chain = true;
+                    tl = (unsigned long long)wall_clock64();
+                }
+            }
+            bool stop = !grid && !chain;  // the other workgroups wait for the chain's end
+            if (chain && !block_local_ok(a, it, pc, block_team())) {
+                fg = true;
+                stop = true;
+            }
+            if (!stop) {
+                run_step(a, it, pc, chain ? block_team() : grid_team(), acc);
+                if (chain ? threadIdx.x == 0 : clock_thread()) ph_count(chain ? PH_LSTEPS : PH_GSTEPS);
+            }
+            if (grid) {
                 gbar(a.bar);
                 it.sn = take_snap(c);
                 ph_stop(c, pc.step, t0);
                 pc = next_pc(a, it, pc);
             } else {
-                const unsigned long long t0 = ph_start();
-                const int slot = pubs & 1;
-                if (blockIdx.x == 0) {
-                    const Team T = block_team();
-                    bool fg = false;
-                    const unsigned long long tl = (unsigned long long)wall_clock64();
-                    for (;;) {
-                        if (!block_local_ok(a, it, pc, T)) { fg = true; break; }
-                        run_step(a, it, pc, T, acc);
-                        ph_count(PH_LSTEPS);
-                        __syncthreads();
-                        it.sn = take_snap(c);
-                        pc = next_pc(a, it, pc);
-                        if (pc.step == S_DONE) break;
-                        work = step_work(a, it, pc);
-                        if (!step_is_local(a, it, pc, work)) break;
-                        // a long chain (a cascade of many small rounds) hands
-                        // back to the grid once per slice, so that no barrier
-                        // wait outlasts its bound
-                        if (slice_over(a.bar, tl)) break;
-                    }
-                    if (threadIdx.x == 0) {
+                if (!stop) {
+                    __syncthreads();
+                    it.sn = take_snap(c);
+                    pc = next_pc(a, it, pc);
+                    // a long chain (a cascade of many small rounds) hands
+                    // back to the grid once per slice, so that no barrier
+                    // wait outlasts its bound
+                    stop = pc.step == S_DONE || !step_is_local(a, it, pc, step_work(a, it, pc)) ||
+                           slice_over(a.bar, tl);
+                }
+                if (stop) {
+                    const int slot = pubs & 1;
+                    if (chain && threadIdx.x == 0) {
                         c->ipub[slot][0] = pc.step;
                         c->ipub[slot][1] = pc.r;
                         c->ipub[slot][2] = fg ? 1 : 0;
                     }
+                    gbar(a.bar);
+                    it.sn = take_snap(c);
+                    pc.step = uniform(ld_rlx(&c->ipub[slot][0]));
+                    pc.r = uniform(ld_rlx(&c->ipub[slot][1]));
+                    force = uniform(ld_rlx(&c->ipub[slot][2])) != 0;
+                    ++pubs;
+                    chain = false;
+                    ph_stop(c, PH_LOCAL, t0);
                 }
-                gbar(a.bar);
-                it.sn = take_snap(c);
-                pc.step = ld_rlx(&c->ipub[slot][0]);
-                pc.r = ld_rlx(&c->ipub[slot][1]);
-                force = ld_rlx(&c->ipub[slot][2]) != 0;
-                ++pubs;
-                ph_stop(c, PH_LOCAL, t0);
             }
-            if (bar_aborted(a.bar)) break;
+            if (!chain && uniform(bar_aborted(a.bar) ? 1 : 0)) break;
         }
         ep = it.ep;
         if (pc.step != S_DONE) { ++it_n; break; }
@@ -2526,7 +2551,7 @@ __device__ __forceinline__ int run_one_batch(const KArgs &a, const ProgDesc *pd,
 __device__ __forceinline__ void run_program(const KArgs &a) {
     Ctl *c = a.ctl;
     ProgDesc *pd = a.prog;
-    int32_t ep = ld_rlx(&c->epoch);
+    int32_t ep = uniform(ld_rlx(&c->epoch));
     Acc acc{};
     int pubs = 0;
     const int32_t nb = pd->nb;
@@ -2572,7 +2597,7 @@ __device__ __forceinline__ void run_server(const KArgs &a) {
     Ctl *c = a.ctl;
     ProgDesc *pd = a.prog;
     ServeHdr *h = pd->hdr;
-    int32_t ep = ld_rlx(&c->epoch);
+    int32_t ep = uniform(ld_rlx(&c->epoch));
     Acc acc{};
     int pubs = 0;
     long long j = pd->sfirst;
@@ -2736,23 +2761,36 @@ __device__ __forceinline__ void dec_round(const KArgs &a, const DState &st, cons
         c->dec_rounds += 1;
     }
     const int32_t k = st.k;
-    auto body = [&](int32_t w) -> bool {
-        if (w < 0 || g.core[w] != -2) return false;
-        if (atomicSub(&g.cd[w], 1) != k + 1) return false;
-        g.core[w] = k;
-        return true;
+    auto s1 = [&](Ent &e) __attribute__((always_inline)) {
+        e.a = -1;
+        if (e.w >= 0) e.a = g.core[e.w];
     };
-    WaveBuf bq = wave_buf(0);
-    auto push_next = [&](int32_t w, bool p) {
-        push_vertex_wb(a, bq, a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn], w, p);
+    auto s2 = [&](Ent &e) __attribute__((always_inline)) {
+        e.b = k;
+        if (e.a == -2) e.b = atomicSub(&g.cd[e.w], 1);
     };
-    acc.scanned += for_vertex_slots(T, a.q.eq[bc], nq, g, a.t.large_deg,
-                                [&](int32_t w, int32_t) { push_next(w, body(w)); });
-    for_chunks(T, a.q.eh[bc], nh, g, a.t.chunk, [&](int32_t x, int32_t lo, int32_t hi, int32_t) {
+    auto s3 = [&](Ent &) __attribute__((always_inline)) {};
+    auto s4 = [&](Ent &e) __attribute__((always_inline)) {
+        e.a = e.b == k + 1 ? 1 : 0;
+        if (e.a) g.core[e.w] = k;
+    };
+    Pusher pq{wave_buf(0), wave_buf(3), a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn], g.len,
+              a.t.large_deg, a.t.chunk};
+    for_chunks(T, a.q.eh[bc], nh, g, g.len, a.t.chunk, nullptr,
+               [&](int32_t, int32_t lo, int32_t hi, int32_t, int32_t, int64_t o, int32_t) {
         if (lane() == 0) acc.scanned += hi - lo;
-        wave_walk(g, x, lo, hi, [&](int32_t w, int32_t) { push_next(w, body(w)); });
+        wave_walk_st(g.nbr + o, lo, hi, k, s1, s2, s3, s4,
+                     [&](int32_t w, int32_t f) { push_deep(a, pq, w, f != 0); });
     });
-    wb_flush(bq, a.q.eq[bn], a.q.vcap, &c->eq_tail[sn], &c->overflow);
+    for_batches_deep(T, a.q.eq[bc], nq, pq, [&](int32_t v, int32_t) {
+        const int32_t L = v >= 0 ? g.len[v] : 0;
+        acc.scanned += L;
+        return flat_walk_st(g.nbr, g, v, L, k, s1, s2, s3, s4,
+                            [&](int32_t, int32_t w, int32_t f, unsigned long long, int64_t, int32_t) {
+                                push_deep(a, pq, w, f != 0);
+                            });
+    });
+    push_done(a, pq);
 }
 
 __device__ __forceinline__ bool dec_block_local_ok(const KArgs &a, const DState &st, const Team &T) {
@@ -2778,16 +2816,16 @@ __device__ __forceinline__ DState dec_next(const KArgs &a, const DState &st) {
         nx.j = st.j + 1;
         nx.f = st.f + 1;
         const int fs = nx.f % 3;
-        if (ld_rlx(&c->eq_tail[fs]) + ld_rlx(&c->eh_tail[fs]) != 0) {
+        if (uniform(ld_rlx(&c->eq_tail[fs]) + ld_rlx(&c->eh_tail[fs])) != 0) {
             nx.step = D_ROUND;
             return nx;
         }
         const int s1 = nx.j % 3;
-        if (ld_rlx(&c->rm_count[s1]) == 0) {
+        if (uniform(ld_rlx(&c->rm_count[s1])) == 0) {
             nx.step = D_DONE;
             return nx;
         }
-        int32_t md = ld_rlx(&c->min_deg[s1]);
+        const int32_t md = uniform(ld_rlx(&c->min_deg[s1]));
         nx.k = md > st.k + 1 ? md : st.k + 1;
         nx.step = D_SWEEP;
         return nx;
@@ -2795,7 +2833,7 @@ __device__ __forceinline__ DState dec_next(const KArgs &a, const DState &st) {
     // after a round
     nx.f = st.f + 1;
     const int fs = nx.f % 3;
-    if (ld_rlx(&c->eq_tail[fs]) + ld_rlx(&c->eh_tail[fs]) != 0) {
+    if (uniform(ld_rlx(&c->eq_tail[fs]) + ld_rlx(&c->eh_tail[fs])) != 0) {
         nx.step = D_ROUND;
         return nx;
     }
@@ -2847,12 +2885,12 @@ __device__ __forceinline__ void decompose(const KArgs &a, Acc &acc) {
                 }
             }
             gbar(a.bar);
-            st.step = ld_rlx(&c->dpub[slot][0]);
-            st.k = ld_rlx(&c->dpub[slot][1]);
-            st.j = ld_rlx(&c->dpub[slot][2]);
-            st.f = ld_rlx(&c->dpub[slot][3]);
-            kmax = ld_rlx(&c->dpub[slot][4]);
-            force = ld_rlx(&c->dpub[slot][5]) != 0;
+            st.step = uniform(ld_rlx(&c->dpub[slot][0]));
+            st.k = uniform(ld_rlx(&c->dpub[slot][1]));
+            st.j = uniform(ld_rlx(&c->dpub[slot][2]));
+            st.f = uniform(ld_rlx(&c->dpub[slot][3]));
+            kmax = uniform(ld_rlx(&c->dpub[slot][4]));
+            force = uniform(ld_rlx(&c->dpub[slot][5])) != 0;
             ++pubs;
         }
     }

@@ -80,7 +80,7 @@ __device__ __forceinline__ void push_vertex(const KArgs &a, int32_t *vq, int32_t
 // LDS and appends them with one atomic per 64 or more entries; a round
 // flushes its buffers before its barrier.  wb_push / push_vertex_wb must be
 // called by every lane of the wave (pred selects the pushing lanes).
-constexpr int PUSH_SLOTS = 3;
+constexpr int PUSH_SLOTS = 4;
 struct WaveBuf {
     int32_t *buf;  // 2 * WAVE entries of this wave's slot
     int32_t n;     // entries held (uniform over the wave)
@@ -111,10 +111,50 @@ __device__ __forceinline__ void wb_push(WaveBuf &b, int32_t *q, int32_t qcap, in
     b.n += __popcll(m);
     if (b.n >= WAVE) wb_flush(b, q, qcap, tail, overflow);
 }
-// push_vertex through a wave buffer (long lists go straight to the chunk
-// queue, one atomic per wave), for a walk of L entries of w (the caller
-// gives L: the list length, or the length of another per-vertex run) and
-// runs longer than `large` split into items of `chunk` entries.
+// push_vertex through wave buffers, for a walk of L entries of w (the caller
+// gives L: the list length, or the length of another per-vertex run): walks
+// of up to `large` entries go to b, longer ones of up to DEEP_LIST to m (the
+// wave may walk them itself in this round, see for_batches_deep; flushed as
+// chunk items otherwise), the others straight to the chunk queue as items of
+// `chunk` entries.  lens: the walk lengths.
+constexpr int DEEP_LIST = 512;
+struct Pusher {
+    WaveBuf b, m;
+    int32_t *vq, *vtail;
+    int64_t *hq;
+    int32_t *htail;
+    const int32_t *lens;
+    int32_t large, chunk;
+};
+__device__ __forceinline__ void mid_flush(const KArgs &a, Pusher &p) {
+    if (p.m.n == 0) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // other lanes' LDS writes come first
+    for (int i0 = 0; i0 < p.m.n; i0 += WAVE) {
+        const bool has = i0 + lane() < p.m.n;
+        const int32_t w = has ? p.m.buf[i0 + lane()] : -1;
+        push_chunks(a, p.hq, p.htail, w, has ? nchunks(p.lens[w], p.chunk) : 0);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // reads done before the slots are reused
+    p.m.n = 0;
+}
+__device__ __forceinline__ void push_deep(const KArgs &a, Pusher &p, int32_t w, bool pred) {
+    if (__ballot(pred) == 0ull) return;
+    const int32_t L = pred ? p.lens[w] : 0;
+    wb_push(p.b, p.vq, a.q.vcap, p.vtail, w, pred && L <= p.large, &a.ctl->overflow);
+    const bool mid = pred && L > p.large && L <= DEEP_LIST;
+    const unsigned long long mm = __ballot(mid);
+    if (mm) {
+        if (mid) p.m.buf[p.m.n + __popcll(mm & lanes_below())] = w;
+        p.m.n += __popcll(mm);
+        if (p.m.n >= WAVE) mid_flush(a, p);
+    }
+    push_chunks(a, p.hq, p.htail, w, pred && L > DEEP_LIST ? nchunks(L, p.chunk) : 0);
+}
+__device__ __forceinline__ void push_done(const KArgs &a, Pusher &p) {
+    wb_flush(p.b, p.vq, a.q.vcap, p.vtail, &a.ctl->overflow);
+    mid_flush(a, p);
+}
+// ... without walks of the wave's own: long lists straight to the chunk queue
 __device__ __forceinline__ void push_vertex_wb_len(const KArgs &a, WaveBuf &b, int32_t *vq, int32_t *vtail,
                                                    int64_t *hq, int32_t *htail, int32_t w, int32_t L,
                                                    bool pred, int32_t large, int32_t chunk) {
@@ -151,17 +191,29 @@ __device__ __forceinline__ void for_all_vertices(const Team &T, int32_t n, const
     }
 }
 
-// Team-stride over chunk items, one wave per item: fc(v, lo, hi, nch).
+// Team-stride over chunk items, one wave per item: fc(v, lo, hi, L, k, o, x)
+// with v's list length L (or its length in `lens`), core number k, first slot
+// o and xw[v] (-1 without xw), all in scalar registers.  An item's words are
+// loaded together, and with them the next item.
 template <class FC>
 __device__ __forceinline__ void for_chunks(const Team &T, const int64_t *q, int32_t n, const DevGraph &g,
-                                           int32_t chunk, FC &&fc) {
-    for (int32_t j = T.wave(); j < n; j += T.nwaves()) {
-        int64_t it = q[j];
-        int32_t v = item_v(it), c = item_c(it);
-        int32_t L = g.len[v];
-        int32_t lo = c * chunk;
-        int32_t hi = lo + chunk < L ? lo + chunk : L;
-        fc(v, lo, hi, nchunks(L, chunk));
+                                           const int32_t *lens, int32_t chunk, const int32_t *xw, FC &&fc) {
+    int32_t j = T.wave();
+    if (j >= n) return;  // uniform
+    int64_t nx = q[j];
+    while (j < n) {
+        const int64_t it = uniform64(nx);
+        const int32_t v = item_v(it), c = item_c(it);
+        j += T.nwaves();
+        if (j < n) nx = q[j];
+        const int32_t L0 = lens[v], k0 = g.core[v];
+        const int64_t o0 = g.off[v];
+        int32_t x0 = -1;
+        if (xw) x0 = xw[v];
+        const int32_t L = uniform(L0), k = uniform(k0), x = uniform(x0);
+        const int64_t o = uniform64(o0);
+        const int32_t lo = c * chunk;
+        fc(v, lo, lo + chunk < L ? lo + chunk : L, L, k, o, x);
     }
 }
 
@@ -177,56 +229,115 @@ __device__ __forceinline__ void wave_walk(const DevGraph &g, int32_t v, int32_t 
     }
 }
 
-// Wave walk of slots [lo, hi) of v, up to WALK_STEPS steps at a time: the
-// entries of those steps are loaded, then pre(w) gathers one word per entry
-// (it must read data that f does not change during the walk), before
-// f(w, pre(w)) runs step by step on every lane (w < 0: padding or a
-// tombstone).  The reads of a step then overlap those of the next ones: a
-// walk of a long list is bound by the latency of its dependent reads.
+// Staged walks.  A step of a walk is a chain of dependent reads (the entry,
+// the neighbour's core or counter, its SD and stamp, the atomic that claims
+// it); a wave that walks a few hundred entries one step at a time waits for
+// that chain, 2 to 3 us, at every step.  The staged walks take WALK_STEPS
+// steps together, stage by stage, so that the reads and atomics of all of them
+// are in flight at once (8 batches on R-MAT 22 and back: expansion 93 to
+// 78 ms, SD 21 to 15 ms; 512 threads per CU leave the registers for it).  A stage may test what earlier stages loaded and issue the next
+// load or atomic, but must not look at what it issues itself (that would wait
+// for it before the next step's is issued):
+//   s1(e)   first gather of entry e.w (w < 0: none or a tombstone)
+//   s2(e)   second gathers, chosen by the first
+//   s3(e)   the atomic
+//   s4(e)   the entry's flags, into e.a
+//   fin(..) votes and pushes, step by step on every lane
+// The gathers may read what another wave's atomic is changing: a stale stamp
+// or counter only defers to the atomic.
 constexpr int WALK_STEPS = 4;
-template <class P, class F>
-__device__ __forceinline__ void wave_walk_pre(const DevGraph &g, int32_t v, int32_t lo, int32_t hi, P &&pre,
-                                              F &&f) {
-    const int32_t *p = g.nbr + g.off[v];
+struct Ent {
+    int32_t w, k;        // entry, and the k of the list it is in
+    int32_t a, b, c, d;  // the stages' words
+};
+// The steps are written out (constant indices only), so that the entries
+// stay in registers.
+static_assert(WALK_STEPS == 4, "CM_STEPS and pick() write out four steps");
+__device__ __forceinline__ int32_t pick(int32_t x0, int32_t x1, int32_t x2, int32_t x3, int u) {
+    const int32_t lo = u == 0 ? x0 : x1, hi = u == 2 ? x2 : x3;
+    return u < 2 ? lo : hi;
+}
+#define CM_STEPS(body)                      \
+    do {                                    \
+        { constexpr int u = 0; body }       \
+        { constexpr int u = 1; body }       \
+        { constexpr int u = 2; body }       \
+        { constexpr int u = 3; body }       \
+    } while (0)
+template <class S1, class S2, class S3, class S4>
+__device__ __forceinline__ void walk_stages(Ent (&e)[WALK_STEPS], S1 &&s1, S2 &&s2, S3 &&s3, S4 &&s4) {
+    CM_STEPS(s1(e[u]););
+    CM_STEPS(s2(e[u]););
+    CM_STEPS(s3(e[u]););
+    CM_STEPS(s4(e[u]););
+}
+
+// Staged wave walk of p[lo, hi), every entry with the same k: fin(w, flags).
+template <class S1, class S2, class S3, class S4, class FIN>
+__device__ __forceinline__ void wave_walk_st(const int32_t *p, int32_t lo, int32_t hi, int32_t k, S1 &&s1,
+                                             S2 &&s2, S3 &&s3, S4 &&s4, FIN &&fin) {
     for (int32_t s0 = lo; s0 < hi; s0 += WALK_STEPS * WAVE) {
-        int32_t w[WALK_STEPS], x[WALK_STEPS];
-#pragma unroll
-        for (int u = 0; u < WALK_STEPS; ++u) {
+        Ent e[WALK_STEPS];
+        CM_STEPS(
             const int32_t i = s0 + u * WAVE + lane();
-            w[u] = i < hi ? p[i] : -1;
-        }
-#pragma unroll
-        for (int u = 0; u < WALK_STEPS; ++u) x[u] = w[u] >= 0 ? pre(w[u]) : -1;
-#pragma unroll
-        for (int u = 0; u < WALK_STEPS; ++u)
-            if (s0 + u * WAVE < hi) f(w[u], x[u]);
+            e[u].w = -1;
+            e[u].k = k;
+            if (i < hi) e[u].w = p[i];
+        );
+        walk_stages(e, s1, s2, s3, s4);
+#pragma unroll 1
+        for (int u = 0; u < WALK_STEPS && s0 + u * WAVE < hi; ++u)
+            fin(pick(e[0].w, e[1].w, e[2].w, e[3].w, u), pick(e[0].a, e[1].a, e[2].a, e[3].a, u));
     }
 }
 
-// Wave walk of chunk [lo, hi) of v through v's up-list (ub = ubl[v] >= 0):
-// the chunk's compacted up-list entries, built from slots [lo, min(hi, ub))
-// and ending at a negative entry when fewer, then the slots appended since
-// (from ub on).  f(w) runs on every lane each step (w < 0: none).  Returns
-// the entries read (uniform).
-template <class F>
-__device__ __forceinline__ int32_t walk_chunk_up(const DevGraph &g, int32_t v, int32_t lo, int32_t hi,
-                                                 int32_t ub, F &&f) {
+// Staged wave walk of chunk [lo, hi) of the list at slot o through its up-list
+// (ub = ubl of its owner, >= 0): the chunk's compacted up-list entries, built from slots
+// [lo, min(hi, ub)) and ending at a negative entry when fewer, then the slots
+// appended since (from ub on).  Returns the entries read (uniform).
+template <class S1, class S2, class S3, class S4, class FIN>
+__device__ __forceinline__ int32_t walk_chunk_up(const DevGraph &g, int32_t lo, int32_t hi,
+                                                 int32_t ub, int32_t k, int64_t o, S1 &&s1, S2 &&s2,
+                                                 S3 &&s3, S4 &&s4, FIN &&fin) {
     int32_t seen = 0;
     const int32_t hb = hi < ub ? hi : ub;
-    const int32_t *up = g.upl + g.off[v] + lo;
-    for (int32_t s = 0; lo + s < hb; s += WAVE) {
-        const int32_t i = s + lane();
-        int32_t w = lo + i < hb ? up[i] : -1;
-        const unsigned long long neg = __ballot(w < 0);
-        if (neg && lane() >= __ffsll((long long)neg) - 1) w = -1;
-        seen += neg ? __ffsll((long long)neg) - 1 : WAVE;
-        f(w);
-        if (neg) break;
-    }
-    const int32_t ab = lo > ub ? lo : ub;
-    if (ab < hi) {
-        seen += hi - ab;
-        wave_walk(g, v, ab, hi, [&](int32_t w, int32_t) { f(w); });
+    const int32_t nb = hb - lo;  // slots of the chunk's up-list
+    const int32_t *up = g.upl + o + lo;
+    const int32_t *app = g.nbr + o;
+    const int32_t ab = lo > ub ? lo : ub;  // first appended slot
+    bool more = nb > 0;
+    int32_t s0 = 0, a0 = ab;
+    // one loop for both parts keeps one copy of the stages
+    while (more || a0 < hi) {
+        Ent e[WALK_STEPS];
+        const int32_t *p = more ? up : app;
+        const int32_t first = more ? s0 : a0, end = more ? nb : hi;
+        CM_STEPS(
+            const int32_t i = first + u * WAVE + lane();
+            e[u].w = -1;
+            e[u].k = k;
+            if (i < end) e[u].w = p[i];
+        );
+        if (more) {
+            CM_STEPS(
+                const unsigned long long neg = more ? __ballot(e[u].w < 0) : ~0ull;
+                const int32_t live = neg ? __ffsll((long long)neg) - 1 : WAVE;
+                if (lane() >= live) e[u].w = -1;
+                seen += live;
+                if (neg) more = false;
+            );
+            s0 += WALK_STEPS * WAVE;
+        } else {
+            const int32_t got = hi - a0;
+            seen += got < WALK_STEPS * WAVE ? got : WALK_STEPS * WAVE;
+            a0 += WALK_STEPS * WAVE;
+        }
+        walk_stages(e, s1, s2, s3, s4);
+#pragma unroll 1
+        for (int u = 0; u < WALK_STEPS; ++u) {
+            const int32_t wu = pick(e[0].w, e[1].w, e[2].w, e[3].w, u);
+            if (__ballot(wu >= 0) != 0ull) fin(wu, pick(e[0].a, e[1].a, e[2].a, e[3].a, u));
+        }
     }
     return seen;
 }
@@ -249,29 +360,67 @@ __device__ __forceinline__ void for_batches(const Team &T, const int32_t *q, int
     }
 }
 
+// for_batches over a round's queue, then over what the wave itself found:
+// once its share of the queue is done, the wave takes the vertices in its own
+// push buffers as its next batches -- a long list alone, or the short ones
+// together if they are few (a wide frontier is spread over all waves by the
+// queue instead) -- as long as it has walked fewer than DEEP_STEPS steps of
+// 64 entries in this round.  Cascades are order-free closures (every vertex
+// is claimed, evicted or peeled exactly once through an atomic), so a vertex
+// may be walked in the round that finds it.  fb(v, limit) walks the lists of
+// up to `limit` entries and returns the entries it walked (uniform).
+// A grid round costs about 6 us of barrier plus its first chain of reads, a
+// wave's own group of steps about 3 us: 12 steps and 32 vertices were the best
+// of (4, 8), (8, 12), (12, 32), (16, 16) over the update workloads (ER 2^18,
+// 100 edges: 1.84 ms without, 2.01 / 1.53 / 1.39 / 1.49 ms; 64-graph pool:
+// 55.1 ms without, 47.6 / 46.7 / 47.5 / 47.4 ms).
+constexpr int DEEP_STEPS = 12, DEEP_WIDTH = 32;
+template <class FB>
+__device__ __forceinline__ void for_batches_deep(const Team &T, const int32_t *q, int32_t n, Pusher &p,
+                                                 FB &&fb) {
+    const int nw = T.nwaves();
+    int per = (int)(((int64_t)n + nw - 1) / nw);
+    per = per < 1 ? 1 : (per > WAVE ? WAVE : per);
+    const int step = nw * per;
+    int32_t base = T.wave() * per;
+    int32_t left = DEEP_STEPS;
+    for (;;) {
+        int32_t v = -1, limit = p.large;
+        if (base < n) {
+            const int32_t i = base + lane();
+            if (lane() < per && i < n) v = q[i];
+            base += step;
+        } else {
+            if (left <= 0 || p.m.n + p.b.n == 0 || (p.m.n == 0 && p.b.n > DEEP_WIDTH)) break;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // other lanes' LDS writes come first
+            if (p.m.n > 0) {
+                p.m.n -= 1;
+                if (lane() == 0) v = p.m.buf[p.m.n];
+                limit = DEEP_LIST;
+            } else {
+                if (lane() < p.b.n) v = p.b.buf[lane()];
+                p.b.n = 0;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // reads done before the slots are reused
+        }
+        left -= (fb(v, limit) + WAVE - 1) / WAVE;
+    }
+}
+
 // Flattened walk over the lists of a wave's batch: lane j holds vertex v_j
 // and the number L_j of leading slots of its list to walk (0 for none).
 // The lists are laid end to end and every lane takes one slot per step, so
 // a batch of short and medium lists keeps all 64 lanes busy with 64 loads
-// in flight instead of walking the lists one after another.  f(j, w, own,
-// oj, lo) runs on every lane each step (it may use wave votes): j = the lane
-// whose list holds the slot this lane reads (-1 when it reads none), w = the
-// slot's entry of `arr` (< 0 for a tombstone or none), own = the lanes that
-// read a slot of THIS lane's list in this step, so that
-// popcount(ballot(p) & own) counts p over this lane's slots; oj = the first
-// slot of lane j's list and lo = the first lane of this step that reads
-// from lane j's list (lanes lo .. this lane - 1 read the slots just before
-// this one), for writing compacted per-list output.  arr is the adjacency
-// pool or an array with its slot ranges.
+// in flight instead of walking the lists one after another.  f(j, w, own)
+// runs on every lane each step (it may use wave votes): j = the lane whose
+// list holds the slot this lane reads (-1 when it reads none), w = the slot's
+// entry (< 0 for a tombstone or none), own = the lanes that read a slot of
+// THIS lane's list in this step, so that popcount(ballot(p) & own) counts p
+// over this lane's slots.
 template <class F>
-__device__ __forceinline__ void flat_walk_pos(const int32_t *arr, const DevGraph &g, int32_t v, int32_t L,
-                                              F &&f) {
-    int32_t incl = L;
-    for (int o = 1; o < WAVE; o <<= 1) {
-        const int32_t t = __shfl_up(incl, o);
-        if (lane() >= o) incl += t;
-    }
-    const int32_t total = __shfl(incl, WAVE - 1);
+__device__ __forceinline__ void flat_walk(const DevGraph &g, int32_t v, int32_t L, F &&f) {
+    const int32_t incl = wave_incl_add(L);
+    const int32_t total = __builtin_amdgcn_readlane(incl, WAVE - 1);
     const int32_t excl = incl - L;
     const int64_t off = v >= 0 ? g.off[v] : 0;  // independent of L: issues with the length load
     for (int32_t base = 0; base < total; base += WAVE) {
@@ -285,52 +434,81 @@ __device__ __forceinline__ void flat_walk_pos(const int32_t *arr, const DevGraph
         const int32_t xj = __shfl(excl, j);
         const int64_t oj = __shfl(off, j);
         const bool has = e < total;
-        const int32_t w = has ? arr[oj + (e - xj)] : -1;
+        const int32_t w = has ? g.nbr[oj + (e - xj)] : -1;
         int32_t lo = excl - base, hi = incl - base;
         lo = lo < 0 ? 0 : (lo > WAVE ? WAVE : lo);
         hi = hi < 0 ? 0 : (hi > WAVE ? WAVE : hi);
         const unsigned long long own =
             hi > lo ? ((hi - lo == WAVE ? ~0ull : ((1ull << (hi - lo)) - 1ull)) << lo) : 0ull;
-        const int32_t loj = xj - base > 0 ? xj - base : 0;
-        f(has ? j : -1, w, own, oj, loj);
+        f(has ? j : -1, w, own);
     }
 }
-// The same over the adjacency pool, without the position arguments.
-template <class F>
-__device__ __forceinline__ void flat_walk(const DevGraph &g, int32_t v, int32_t L, F &&f) {
-    flat_walk_pos(g.nbr, g, v, L, [&](int32_t j, int32_t w, unsigned long long own, int64_t, int32_t) {
-        f(j, w, own);
-    });
+
+// The wave's owner marks of flat_walk_st (one copy for all walks of a kernel).
+__device__ __forceinline__ int32_t *mark_buf() {
+    __shared__ int32_t lds_mark[COOP_THREADS / WAVE][WALK_STEPS * WAVE];
+    return lds_mark[threadIdx.x / WAVE];
 }
 
-// Team-stride over a vertex queue visiting every slot of every list:
-// fs(w, k) runs on every lane per step, k = core number of the list's
-// owner (w < 0: no slot or a tombstone).  Lists of up to `large` slots are
-// walked flattened, batch by batch; a longer one (possible only for queue
-// entries not routed through push_vertex) is walked by the wave alone.
-// Returns the slots visited by this lane's owned lists (for statistics).
-template <class FS>
-__device__ __forceinline__ long long for_vertex_slots(const Team &T, const int32_t *q, int32_t n,
-                                                      const DevGraph &g, int32_t large, FS &&fs) {
-    long long seen = 0;
-    for_batches(T, q, n, [&](int32_t v) {
-        const int32_t L = v >= 0 ? g.len[v] : 0;
-        const int32_t k = v >= 0 ? g.core[v] : 0;
-        const bool big = L > large;
-        seen += L;
-        flat_walk(g, v, big ? 0 : L, [&](int32_t j, int32_t w, unsigned long long) {
-            fs(w, __shfl(k, j < 0 ? 0 : j));
-        });
-        unsigned long long m = __ballot(big);
-        while (m) {
-            const int src = __ffsll((long long)m) - 1;
-            m &= m - 1ull;
-            const int32_t vv = __shfl(v, src);
-            const int32_t kk = __shfl(k, src);
-            wave_walk(g, vv, 0, __shfl(L, src), [&](int32_t w, int32_t) { fs(w, kk); });
+// Staged flattened walk (flat_walk, WALK_STEPS steps at a time): lane j holds
+// vertex v_j, the number L_j of slots of its run in `arr` to walk and its k_j.
+// fin(j, w, flags, own, oj, lo): j, w and own as f of flat_walk (j >= 0), the
+// entry's flags, oj = the first slot of lane j's list and lo = the first lane
+// of this step that reads from it (lanes lo .. this lane - 1 read the slots
+// just before this one), for writing compacted per-list output.  The owners
+// of a group's slots come from marks in LDS: every list that starts inside the
+// group marks its first slot with its lane, and a running maximum spreads it
+// (a binary search by shuffles cost six dependent LDS round trips per step).
+// Returns the slots walked (uniform).
+template <class S1, class S2, class S3, class S4, class FIN>
+__device__ __forceinline__ int32_t flat_walk_st(const int32_t *arr, const DevGraph &g, int32_t v, int32_t L,
+                                                int32_t k, S1 &&s1, S2 &&s2, S3 &&s3, S4 &&s4, FIN &&fin) {
+    int32_t *mark = mark_buf();
+    const int64_t off = v >= 0 ? g.off[v] : 0;  // independent of L: issues with the length load
+    const int32_t incl = wave_incl_add(L);
+    const int32_t total = __builtin_amdgcn_readlane(incl, WAVE - 1);
+    const int32_t excl = incl - L;
+    int32_t carry = 0;  // owner of the last slot before the group, plus one
+    for (int32_t base = 0; base < total; base += WALK_STEPS * WAVE) {
+        Ent e[WALK_STEPS];
+        int32_t jj[WALK_STEPS];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // last group's reads come first
+        CM_STEPS(mark[u * WAVE + lane()] = 0;);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (L > 0 && excl >= base && excl < base + WALK_STEPS * WAVE) mark[excl - base] = lane() + 1;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        CM_STEPS(jj[u] = mark[u * WAVE + lane()];);
+        CM_STEPS(
+            int32_t m = wave_incl_max(jj[u]);
+            m = m > carry ? m : carry;
+            carry = __builtin_amdgcn_readlane(m, WAVE - 1);
+            jj[u] = m - 1;
+        );
+        CM_STEPS(
+            const int32_t i = base + u * WAVE + lane();
+            const int32_t xj = __shfl(excl, jj[u]);
+            const int64_t oj = __shfl(off, jj[u]);
+            e[u].k = __shfl(k, jj[u]);
+            e[u].w = -1;
+            if (i < total) e[u].w = arr[oj + (i - xj)];
+        );
+        walk_stages(e, s1, s2, s3, s4);
+#pragma unroll 1
+        for (int u = 0; u < WALK_STEPS && base + u * WAVE < total; ++u) {
+            const int32_t b0 = base + u * WAVE;
+            const int32_t j = pick(jj[0], jj[1], jj[2], jj[3], u);
+            const int32_t xj = __shfl(excl, j);
+            const int64_t oj = __shfl(off, j);
+            int32_t lo = excl - b0, hi = incl - b0;
+            lo = lo < 0 ? 0 : (lo > WAVE ? WAVE : lo);
+            hi = hi < 0 ? 0 : (hi > WAVE ? WAVE : hi);
+            const unsigned long long own =
+                hi > lo ? ((hi - lo == WAVE ? ~0ull : ((1ull << (hi - lo)) - 1ull)) << lo) : 0ull;
+            fin(j, pick(e[0].w, e[1].w, e[2].w, e[3].w, u), pick(e[0].a, e[1].a, e[2].a, e[3].a, u), own, oj,
+                xj - b0 > 0 ? xj - b0 : 0);
         }
-    });
-    return seen;
+    }
+    return total;
 }
 
 }  // namespace cm

@@ -1,0 +1,96 @@
+"""Cascades at the edges of the walks that run them: chains that end inside,
+at and past the steps a wave walks of its own finds in one round, and lists
+around one wave step, one group of steps, one chunk and the longest list a
+wave walks alone; every result against a recount from scratch."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1612_09368_amd as cm
+
+pytestmark = pytest.mark.gpu
+
+FORMS = [dict(mode=cm.MODE_PLAIN), dict(mode=cm.MODE_PERSISTENT), dict(mode=cm.MODE_PERSISTENT, expand_mode=2),
+         dict(mode=cm.MODE_PERSISTENT, expand_mode=3, large_degree=16, chunk=32)]
+
+
+def _check(g, ref):
+    assert np.array_equal(g.cores(), ref.cores())
+    n, s, d = ref.n, *ref.edges()
+    c = ref.cores()
+    sd = np.zeros(n, np.int64)
+    np.add.at(sd, s, c[d] >= c[s])
+    np.add.at(sd, d, c[s] >= c[d])
+    assert np.array_equal(g.superior_degrees(), np.where(c >= 0, sd, 0))
+
+
+def _round_trip(n, s, d, batch, cfg):
+    """Delete the batch, insert it again, checked after load and each half."""
+    assert torch.cuda.is_available()
+    s, d = np.asarray(s, np.int32), np.asarray(d, np.int32)
+    b = np.asarray(batch, np.int32).reshape(-1, 2)
+    ref = oracle.DynamicGraph(n, s, d)
+    with cm.Graph(**cfg) as g:
+        g.load(n, s, d)
+        g.decompose()
+        _check(g, ref)
+        for _ in range(2):
+            g.delete_edges(b[:, 0], b[:, 1])
+            ref.delete_edges(b[:, 0].copy(), b[:, 1].copy())
+            _check(g, ref)
+            g.insert_edges(b[:, 0], b[:, 1])
+            ref.insert_edges(b[:, 0].copy(), b[:, 1].copy())
+            _check(g, ref)
+
+
+@pytest.mark.parametrize("cfg", FORMS, ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items()))
+@pytest.mark.parametrize("n", [3, 8, 15, 16, 17, 18, 19, 33, 65, 129, 1000])
+def test_chain_depth(n, cfg):
+    """A cycle loses one edge: the peel runs down both arms; putting it back
+    expands over the whole cycle.  A second cycle keeps its cores."""
+    s = np.concatenate([np.arange(n), n + np.arange(n)])
+    d = np.concatenate([(np.arange(n) + 1) % n, n + (np.arange(n) + 1) % n])
+    _round_trip(2 * n, np.minimum(s, d), np.maximum(s, d), [(0, 1)], cfg)
+
+
+@pytest.mark.parametrize("cfg", FORMS, ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items()))
+@pytest.mark.parametrize("width", [1, 7, 12, 13, 63, 64, 65, 200])
+def test_wide_then_narrow(width, cfg):
+    """Cycles that share a vertex: one deletion peels `width` arms at once,
+    then each arm alone."""
+    arm = 24
+    s, d = [], []
+    nxt = 1
+    for _ in range(width):
+        ids = [0, *range(nxt, nxt + arm), 0]
+        nxt += arm
+        for a, b in zip(ids, ids[1:]):
+            s.append(min(a, b))
+            d.append(max(a, b))
+    cut = [(s[i * (arm + 1) + arm // 2], d[i * (arm + 1) + arm // 2]) for i in range(width)]
+    _round_trip(nxt, s, d, cut, cfg)
+
+
+@pytest.mark.parametrize("cfg", FORMS, ids=lambda c: "-".join(f"{k}{v}" for k, v in c.items()))
+@pytest.mark.parametrize("deg", [62, 63, 64, 65, 128, 255, 256, 257, 511, 512, 513, 1030])
+def test_hub_lists(deg, cfg):
+    """Hubs of about `deg` neighbours along a chain: every hub's list holds a
+    wheel (rim vertices at core 3) and its two chain neighbours, so that rim
+    edges pull hubs and rims across a level."""
+    hubs, s, d = 4, [], []
+    rim0 = hubs
+    cut = []
+    for h in range(hubs):
+        r = np.arange(rim0 + h * deg, rim0 + (h + 1) * deg)
+        for a, b in zip(r, np.roll(r, -1)):
+            s.append(min(a, b))
+            d.append(max(a, b))
+        s += [h] * deg
+        d += r.tolist()
+        cut.append((int(r[0]), int(r[1])))
+        cut.append((int(r[deg // 2]), int(r[deg // 2 + 1])))
+        if h:
+            s.append(h - 1)
+            d.append(h)
+    _round_trip(hubs + hubs * deg, s, d, cut, cfg)

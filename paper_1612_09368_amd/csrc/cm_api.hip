@@ -10,6 +10,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include <rocprofiler-sdk-roctx/roctx.h>
@@ -120,6 +121,11 @@ struct cm_graph {
     int32_t epoch = 0;
     int32_t bstamp = 0;
     std::string err;
+    // device allocations and their sizes; while a graph is loaded, the blocks
+    // the previous one gives up wait in `spare` (see Reuse)
+    std::unordered_map<void *, size_t> blocks;
+    std::vector<std::pair<void *, size_t>> spare;
+    bool reuse = false;
 };
 
 // ---------------------------------------------------------------------------
@@ -190,20 +196,66 @@ template <class T>
 void dev_alloc(cm_graph *g, T **p, int64_t count) {
     *p = nullptr;
     if (count <= 0) count = 1;
-    hipError_t e = hipMalloc((void **)p, sizeof(T) * (size_t)count);
+    const size_t need = sizeof(T) * (size_t)count;
+    size_t best = SIZE_MAX;
+    for (size_t i = 0; i < g->spare.size(); ++i) {
+        const size_t have = g->spare[i].second;
+        if (have >= need && have <= need + need / 4 + 4096 && (best == SIZE_MAX || have < g->spare[best].second))
+            best = i;
+    }
+    if (best != SIZE_MAX) {
+        *p = (T *)g->spare[best].first;
+        g->blocks[(void *)*p] = g->spare[best].second;
+        g->spare.erase(g->spare.begin() + (std::ptrdiff_t)best);
+        return;
+    }
+    hipError_t e = hipMalloc((void **)p, need);
+    if (e != hipSuccess && !g->spare.empty()) {
+        // the spare blocks may be what is missing
+        (void)hipGetLastError();
+        for (auto &b : g->spare) (void)hipFree(b.first);
+        g->spare.clear();
+        e = hipMalloc((void **)p, need);
+    }
     if (e != hipSuccess) {
         (void)hipGetLastError();
         *p = nullptr;
-        g->err = "device allocation of " + std::to_string(sizeof(T) * (size_t)count) + " bytes failed";
+        g->err = "device allocation of " + std::to_string(need) + " bytes failed";
         throw Fail{CM_E_NOMEM};
     }
+    g->blocks[(void *)*p] = need;
 }
 
 template <class T>
-void dev_free(T *&p) {
-    if (p) (void)hipFree((void *)p);
+void dev_free(cm_graph *g, T *&p) {
+    if (p) {
+        const auto it = g->blocks.find((void *)p);
+        const size_t bytes = it == g->blocks.end() ? 0 : it->second;
+        if (it != g->blocks.end()) g->blocks.erase(it);
+        if (g->reuse && bytes) g->spare.emplace_back((void *)p, bytes);
+        else (void)hipFree((void *)p);
+    }
     p = nullptr;
 }
+
+// While one lives, blocks given up by the handle serve its next allocations
+// of about their size; what is left over is freed at its end.  Loading a graph
+// over another replaces some 40 arrays of the same sizes: hipMalloc and hipFree
+// of a 4 to 16 MB block take 70 to 200 us each (Chung-Lu 10^6 / 10^7: 15.3 ms a
+// load with them, of which the kernels 6).  Everything the blocks are used for
+// is ordered on the handle's stream.
+struct Reuse {
+    cm_graph *g;
+    explicit Reuse(cm_graph *h) : g(h) { g->reuse = true; }
+    ~Reuse() {
+        g->reuse = false;
+        if (!g->spare.empty()) (void)hipStreamSynchronize(g->stream);
+        for (auto &b : g->spare) (void)hipFree(b.first);
+        g->spare.clear();
+    }
+    Reuse(const Reuse &) = delete;
+    Reuse &operator=(const Reuse &) = delete;
+};
 
 int64_t next_pow2(int64_t x) {
     int64_t p = 1;
@@ -340,10 +392,10 @@ void alloc_vertex_arrays(cm_graph *g, int32_t n_cap, int32_t n_keep) {
                               hipMemcpyDeviceToDevice, st));
     HIPCHK(hipStreamSynchronize(st));
     DevGraph old = g->g;
-    dev_free(old.len); dev_free(old.cap); dev_free(old.core); dev_free(old.mcd);
-    dev_free(old.stamp.p); dev_free(old.chg); dev_free(old.dec);
-    dev_free(old.done); dev_free(old.matched); dev_free(old.bmark); dev_free(old.gain);
-    dev_free(old.off); dev_free(old.claim); dev_free(old.slen); dev_free(old.ubl);
+    dev_free(g, old.len); dev_free(g, old.cap); dev_free(g, old.core); dev_free(g, old.mcd);
+    dev_free(g, old.stamp.p); dev_free(g, old.chg); dev_free(g, old.dec);
+    dev_free(g, old.done); dev_free(g, old.matched); dev_free(g, old.bmark); dev_free(g, old.gain);
+    dev_free(g, old.off); dev_free(g, old.claim); dev_free(g, old.slen); dev_free(g, old.ubl);
     ng.nbr = g->g.nbr;
     ng.sub = g->g.sub;
     ng.upl = g->g.upl;
@@ -352,27 +404,27 @@ void alloc_vertex_arrays(cm_graph *g, int32_t n_cap, int32_t n_keep) {
     g->g = ng;
 
     // vertex-sized batch / queue arrays
-    dev_free(g->b.vlist); dev_free(g->b.reloc); dev_free(g->b.reloc_off); dev_free(g->b.reloc_cap);
+    dev_free(g, g->b.vlist); dev_free(g, g->b.reloc); dev_free(g, g->b.reloc_off); dev_free(g, g->b.reloc_cap);
     dev_alloc(g, &g->b.vlist, n_cap);
     dev_alloc(g, &g->b.reloc, n_cap);
     dev_alloc(g, &g->b.reloc_off, n_cap);
     dev_alloc(g, &g->b.reloc_cap, n_cap);
     for (int i = 0; i < 2; ++i) {
-        dev_free(g->q.fq[i]); dev_free(g->q.eq[i]);
+        dev_free(g, g->q.fq[i]); dev_free(g, g->q.eq[i]);
         dev_alloc(g, &g->q.fq[i], n_cap);
         dev_alloc(g, &g->q.eq[i], n_cap);
     }
-    dev_free(g->q.cand); dev_free(g->q.chg); dev_free(g->q.touched);
+    dev_free(g, g->q.cand); dev_free(g, g->q.chg); dev_free(g, g->q.touched);
     dev_alloc(g, &g->q.cand, n_cap);
     dev_alloc(g, &g->q.chg, n_cap);
     dev_alloc(g, &g->q.touched, n_cap);
     g->q.vcap = n_cap;
-    dev_free(g->firstidx);
+    dev_free(g, g->firstidx);
     dev_alloc(g, &g->firstidx, n_cap);
     HIPCHK(fill_i32(g->firstidx, INT_MAX, n_cap, st));
     int64_t need_tmp = scan_tmp_len(n_cap);
     if (need_tmp > g->scan_tmp_cap) {
-        dev_free(g->scan_tmp);
+        dev_free(g, g->scan_tmp);
         dev_alloc(g, &g->scan_tmp, need_tmp);
         g->scan_tmp_cap = need_tmp;
     }
@@ -384,11 +436,11 @@ void alloc_chunk_queues(cm_graph *g) {
     if (h > INT_MAX) h = INT_MAX;
     if (h > g->q.hcap) {
         for (int i = 0; i < 2; ++i) {
-            dev_free(g->q.fh[i]); dev_free(g->q.eh[i]);
+            dev_free(g, g->q.fh[i]); dev_free(g, g->q.eh[i]);
             dev_alloc(g, &g->q.fh[i], h);
             dev_alloc(g, &g->q.eh[i], h);
         }
-        dev_free(g->q.chh);
+        dev_free(g, g->q.chh);
         dev_alloc(g, &g->q.chh, h);
         g->q.hcap = (int32_t)h;
     }
@@ -398,7 +450,7 @@ void alloc_chunk_queues(cm_graph *g) {
         const int64_t ac = std::min<int64_t>((int64_t)g->g.n_cap + 2 * (int64_t)g->q.hcap, INT_MAX);
         if (ac > g->q.acap) {
             for (int i = 0; i < 2; ++i) {
-                dev_free(g->q.aq[i]);
+                dev_free(g, g->q.aq[i]);
                 dev_alloc(g, &g->q.aq[i], ac);
                 HIPCHK(fill_u64(g->q.aq[i], ~0ull, ac, g->stream));
             }
@@ -432,9 +484,9 @@ void ensure_batch(cm_graph *g, int64_t s) {
     if (s > g->batch_cap) {
         int64_t c = std::max<int64_t>(s, 1024);
         DevBatch &b = g->b;
-        dev_free(b.err); dev_free(b.eu); dev_free(b.ev); dev_free(b.su); dev_free(b.sv);
-        dev_free(b.hslot); dev_free(b.rem[0]); dev_free(b.rem[1]); dev_free(b.sel); dev_free(b.esel);
-        dev_free(g->src_buf); dev_free(g->dst_buf);
+        dev_free(g, b.err); dev_free(g, b.eu); dev_free(g, b.ev); dev_free(g, b.su); dev_free(g, b.sv);
+        dev_free(g, b.hslot); dev_free(g, b.rem[0]); dev_free(g, b.rem[1]); dev_free(g, b.sel); dev_free(g, b.esel);
+        dev_free(g, g->src_buf); dev_free(g, g->dst_buf);
         dev_alloc(g, &b.err, c); dev_alloc(g, &b.eu, c); dev_alloc(g, &b.ev, c);
         dev_alloc(g, &b.su, c); dev_alloc(g, &b.sv, c); dev_alloc(g, &b.hslot, c);
         dev_alloc(g, &b.rem[0], c); dev_alloc(g, &b.rem[1], c); dev_alloc(g, &b.sel, c);
@@ -446,7 +498,7 @@ void ensure_batch(cm_graph *g, int64_t s) {
     }
     int64_t hc = next_pow2(std::max<int64_t>(2 * s, 1024));
     if (hc > g->hash_cap) {
-        dev_free(g->b.hkey); dev_free(g->b.hval);
+        dev_free(g, g->b.hkey); dev_free(g, g->b.hval);
         dev_alloc(g, &g->b.hkey, hc);
         dev_alloc(g, &g->b.hval, hc);
         g->hash_cap = (int32_t)hc;
@@ -457,7 +509,7 @@ void ensure_batch(cm_graph *g, int64_t s) {
     int64_t sc = 2 * s + g->g.pool_size / std::max(1, g->tune.chunk) + 1024;
     sc = std::min<int64_t>(sc, INT_MAX);
     if (sc > g->scan_cap) {
-        dev_free(g->b.scanq);
+        dev_free(g, g->b.scanq);
         dev_alloc(g, &g->b.scanq, sc);
         g->scan_cap = (int32_t)sc;
     }
@@ -492,21 +544,21 @@ void repack(cm_graph *g, int64_t extra) {
     dev_alloc(g, &newnbr, pool);
     if (g->tune.sublists) {
         // supporter lists live only within an iteration: nothing to copy
-        dev_free(g->g.sub);
+        dev_free(g, g->g.sub);
         dev_alloc(g, &g->g.sub, pool);
     }
     if (g->tune.uplists) {
         // every up-list is invalidated with the move (repack_finish)
-        dev_free(g->g.upl);
+        dev_free(g, g->g.upl);
         dev_alloc(g, &g->g.upl, pool);
     }
     HIPCHK(repack_copy(a, newoff, newnbr, g->grid_reg, st));
     HIPCHK(repack_finish(a, newoff, cnt, g->grid_reg, st));
     HIPCHK(fill_i32(cnt, 0, g->g.n_cap, st));
     HIPCHK(hipStreamSynchronize(st));
-    dev_free(caps64);
-    dev_free(newoff);
-    dev_free(g->g.nbr);
+    dev_free(g, caps64);
+    dev_free(g, newoff);
+    dev_free(g, g->g.nbr);
     g->g.nbr = newnbr;
     g->g.pool_size = pool;
     unsigned long long tail = (unsigned long long)total;
@@ -841,8 +893,8 @@ void program_execute(cm_graph *g, const std::vector<ProgBatch> &pb, const int32_
     const int32_t nb = (int32_t)pb.size();
     out.assign((size_t)nb, ProgOut{});
     if (nb > g->prog_cap) {
-        dev_free(g->d_pbatch);
-        dev_free(g->d_pout);
+        dev_free(g, g->d_pbatch);
+        dev_free(g, g->d_pout);
         int32_t c = std::max(nb, 64);
         dev_alloc(g, &g->d_pbatch, c);
         dev_alloc(g, &g->d_pout, c);
@@ -946,7 +998,7 @@ void stats_from_out(cm_graph *g, const ProgOut &o, int64_t items, int launches, 
 template <class T>
 void grow_dev(cm_graph *g, T *&p, int64_t &cap_io, int64_t need) {
     if (need <= cap_io && p) return;
-    dev_free(p);
+    dev_free(g, p);
     int64_t c = std::max<int64_t>(need, 1024);
     dev_alloc(g, &p, c);
     cap_io = c;
@@ -981,29 +1033,29 @@ void require_ready(cm_graph *g, bool need_cores) {
 
 void release_all(cm_graph *g) {
     DevGraph &d = g->g;
-    dev_free(d.off); dev_free(d.len); dev_free(d.cap); dev_free(d.nbr); dev_free(d.core);
-    dev_free(d.mcd); dev_free(d.stamp.p); dev_free(d.chg); d.cd.p = nullptr; dev_free(d.dec);
-    dev_free(d.done); dev_free(d.matched); dev_free(d.claim); dev_free(d.bmark); dev_free(d.gain);
-    dev_free(d.sub); dev_free(d.slen); dev_free(d.upl); dev_free(d.ubl);
+    dev_free(g, d.off); dev_free(g, d.len); dev_free(g, d.cap); dev_free(g, d.nbr); dev_free(g, d.core);
+    dev_free(g, d.mcd); dev_free(g, d.stamp.p); dev_free(g, d.chg); d.cd.p = nullptr; dev_free(g, d.dec);
+    dev_free(g, d.done); dev_free(g, d.matched); dev_free(g, d.claim); dev_free(g, d.bmark); dev_free(g, d.gain);
+    dev_free(g, d.sub); dev_free(g, d.slen); dev_free(g, d.upl); dev_free(g, d.ubl);
     DevBatch &b = g->b;
-    dev_free(b.err); dev_free(b.eu); dev_free(b.ev); dev_free(b.su); dev_free(b.sv);
-    dev_free(b.hslot); dev_free(b.rem[0]); dev_free(b.rem[1]); dev_free(b.sel); dev_free(b.esel);
-    dev_free(b.hkey); dev_free(b.hval); dev_free(b.vlist); dev_free(b.scanq); dev_free(b.reloc);
-    dev_free(b.reloc_off); dev_free(b.reloc_cap);
+    dev_free(g, b.err); dev_free(g, b.eu); dev_free(g, b.ev); dev_free(g, b.su); dev_free(g, b.sv);
+    dev_free(g, b.hslot); dev_free(g, b.rem[0]); dev_free(g, b.rem[1]); dev_free(g, b.sel); dev_free(g, b.esel);
+    dev_free(g, b.hkey); dev_free(g, b.hval); dev_free(g, b.vlist); dev_free(g, b.scanq); dev_free(g, b.reloc);
+    dev_free(g, b.reloc_off); dev_free(g, b.reloc_cap);
     DevQueues &q = g->q;
     for (int i = 0; i < 2; ++i) {
-        dev_free(q.fq[i]); dev_free(q.fh[i]); dev_free(q.eq[i]); dev_free(q.eh[i]);
+        dev_free(g, q.fq[i]); dev_free(g, q.fh[i]); dev_free(g, q.eq[i]); dev_free(g, q.eh[i]);
     }
-    dev_free(q.cand); dev_free(q.chg); dev_free(q.chh); dev_free(q.touched);
-    dev_free(q.aq[0]); dev_free(q.aq[1]);
-    dev_free(g->d_pbatch); dev_free(g->d_pout); dev_free(g->d_isrc); dev_free(g->d_idst);
-    dev_free(g->d_isub); dev_free(g->d_sub_bad);
+    dev_free(g, q.cand); dev_free(g, q.chg); dev_free(g, q.chh); dev_free(g, q.touched);
+    dev_free(g, q.aq[0]); dev_free(g, q.aq[1]);
+    dev_free(g, g->d_pbatch); dev_free(g, g->d_pout); dev_free(g, g->d_isrc); dev_free(g, g->d_idst);
+    dev_free(g, g->d_isub); dev_free(g, g->d_sub_bad);
     g->prog_cap = 0; g->items_cap = 0; g->sub_cap = 0;
     if (g->gexec) (void)hipGraphExecDestroy(g->gexec);
     if (g->graph) (void)hipGraphDestroy(g->graph);
     g->gexec = nullptr; g->graph = nullptr; g->graph_key.clear();
     // (the small scratch buffers allocated by cm_create stay until cm_destroy)
-    dev_free(g->src_buf); dev_free(g->dst_buf); dev_free(g->scan_tmp); dev_free(g->firstidx);
+    dev_free(g, g->src_buf); dev_free(g, g->dst_buf); dev_free(g, g->scan_tmp); dev_free(g, g->firstidx);
     g->g = DevGraph{};
     g->b = DevBatch{};
     g->q = DevQueues{};
@@ -1153,9 +1205,9 @@ void cm_destroy(cm_graph *g) {
     (void)hipStreamSynchronize(g->stream);
     serve_free(g);
     release_all(g);
-    dev_free(g->i64_scratch);
-    dev_free(g->u64_scratch);
-    dev_free(g->d_prog);
+    dev_free(g, g->i64_scratch);
+    dev_free(g, g->u64_scratch);
+    dev_free(g, g->d_prog);
     if (g->h_prog) (void)hipHostFree(g->h_prog);
     if (g->ctl) (void)hipFree(g->ctl);
     if (g->bar) (void)hipFree(g->bar);
@@ -1167,9 +1219,9 @@ void cm_destroy(cm_graph *g) {
         for (auto &e : pr)
             if (e) (void)hipEventDestroy(e);
     if (g->lout) (void)hipHostFree(g->lout);
-    dev_free(g->dl.sel);
-    dev_free(g->dl.chg);
-    dev_free(g->dl.n);
+    dev_free(g, g->dl.sel);
+    dev_free(g, g->dl.chg);
+    dev_free(g, g->dl.n);
     delete g;
 }
 
@@ -1181,6 +1233,7 @@ int cm_load_graph(cm_graph *g, int32_t n, int64_t m, const int32_t *src, const i
     if (g->serving) return CM_E_STATE;
     hipStream_t st = g->stream;
     try {
+        Reuse reuse(g);
         release_all(g);
         g->loaded = g->decomposed = false;
         g->m = 0;
@@ -1202,33 +1255,41 @@ int cm_load_graph(cm_graph *g, int32_t n, int64_t m, const int32_t *src, const i
             HIPCHK(hipMemcpyAsync(dd, dst, sizeof(int32_t) * (size_t)m, hipMemcpyHostToDevice, st));
         }
         int rc = CM_OK;
+        int32_t *pos = nullptr;  // the edges' places in their two lists
         if (m > 0) {
-            // range / self-loop / duplicate check
-            int64_t hc = next_pow2(2 * m);
+            // range / self-loop / duplicate check, list lengths and the
+            // edges' places in their lists, in one pass over the edges
+            const int64_t hc = next_pow2(2 * m);
             unsigned long long *hkey = nullptr;
-            int64_t *hval = nullptr;
             dev_alloc(g, &hkey, hc);
-            dev_alloc(g, &hval, hc);
+            dev_alloc(g, &pos, 2 * m);
             HIPCHK(fill_u64(hkey, ~0ull, hc, st));
-            HIPCHK(fill_i64(hval, INT64_MAX, hc, st));
             HIPCHK(fill_u64(g->u64_scratch, ~0ull, 1, st));
-            HIPCHK(load_check(ds, dd, m, n, hkey, hval, (uint32_t)(hc - 1), g->u64_scratch, st));
+            HIPCHK(load_count(ds, dd, m, n, hkey, (uint32_t)(hc - 1), g->g.len, pos, g->u64_scratch, st));
             HIPCHK(hipMemcpyAsync(g->hu64, g->u64_scratch, sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
             HIPCHK(hipStreamSynchronize(st));
-            dev_free(hkey);
-            dev_free(hval);
             unsigned long long fb = g->hu64[0];
             if (fb != ~0ull) {
-                rc = -(int)(fb & 0xff);
+                // something is wrong: find the first bad edge and its code
+                int64_t *hval = nullptr;
+                dev_alloc(g, &hval, hc);
+                HIPCHK(fill_u64(hkey, ~0ull, hc, st));
+                HIPCHK(fill_i64(hval, INT64_MAX, hc, st));
+                HIPCHK(fill_u64(g->u64_scratch, ~0ull, 1, st));
+                HIPCHK(load_check(ds, dd, m, n, hkey, hval, (uint32_t)(hc - 1), g->u64_scratch, st));
+                HIPCHK(hipMemcpyAsync(g->hu64, g->u64_scratch, sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
+                HIPCHK(hipStreamSynchronize(st));
+                dev_free(g, hval);
+                fb = g->hu64[0];
+                rc = fb == ~0ull ? CM_E_INTERNAL : -(int)(fb & 0xff);
                 g->err = std::string("invalid edge ") + std::to_string((long long)(fb >> 8)) + ": " +
                          cm_strerror(rc);
             }
+            dev_free(g, hkey);
         }
         if (rc == CM_OK) {
             // alive ids get core 0 until decomposed
             HIPCHK(fill_i32(g->g.core, 0, n, st));
-            HIPCHK(fill_i32(g->g.len, 0, g->g.n_cap, st));
-            if (m > 0) HIPCHK(count_deg(ds, dd, m, g->g.len, st));
             int64_t *caps64 = nullptr;
             dev_alloc(g, &caps64, g->g.n_cap);
             HIPCHK(caps_from_counts(g->g.len, n, g->g.n_cap, caps64, g->g.cap, st));
@@ -1236,15 +1297,14 @@ int cm_load_graph(cm_graph *g, int32_t n, int64_t m, const int32_t *src, const i
             int64_t total = 0;
             HIPCHK(hipMemcpyAsync(&total, g->i64_scratch, sizeof(int64_t), hipMemcpyDeviceToHost, st));
             HIPCHK(hipStreamSynchronize(st));
-            dev_free(caps64);
+            dev_free(g, caps64);
             int64_t pool = total + total / 4 + 4096;
             if (g->cfg.edge_capacity_hint > pool) pool = g->cfg.edge_capacity_hint;
             dev_alloc(g, &g->g.nbr, pool);
             if (g->tune.sublists) dev_alloc(g, &g->g.sub, pool);
             if (g->tune.uplists) dev_alloc(g, &g->g.upl, pool);
             g->g.pool_size = pool;
-            HIPCHK(fill_i32(g->g.len, 0, g->g.n_cap, st));
-            if (m > 0) HIPCHK(scatter_edges(ds, dd, m, g->g.off, g->g.len, g->g.nbr, st));
+            if (m > 0) HIPCHK(scatter_edges(ds, dd, m, g->g.off, pos, g->g.nbr, st));
             // control block
             HIPCHK(hipMemsetAsync(g->ctl, 0, sizeof(Ctl), st));
             unsigned long long tail = (unsigned long long)total;
@@ -1258,9 +1318,10 @@ int cm_load_graph(cm_graph *g, int32_t n, int64_t m, const int32_t *src, const i
             g->n_alive = n;
             g->loaded = true;
         }
+        dev_free(g, pos);
         if (own) {
-            dev_free(ds);
-            dev_free(dd);
+            dev_free(g, ds);
+            dev_free(g, dd);
         }
         if (rc != CM_OK) {
             release_all(g);
@@ -1494,7 +1555,7 @@ int cm_insert_vertices(cm_graph *g, int32_t c, const int64_t *off, const int32_t
             g->b.src_in = g->src_buf;
             g->b.dst_in = g->dst_buf;
         }
-        if (own_off) dev_free(doff);
+        if (own_off) dev_free(g, doff);
         if (total > 0 && g->cfg.mode == CM_MODE_PERSISTENT) {
             // one persistent launch: the new vertices enter as stars
             std::vector<ProgBatch> pb(1);
@@ -1574,7 +1635,7 @@ int cm_delete_vertices(cm_graph *g, int32_t c, const int32_t *ids, int on_device
             int64_t idx = (int64_t)(fb >> 8);
             if (stats) stats->first_bad = idx;
             if (g->cfg.strict) {
-                if (own) dev_free(dids);
+                if (own) dev_free(g, dids);
                 g->err = std::string("invalid vertex item ") + std::to_string((long long)idx) + ": " +
                          cm_strerror(code);
                 return finish(g, code, stats, t0);
@@ -1593,7 +1654,7 @@ int cm_delete_vertices(cm_graph *g, int32_t c, const int32_t *ids, int on_device
                 keep.push_back(x);
             }
             if (stats) stats->dropped = c - (int64_t)keep.size();
-            if (own) dev_free(dids);
+            if (own) dev_free(g, dids);
             dev_alloc(g, &dids, std::max<int64_t>(1, (int64_t)keep.size()));
             own = true;
             c = (int32_t)keep.size();
@@ -1626,12 +1687,12 @@ int cm_delete_vertices(cm_graph *g, int32_t c, const int32_t *ids, int on_device
                 stats->dropped = dropped_host;
             }
             if (out[0].status != 0) {
-                if (own) dev_free(dids);
+                if (own) dev_free(g, dids);
                 g->err = std::string("vertex deletion failed: ") + cm_strerror(out[0].status);
                 return finish(g, out[0].status, stats, t0);
             }
             g->m -= out[0].valid;
-            if (own) dev_free(dids);
+            if (own) dev_free(g, dids);
             g->n_alive -= c;
             return finish(g, CM_OK, stats, t0);
         }
@@ -1650,7 +1711,7 @@ int cm_delete_vertices(cm_graph *g, int32_t c, const int32_t *ids, int on_device
         KArgs a3 = make_args(g);
         HIPCHK(vdel_finish(a3, dids, c, st));
         HIPCHK(hipStreamSynchronize(st));
-        if (own) dev_free(dids);
+        if (own) dev_free(g, dids);
         g->n_alive -= c;
     } catch (const Fail &f) {
         return finish(g, f.code, stats, t0);
@@ -1716,7 +1777,7 @@ void serve_free(cm_graph *g) {
     g->sring = nullptr;
     g->sout = nullptr;
     g->ssrc = g->sdst = nullptr;
-    dev_free(g->d_bsub);
+    dev_free(g, g->d_bsub);
 }
 
 template <class T>
@@ -2178,8 +2239,8 @@ int cm_snapshot(cm_graph *g, const char *path) {
             HIPCHK(hipMemcpyAsync(xs.data(), dx, sizeof(int32_t) * (size_t)m, hipMemcpyDeviceToHost, st));
             HIPCHK(hipMemcpyAsync(ys.data(), dy, sizeof(int32_t) * (size_t)m, hipMemcpyDeviceToHost, st));
             HIPCHK(hipStreamSynchronize(st));
-            dev_free(dx);
-            dev_free(dy);
+            dev_free(g, dx);
+            dev_free(g, dy);
         }
         HIPCHK(hipStreamSynchronize(st));
         for (int32_t v = 0; v < n; ++v)
@@ -2387,8 +2448,8 @@ int cm_export_edges(cm_graph *g, int32_t *src, int32_t *dst, int64_t cap, int64_
         }
         HIPCHK(hipStreamSynchronize(st));
         if (own) {
-            dev_free(xs);
-            dev_free(ys);
+            dev_free(g, xs);
+            dev_free(g, ys);
         }
     } catch (const Fail &f) {
         return f.code;
@@ -2434,7 +2495,7 @@ int cm_run_batches(cm_graph *g, int32_t nb, const int32_t *kinds, const int64_t 
         const int32_t *ds = src, *dd = dst, *dsub = sub;
         if (!on_device && total > 0) {
             if (total > g->items_cap) {
-                dev_free(g->d_isrc); dev_free(g->d_idst); dev_free(g->d_isub);
+                dev_free(g, g->d_isrc); dev_free(g, g->d_idst); dev_free(g, g->d_isub);
                 int64_t c = std::max<int64_t>(total, 1024);
                 dev_alloc(g, &g->d_isrc, c);
                 dev_alloc(g, &g->d_idst, c);

@@ -17,11 +17,13 @@ int64_t scan_tmp_len(int64_t n);
 hipError_t load_check(const int32_t *src, const int32_t *dst, int64_t m, int32_t n,
                       unsigned long long *hkey, int64_t *hval, uint32_t mask,
                       unsigned long long *first_bad, hipStream_t st);
-hipError_t count_deg(const int32_t *src, const int32_t *dst, int64_t m, int32_t *len, hipStream_t st);
+hipError_t load_count(const int32_t *src, const int32_t *dst, int64_t m, int32_t n,
+                      unsigned long long *hkey, uint32_t mask, int32_t *len, int32_t *pos,
+                      unsigned long long *bad, hipStream_t st);
 hipError_t caps_from_counts(const int32_t *cnt, int32_t n, int32_t n_cap, int64_t *caps64,
                             int32_t *cap, hipStream_t st);
 hipError_t scatter_edges(const int32_t *src, const int32_t *dst, int64_t m, const int64_t *off,
-                         int32_t *len, int32_t *nbr, hipStream_t st);
+                         const int32_t *pos, int32_t *nbr, hipStream_t st);
 hipError_t count_live(const KArgs &a, int32_t *cnt, int blocks, hipStream_t st);
 hipError_t repack_copy(const KArgs &a, const int64_t *newoff, int32_t *newnbr, int blocks, hipStream_t st);
 hipError_t repack_finish(const KArgs &a, const int64_t *newoff, const int32_t *cnt, int blocks,

@@ -94,3 +94,33 @@ def test_hub_lists(deg, cfg):
             s.append(h - 1)
             d.append(h)
     _round_trip(hubs + hubs * deg, s, d, cut, cfg)
+
+
+def _cliques(sizes):
+    s, d, base = [], [], 0
+    for k in sizes:
+        i, j = np.triu_indices(k, 1)
+        s.append(base + i)
+        d.append(base + j)
+        base += k
+    return base, np.concatenate(s).astype(np.int32), np.concatenate(d).astype(np.int32)
+
+
+@pytest.mark.parametrize("bad,code", [((0, 1), cm.E_DUP), ((1, 0), cm.E_DUP), ((4, 4), cm.E_SELF_LOOP),
+                                      ((0, 99), cm.E_RANGE), ((-1, 3), cm.E_RANGE)])
+@pytest.mark.parametrize("where", [1, 20, -1])
+def test_load_rejects_and_loads_again(bad, code, where):
+    """A bad edge anywhere fails the load with its own code; the handle then
+    loads graphs of other sizes, larger and smaller, over each other."""
+    with cm.Graph() as g:
+        for sizes in ([12, 9], [40, 30, 3], [5]):
+            n, s, d = _cliques(sizes)
+            if sizes[0] == 12:
+                w = where if where >= 0 else len(s)
+                with pytest.raises(cm.CoreMaintError) as e:
+                    g.load(n, np.insert(s, w, bad[0]), np.insert(d, w, bad[1]))
+                assert e.value.status == code
+            for _ in range(2):
+                g.load(n, s, d)
+                g.decompose()
+                _check(g, oracle.DynamicGraph(n, s, d))

@@ -790,6 +790,18 @@ void run_maintenance(cm_graph *g, bool inserting, cm_batch_stats *stats) {
     }
 }
 
+// Whether a one-call vertex operation enters (leaves) with whole vertex stars,
+// in one program launch, or edge by edge as superior edge sets.  The edge
+// reduction takes one launch per set in the plain form, and a vertex of degree
+// d up to d sets: 1,000 vertices into an R-MAT 17 graph take 465 launches,
+// 108 ms, against 1.8 ms as stars (1,000 out: 327, 36 ms, against 4.0 ms), and
+// one vertex costs the same both ways (0.31 and 0.30 ms).  It stays for what
+// stars do not offer: the iteration log (a star is not a superior edge set)
+// and the one-edge regime.
+bool vertex_stars(const cm_graph *g) {
+    return g->cfg.mode == CM_MODE_PERSISTENT || (!g->cfg.debug && !g->cfg.single_edge && !g->cfg.async_steps);
+}
+
 // Shared body of edge insertion / deletion on staged device inputs.
 int64_t edge_batch(cm_graph *g, int64_t s, bool inserting, cm_batch_stats *stats, int64_t *dropped,
                    bool strict_override, bool strict_value, bool packed = false) {
@@ -1556,8 +1568,8 @@ int cm_insert_vertices(cm_graph *g, int32_t c, const int64_t *off, const int32_t
             g->b.dst_in = g->dst_buf;
         }
         if (own_off) dev_free(g, doff);
-        if (total > 0 && g->cfg.mode == CM_MODE_PERSISTENT) {
-            // one persistent launch: the new vertices enter as stars
+        if (total > 0 && vertex_stars(g)) {
+            // one program launch: the new vertices enter as stars
             std::vector<ProgBatch> pb(1);
             pb[0].off = 0;
             pb[0].s = (int32_t)total;
@@ -1667,8 +1679,8 @@ int cm_delete_vertices(cm_graph *g, int32_t c, const int32_t *ids, int on_device
             HIPCHK(hipStreamSynchronize(st));
             total = (int64_t)g->hu64[1];
         }
-        if (g->cfg.mode == CM_MODE_PERSISTENT && c > 0) {
-            // one persistent launch: the ids leave as stars
+        if (vertex_stars(g) && c > 0) {
+            // one program launch: the ids leave as stars
             ensure_batch(g, std::max<int64_t>(std::max<int64_t>(total, c), 1));
             std::vector<ProgBatch> pb(1);
             pb[0].off = 0;

@@ -106,6 +106,26 @@ def _cliques(sizes):
     return base, np.concatenate(s).astype(np.int32), np.concatenate(d).astype(np.int32)
 
 
+@pytest.mark.parametrize("mode", [cm.MODE_PLAIN, cm.MODE_PERSISTENT])
+def test_vertex_stars_filter_mode(mode):
+    """One-call vertex operations with invalid items, dropped one by one."""
+    rng = np.random.RandomState(5)
+    n, s, d = _cliques([12, 9, 30, 5])
+    off = np.array([0, 5, 5, 12, 15], np.int64)
+    nb = np.concatenate([[0, 3, 3, n + 50, 20], rng.permutation(n)[:7], [n, n + 2, 1]]).astype(np.int32)
+    with cm.Graph(mode=mode, strict=False) as g:
+        g.load(n, s, d)
+        g.decompose()
+        ref = oracle.DynamicGraph(n, s, d)
+        g.insert_vertices(off, nb)
+        ref.insert_vertices(off, nb, strict=False)
+        _check(g, ref)
+        ids = np.array([0, 13, 13, n + 1, n + 99, 2], np.int32)
+        g.delete_vertices(ids)
+        ref.delete_vertices(ids, strict=False)
+        _check(g, ref)
+
+
 @pytest.mark.parametrize("bad,code", [((0, 1), cm.E_DUP), ((1, 0), cm.E_DUP), ((4, 4), cm.E_SELF_LOOP),
                                       ((0, 99), cm.E_RANGE), ((-1, 3), cm.E_RANGE)])
 @pytest.mark.parametrize("where", [1, 20, -1])

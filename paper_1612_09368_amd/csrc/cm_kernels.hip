@@ -34,6 +34,7 @@ __global__ void k_ctl_batch_reset(Ctl *c, int cur) {
             c->fq_tail[j] = 0; c->fh_tail[j] = 0;
             c->eq_tail[j] = 0; c->eh_tail[j] = 0;
             c->rm_count[j] = 0; c->min_deg[j] = 0x7fffffff;
+            c->nr_count[j] = 0; c->nr_min[j] = 0x7fffffff;
         }
         c->cand_count = 0; c->chg_count = 0; c->chh_count = 0;
         c->touched_count = 0; c->changed_count = 0;
@@ -318,9 +319,9 @@ __global__ void k_export(KArgs a, int32_t *xs, int32_t *ys, int64_t cap, unsigne
 // ---------------------------------------------------------------------------
 // Decomposition
 // ---------------------------------------------------------------------------
+// Current degrees (live entries) and the "not yet peeled" mark.
 __global__ void k_dec_prep(KArgs a) {
     const DevGraph &g = a.g;
-    Ctl *c = a.ctl;
     // cores are recomputed from scratch: no up-list survives
     if (g.ubl)
         for (int32_t v = gtid(); v < g.n_cap; v += gthreads()) g.ubl[v] = -1;
@@ -331,19 +332,17 @@ __global__ void k_dec_prep(KArgs a) {
             int32_t d = 0;
             for (int32_t s = 0; s < L; ++s) d += p[s] >= 0;
             g.cd[v] = d;
+            g.core[v] = -2;
         },
         [&](int32_t v, int32_t L) {
             int32_t d = 0;
             wave_walk(g, v, 0, L, [&](int32_t w, int32_t) { d += w >= 0; });
             d = wave_sum(d);
-            if (lane() == 0) g.cd[v] = d;
+            if (lane() == 0) {
+                g.cd[v] = d;
+                g.core[v] = -2;
+            }
         });
-    for (int32_t base = gwave() * WAVE; base < g.n_ids; base += nwaves() * WAVE) {
-        int32_t v = base + lane();
-        bool alive = v < g.n_ids && g.core[v] != -1;
-        if (alive) g.core[v] = -2;
-        push_agg<int32_t>(a.q.fq[0], a.q.vcap, &c->rm_count[0], v, alive, &c->overflow);
-    }
 }
 
 __global__ void __launch_bounds__(COOP_THREADS) k_decompose(KArgs a) {

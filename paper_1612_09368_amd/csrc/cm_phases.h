@@ -2699,68 +2699,139 @@ __device__ __forceinline__ void run_server(const KArgs &a) {
 // Level k: every remaining vertex whose current degree is <= k gets core k
 // and is removed; removing a vertex lowers its remaining neighbours'
 // degrees, and a neighbour joins the level when its degree crosses from k+1
-// to k (exactly once).  Empty levels are skipped by jumping k to the
-// smallest remaining degree.  cd[] holds the current degree; core = -2 marks
-// "not yet peeled".  Remaining lists: q.fq[0..1] (counts rm_count, rotating
-// by sweep j); frontier: q.eq / q.eh (counts rotating by the frontier index
+// to k (exactly once).  cd[] holds the current degree; core = -2 marks "not
+// yet peeled".
+//
+// A level starts with a sweep for the vertices its predecessors left at
+// degree k.  A graph has far more levels than its vertices have core numbers
+// on average (Chung-Lu 10^6 / 10^7: 300 levels, half of the vertices gone
+// after 10), so the sweep does not read every remaining vertex: the remaining
+// vertices of degree below `top` form the near list, which each level sweeps,
+// and the others the far list, which is swept only when k reaches top (then
+// top moves up by an eighth of k, at least 8).  A vertex whose degree crosses
+// to top - 1 during a round joins the near list; one that is removed or joins
+// stays in the far list until its next sweep drops it.  Empty levels are
+// skipped by jumping k to the smallest degree.
+//
+// Far lists: q.fq[j & 1], counts rotating by the far sweep j (sweep 0 reads
+// every id).  Near lists: q.cand / q.touched by nj & 1, counts rotating by
+// nj (a sweep reads list nj and writes list nj + 1, which the rounds after it
+// append to).  Frontier: q.eq / q.eh (counts rotating by the frontier index
 // f: a step reads slot f%3, pushes slot (f+1)%3, clears slot (f+2)%3).
 // Runs as a step machine like the iterations: small sweeps and rounds run in
 // workgroup 0 alone.
 // ===========================================================================
-enum DecStep : int32_t { D_SWEEP = 0, D_ROUND, D_DONE };
+enum DecStep : int32_t { D_FAR = 0, D_NEAR, D_ROUND, D_DONE };
 
 struct DState {
     int32_t step;
-    int32_t k;   // level
-    int32_t j;   // sweep index
-    int32_t f;   // frontier slot index
+    int32_t k;    // level
+    int32_t j;    // far sweep index
+    int32_t f;    // frontier slot index
+    int32_t top;  // near list: degrees below this
+    int32_t nj;   // near list index
+    Snap sn;      // control counters (words 0 .. 63) as the last step left them
 };
+// The control block's first 64 words, which hold every counter of the
+// decomposition (one wave-wide load, as take_snap).
+static_assert(offsetof(Ctl, nr_min) + 12 <= 4 * WAVE, "decomposition counters must fit the snapshot");
+__device__ __forceinline__ Snap dec_snap(const Ctl *c) {
+    return Snap{ld_rlx(reinterpret_cast<const int32_t *>(c) + lane())};
+}
 
+__device__ __forceinline__ int32_t dec_top(int32_t k) { return k + (k / 8 > 8 ? k / 8 : 8); }
+
+// Sweep step (far or near): takes the vertices of degree <= k into the next
+// frontier.  Each wave takes SWEEP_STEPS x 64 entries at a time, loads them
+// together, and appends through its push buffers (one tail atomic per 64 or
+// more entries: returning atomics on one word serialise, about 11 ns each).
+constexpr int SWEEP_STEPS = 4;
 __device__ __forceinline__ void dec_sweep(const KArgs &a, const DState &st, const Team &T) {
     Ctl *c = a.ctl;
     const DevGraph &g = a.g;
-    const int s0 = st.j % 3, s1 = (st.j + 1) % 3, s2 = (st.j + 2) % 3;
+    const bool far = st.step == D_FAR;
     const int fn = (st.f + 1) % 3, fx = (st.f + 2) % 3, fb = (st.f + 1) & 1;
-    const int32_t n = qlen(&c->rm_count[s0], a.q.vcap);
+    const int f0 = st.j % 3, f1 = (st.j + 1) % 3, f2 = (st.j + 2) % 3;
+    const int n0 = st.nj % 3, n1 = (st.nj + 1) % 3, n2 = (st.nj + 2) % 3;
+    const int32_t *src = far ? (st.j == 0 ? nullptr : a.q.fq[st.j & 1]) : (st.nj & 1 ? a.q.touched : a.q.cand);
+    int32_t *nlist = (st.nj + 1) & 1 ? a.q.touched : a.q.cand;
+    int32_t *flist = a.q.fq[(st.j + 1) & 1];
+    const int32_t n = far ? (st.j == 0 ? g.n_ids : sqlen(st.sn, c, &c->rm_count[f0], a.q.vcap))
+                          : sqlen(st.sn, c, &c->nr_count[n0], a.q.vcap);
+    const int32_t top = far ? dec_top(st.k) : st.top;
     if (T.lead()) {
-        c->rm_count[s2] = 0;
-        c->min_deg[s2] = 0x7fffffff;
+        c->nr_count[n2] = 0;
+        c->nr_min[n2] = 0x7fffffff;
         c->eq_tail[fx] = 0; c->eh_tail[fx] = 0;
-    }
-    const int32_t *src = a.q.fq[st.j & 1];
-    int32_t *dst = a.q.fq[(st.j + 1) & 1];
-    int32_t mymin = 0x7fffffff;
-    for (int32_t base = T.wave() * WAVE; base < n; base += T.nwaves() * WAVE) {
-        int32_t idx = base + lane();
-        int32_t v = idx < n ? src[idx] : -1;
-        bool keep = false, take = false;
-        if (v >= 0 && g.core[v] == -2) {
-            int32_t d = g.cd[v];
-            if (d <= st.k) { g.core[v] = st.k; take = true; }
-            else { keep = true; mymin = d < mymin ? d : mymin; }
+        if (far) {
+            c->rm_count[f2] = 0;
+            c->min_deg[f2] = 0x7fffffff;
         }
-        push_vertex(a, a.q.eq[fb], &c->eq_tail[fn], a.q.eh[fb], &c->eh_tail[fn], v, take);
-        push_agg<int32_t>(dst, a.q.vcap, &c->rm_count[s1], v, keep, &c->overflow);
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        int32_t t = __shfl_xor(mymin, o);
-        mymin = t < mymin ? t : mymin;
+    WaveBuf bt = wave_buf(0), bn = wave_buf(1), bf = wave_buf(2);
+    int32_t fmin = 0x7fffffff, nmin = 0x7fffffff;
+    // fewer entries than that per wave: spread them
+    const int32_t share = (int32_t)(((int64_t)n + T.nwaves() - 1) / T.nwaves());
+    const int32_t span = share >= WAVE * SWEEP_STEPS ? WAVE * SWEEP_STEPS : ((share + WAVE - 1) / WAVE) * WAVE;
+    for (int32_t base = T.wave() * span; base < n; base += T.nwaves() * span) {
+        int32_t v[SWEEP_STEPS], cv[SWEEP_STEPS], dv[SWEEP_STEPS];
+#pragma unroll
+        for (int u = 0; u < SWEEP_STEPS; ++u) {
+            const int32_t i = base + u * WAVE + lane();
+            v[u] = -1;
+            if (u * WAVE < span && i < n) v[u] = src ? src[i] : i;
+        }
+#pragma unroll
+        for (int u = 0; u < SWEEP_STEPS; ++u) {
+            cv[u] = 0;
+            dv[u] = 0;
+            if (v[u] >= 0) {
+                cv[u] = g.core[v[u]];
+                dv[u] = g.cd[v[u]];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < SWEEP_STEPS; ++u) {
+            const bool live = cv[u] == -2;
+            const bool take = live && dv[u] <= st.k;
+            const bool near = live && !take && dv[u] < top;
+            const bool keep = live && far && dv[u] >= top;
+            if (take) g.core[v[u]] = st.k;
+            push_vertex_wb(a, bt, a.q.eq[fb], &c->eq_tail[fn], a.q.eh[fb], &c->eh_tail[fn], v[u], take);
+            wb_push(bn, nlist, a.q.vcap, &c->nr_count[n1], v[u], near, &c->overflow);
+            wb_push(bf, flist, a.q.vcap, &c->rm_count[f1], v[u], keep, &c->overflow);
+            if (near) nmin = dv[u] < nmin ? dv[u] : nmin;
+            if (keep) fmin = dv[u] < fmin ? dv[u] : fmin;
+        }
     }
-    if (lane() == 0 && mymin != 0x7fffffff) atomicMin(&c->min_deg[s1], mymin);
+    wb_flush(bt, a.q.eq[fb], a.q.vcap, &c->eq_tail[fn], &c->overflow);
+    wb_flush(bn, nlist, a.q.vcap, &c->nr_count[n1], &c->overflow);
+    wb_flush(bf, flist, a.q.vcap, &c->rm_count[f1], &c->overflow);
+    // smallest degrees (the maxima of their complements)
+    const int32_t nm = 0x7fffffff - __builtin_amdgcn_readlane(wave_incl_max(0x7fffffff - nmin), WAVE - 1);
+    const int32_t fm = 0x7fffffff - __builtin_amdgcn_readlane(wave_incl_max(0x7fffffff - fmin), WAVE - 1);
+    if (lane() == 0 && nm != 0x7fffffff) atomicMin(&c->nr_min[n1], nm);
+    if (lane() == 0 && fm != 0x7fffffff) atomicMin(&c->min_deg[f1], fm);
 }
 
+// A round's own continuation: the peel of a level is all thin cascades
+// (against 12 steps and 32 vertices: 10^6 random edges over 2^20 vertices 1.63
+// to 1.41 ms, R-MAT 22 15.7 to 15.2 ms).
+constexpr int DEC_DEEP = 48, DEC_WIDE = 63;
 __device__ __forceinline__ void dec_round(const KArgs &a, const DState &st, const Team &T, Acc &acc) {
     Ctl *c = a.ctl;
     const DevGraph &g = a.g;
     const int sc = st.f % 3, sn = (st.f + 1) % 3, sx = (st.f + 2) % 3;
     const int bc = st.f & 1, bn = bc ^ 1;
-    const int32_t nq = qlen(&c->eq_tail[sc], a.q.vcap);
-    const int32_t nh = qlen(&c->eh_tail[sc], a.q.hcap);
+    const int32_t nq = sqlen(st.sn, c, &c->eq_tail[sc], a.q.vcap);
+    const int32_t nh = sqlen(st.sn, c, &c->eh_tail[sc], a.q.hcap);
     if (T.lead()) {
         c->eq_tail[sx] = 0; c->eh_tail[sx] = 0;
         c->dec_rounds += 1;
     }
-    const int32_t k = st.k;
+    const int32_t k = st.k, top = st.top;
+    int32_t *nlist = st.nj & 1 ? a.q.touched : a.q.cand;
+    int32_t *ntail = &c->nr_count[st.nj % 3];
     auto s1 = [&](Ent &e) __attribute__((always_inline)) {
         e.a = -1;
         if (e.w >= 0) e.a = g.core[e.w];
@@ -2770,128 +2841,160 @@ __device__ __forceinline__ void dec_round(const KArgs &a, const DState &st, cons
         if (e.a == -2) e.b = atomicSub(&g.cd[e.w], 1);
     };
     auto s3 = [&](Ent &) __attribute__((always_inline)) {};
+    enum : int32_t { GONE = 1, NEAR = 2 };
     auto s4 = [&](Ent &e) __attribute__((always_inline)) {
-        e.a = e.b == k + 1 ? 1 : 0;
-        if (e.a) g.core[e.w] = k;
+        e.a = e.b == k + 1 ? GONE : (e.b == top ? NEAR : 0);
+        if (e.a == GONE) g.core[e.w] = k;
     };
     Pusher pq{wave_buf(0), wave_buf(3), a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn], g.len,
               a.t.large_deg, a.t.chunk};
+    WaveBuf bnear = wave_buf(1);
+    auto fin = [&](int32_t w, int32_t f) {
+        if (__ballot(f != 0) == 0ull) return;
+        push_deep(a, pq, w, f == GONE);
+        wb_push(bnear, nlist, a.q.vcap, ntail, w, f == NEAR, &c->overflow);
+    };
     for_chunks(T, a.q.eh[bc], nh, g, g.len, a.t.chunk, nullptr,
                [&](int32_t, int32_t lo, int32_t hi, int32_t, int32_t, int64_t o, int32_t) {
         if (lane() == 0) acc.scanned += hi - lo;
-        wave_walk_st(g.nbr + o, lo, hi, k, s1, s2, s3, s4,
-                     [&](int32_t w, int32_t f) { push_deep(a, pq, w, f != 0); });
+        wave_walk_st(g.nbr + o, lo, hi, k, s1, s2, s3, s4, fin);
     });
     for_batches_deep(T, a.q.eq[bc], nq, pq, [&](int32_t v, int32_t) {
         const int32_t L = v >= 0 ? g.len[v] : 0;
         acc.scanned += L;
-        return flat_walk_st(g.nbr, g, v, L, k, s1, s2, s3, s4,
-                            [&](int32_t, int32_t w, int32_t f, unsigned long long, int64_t, int32_t) {
-                                push_deep(a, pq, w, f != 0);
-                            });
-    });
+        return flat_walk_st(
+            g.nbr, g, v, L, k, s1, s2, s3, s4,
+            [&](int32_t, int32_t w, int32_t f, unsigned long long, int64_t, int32_t) { fin(w, f); });
+    }, DEC_DEEP, DEC_WIDE);
     push_done(a, pq);
+    wb_flush(bnear, nlist, a.q.vcap, ntail, &c->overflow);
 }
 
 __device__ __forceinline__ bool dec_block_local_ok(const KArgs &a, const DState &st, const Team &T) {
     if (st.step != D_ROUND) return true;
     Ctl *c = a.ctl;
     const int s = st.f % 3;
-    long long w = queue_work(a, T, a.q.eq[st.f & 1], qlen(&c->eq_tail[s], a.q.vcap),
-                             qlen(&c->eh_tail[s], a.q.hcap), 1, a.g.len);
+    long long w = queue_work(a, T, a.q.eq[st.f & 1], sqlen(st.sn, c, &c->eq_tail[s], a.q.vcap),
+                             sqlen(st.sn, c, &c->eh_tail[s], a.q.hcap), 1, a.g.len);
     return w <= a.t.local_work;
 }
 
-__device__ __forceinline__ int64_t dec_work(const KArgs &a, const DState &st) {
+// Sweeps of up to this many vertices run in workgroup 0 (8 entries per
+// thread, two groups of loads: less than a grid barrier).
+constexpr int32_t DEC_LOCAL_SWEEP = 4096;
+__device__ __forceinline__ bool dec_is_local(const KArgs &a, const DState &st) {
     Ctl *c = a.ctl;
-    if (st.step == D_SWEEP) return qlen(&c->rm_count[st.j % 3], a.q.vcap);
+    if (st.step == D_FAR)
+        return (st.j == 0 ? a.g.n_ids : sqlen(st.sn, c, &c->rm_count[st.j % 3], a.q.vcap)) <= DEC_LOCAL_SWEEP;
+    if (st.step == D_NEAR) return sqlen(st.sn, c, &c->nr_count[st.nj % 3], a.q.vcap) <= DEC_LOCAL_SWEEP;
     const int s = st.f % 3;
-    return frontier_work(a, qlen(&c->eq_tail[s], a.q.vcap), qlen(&c->eh_tail[s], a.q.hcap));
+    return frontier_work(a, sqlen(st.sn, c, &c->eq_tail[s], a.q.vcap), sqlen(st.sn, c, &c->eh_tail[s], a.q.hcap)) <= a.t.local_items;
 }
 
 __device__ __forceinline__ DState dec_next(const KArgs &a, const DState &st) {
     Ctl *c = a.ctl;
     DState nx = st;
-    if (st.step == D_SWEEP) {
-        nx.j = st.j + 1;
-        nx.f = st.f + 1;
-        const int fs = nx.f % 3;
-        if (uniform(ld_rlx(&c->eq_tail[fs]) + ld_rlx(&c->eh_tail[fs])) != 0) {
-            nx.step = D_ROUND;
-            return nx;
-        }
-        const int s1 = nx.j % 3;
-        if (uniform(ld_rlx(&c->rm_count[s1])) == 0) {
-            nx.step = D_DONE;
-            return nx;
-        }
-        const int32_t md = uniform(ld_rlx(&c->min_deg[s1]));
-        nx.k = md > st.k + 1 ? md : st.k + 1;
-        nx.step = D_SWEEP;
-        return nx;
-    }
-    // after a round
+    nx.sn = dec_snap(c);
     nx.f = st.f + 1;
+    if (st.step == D_FAR) {
+        nx.j = st.j + 1;
+        nx.top = dec_top(st.k);
+    }
+    if (st.step != D_ROUND) nx.nj = st.nj + 1;
     const int fs = nx.f % 3;
-    if (uniform(ld_rlx(&c->eq_tail[fs]) + ld_rlx(&c->eh_tail[fs])) != 0) {
+    const int32_t front = snap_word(nx.sn, c, &c->eq_tail[fs]) + snap_word(nx.sn, c, &c->eh_tail[fs]);
+    const int32_t near = snap_word(nx.sn, c, &c->nr_count[nx.nj % 3]);
+    const int32_t nmin = snap_word(nx.sn, c, &c->nr_min[nx.nj % 3]);
+    const int32_t fars = nx.j == 0 ? 1 : snap_word(nx.sn, c, &c->rm_count[nx.j % 3]);
+    const int32_t fmin = snap_word(nx.sn, c, &c->min_deg[nx.j % 3]);
+    if (front != 0) {
         nx.step = D_ROUND;
         return nx;
     }
+    // the level is done; smallest degrees of the lists are known right after
+    // a sweep that took nothing (no round has lowered them since)
     nx.k = st.k + 1;
-    nx.step = D_SWEEP;
+    if (st.step != D_ROUND && near != 0 && nmin > nx.k) nx.k = nmin;
+    if (near != 0 && nx.k < nx.top) {
+        nx.step = D_NEAR;
+    } else if (near == 0 && fars == 0) {
+        nx.step = D_DONE;
+    } else {
+        // no vertex below top is left (or the near list is spent): the far
+        // list's degrees are top or more
+        nx.k = nx.k > nx.top ? nx.k : nx.top;
+        if (st.step == D_FAR && near == 0 && fmin > nx.k) nx.k = fmin;
+        nx.step = D_FAR;
+    }
     return nx;
 }
 
 __device__ __forceinline__ void decompose(const KArgs &a, Acc &acc) {
     Ctl *c = a.ctl;
-    DState st{D_SWEEP, 0, 0, 0};
+    DState st{D_FAR, 0, 0, 0, 0, 0, dec_snap(c)};
     int pubs = 0;
     int32_t kmax = 0;
-    bool force = false;
+    bool force = false, chain = false;
+    unsigned long long tl = 0;
     while (st.step != D_DONE) {
-        if (bar_aborted(a.bar)) break;
-        int64_t work = dec_work(a, st);
-        if (force || work > a.t.local_items) {
+        bool grid = false, fg = false;
+        if (!chain) {
+            if (uniform(bar_aborted(a.bar) ? 1 : 0)) break;
+            grid = force || !dec_is_local(a, st);
             force = false;
-            if (st.step == D_SWEEP) dec_sweep(a, st, grid_team());
-            else { dec_round(a, st, grid_team(), acc); kmax = st.k; }
-            if (gtid() == 0) c->st_grid_steps += 1;
+            if (!grid && blockIdx.x == 0) {
+                chain = true;
+                tl = (unsigned long long)wall_clock64();
+            }
+        }
+        bool stop = !grid && !chain;  // the other workgroups wait for the chain's end
+        if (chain && !dec_block_local_ok(a, st, block_team())) {
+            fg = true;
+            stop = true;
+        }
+        if (!stop) {
+            const Team T = chain ? block_team() : grid_team();
+            if (st.step == D_ROUND) {
+                dec_round(a, st, T, acc);
+                kmax = st.k;
+            } else {
+                dec_sweep(a, st, T);
+            }
+            if (T.lead()) {
+                if (chain) c->st_local_steps += 1;
+                else c->st_grid_steps += 1;
+            }
+        }
+        if (grid) {
             gbar(a.bar);
             st = dec_next(a, st);
         } else {
-            const int slot = pubs & 1;
-            if (blockIdx.x == 0) {
-                const Team T = block_team();
-                bool fg = false;
-                const unsigned long long tl = (unsigned long long)wall_clock64();
-                for (;;) {
-                    if (!dec_block_local_ok(a, st, T)) { fg = true; break; }
-                    if (st.step == D_SWEEP) dec_sweep(a, st, T);
-                    else { dec_round(a, st, T, acc); kmax = st.k; }
-                    if (threadIdx.x == 0) c->st_local_steps += 1;
-                    __syncthreads();
-                    st = dec_next(a, st);
-                    if (st.step == D_DONE) break;
-                    if (dec_work(a, st) > a.t.local_items) break;
-                    if (slice_over(a.bar, tl)) break;
-                }
-                if (threadIdx.x == 0) {
-                    c->dpub[slot][0] = st.step;
-                    c->dpub[slot][1] = st.k;
-                    c->dpub[slot][2] = st.j;
-                    c->dpub[slot][3] = st.f;
-                    c->dpub[slot][4] = kmax;
-                    c->dpub[slot][5] = fg ? 1 : 0;
-                }
+            if (!stop) {
+                __syncthreads();
+                st = dec_next(a, st);
+                stop = st.step == D_DONE || !dec_is_local(a, st) || slice_over(a.bar, tl);
             }
-            gbar(a.bar);
-            st.step = uniform(ld_rlx(&c->dpub[slot][0]));
-            st.k = uniform(ld_rlx(&c->dpub[slot][1]));
-            st.j = uniform(ld_rlx(&c->dpub[slot][2]));
-            st.f = uniform(ld_rlx(&c->dpub[slot][3]));
-            kmax = uniform(ld_rlx(&c->dpub[slot][4]));
-            force = uniform(ld_rlx(&c->dpub[slot][5])) != 0;
-            ++pubs;
+            if (stop) {
+                const int slot = pubs & 1;
+                if (chain && threadIdx.x == 0) {
+                    int32_t *p = c->dpub[slot];
+                    p[0] = st.step; p[1] = st.k; p[2] = st.j; p[3] = st.f;
+                    p[4] = st.top; p[5] = st.nj; p[6] = kmax; p[7] = fg ? 1 : 0;
+                }
+                gbar(a.bar);
+                const int32_t w = lane() < 8 ? ld_rlx(&c->dpub[slot][lane()]) : 0;
+                st.step = __builtin_amdgcn_readlane(w, 0);
+                st.k = __builtin_amdgcn_readlane(w, 1);
+                st.j = __builtin_amdgcn_readlane(w, 2);
+                st.f = __builtin_amdgcn_readlane(w, 3);
+                st.top = __builtin_amdgcn_readlane(w, 4);
+                st.nj = __builtin_amdgcn_readlane(w, 5);
+                kmax = __builtin_amdgcn_readlane(w, 6);
+                force = __builtin_amdgcn_readlane(w, 7) != 0;
+                st.sn = dec_snap(c);
+                ++pubs;
+                chain = false;
+            }
         }
     }
     if (gtid() == 0) c->kmax = kmax;

@@ -377,13 +377,13 @@ __device__ __forceinline__ void for_batches(const Team &T, const int32_t *q, int
 constexpr int DEEP_STEPS = 12, DEEP_WIDTH = 32;
 template <class FB>
 __device__ __forceinline__ void for_batches_deep(const Team &T, const int32_t *q, int32_t n, Pusher &p,
-                                                 FB &&fb) {
+                                                 FB &&fb, int deep = DEEP_STEPS, int width = DEEP_WIDTH) {
     const int nw = T.nwaves();
     int per = (int)(((int64_t)n + nw - 1) / nw);
     per = per < 1 ? 1 : (per > WAVE ? WAVE : per);
     const int step = nw * per;
     int32_t base = T.wave() * per;
-    int32_t left = DEEP_STEPS;
+    int32_t left = deep;
     for (;;) {
         int32_t v = -1, limit = p.large;
         if (base < n) {
@@ -391,7 +391,7 @@ __device__ __forceinline__ void for_batches_deep(const Team &T, const int32_t *q
             if (lane() < per && i < n) v = q[i];
             base += step;
         } else {
-            if (left <= 0 || p.m.n + p.b.n == 0 || (p.m.n == 0 && p.b.n > DEEP_WIDTH)) break;
+            if (left <= 0 || p.m.n + p.b.n == 0 || (p.m.n == 0 && p.b.n > width)) break;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // other lanes' LDS writes come first
             if (p.m.n > 0) {
                 p.m.n -= 1;

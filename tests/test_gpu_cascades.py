@@ -106,6 +106,27 @@ def _cliques(sizes):
     return base, np.concatenate(s).astype(np.int32), np.concatenate(d).astype(np.int32)
 
 
+@pytest.mark.parametrize("sizes", [[2], [9, 10], [8, 9, 10, 17, 18, 19], [2, 200], [70, 71, 72, 80, 90, 300],
+                                   list(range(2, 60)), [3] * 1364 + [4], [3] * 1365 + [4], [2] * 2048 + [40]],
+                         ids=lambda x: f"{len(x)}cliques{max(x)}")
+def test_decompose_level_gaps(sizes):
+    """Cliques of chosen sizes: empty levels inside and past the near list's
+    window, and vertex counts around the sweeps that one workgroup runs."""
+    n, s, d = _cliques(sizes)
+    n += 1  # an isolated id
+    with cm.Graph() as g:
+        g.load(n, s, d)
+        g.decompose()
+        ref = oracle.DynamicGraph(n, s, d)
+        _check(g, ref)
+        # dead ids and tombstones, then from scratch again
+        gone = np.arange(0, n, 7, dtype=np.int32)
+        g.delete_vertices(gone)
+        ref.delete_vertices(gone)
+        g.decompose()
+        _check(g, ref)
+
+
 @pytest.mark.parametrize("mode", [cm.MODE_PLAIN, cm.MODE_PERSISTENT])
 def test_vertex_stars_filter_mode(mode):
     """One-call vertex operations with invalid items, dropped one by one."""

@@ -144,7 +144,7 @@ typedef struct cm_batch_stats {
     int64_t local_steps;    /* steps run inside one workgroup */
     int32_t launches;       /* maintenance kernel launches (plain mode: one per superior edge
                                set plus the empty one that ends the batch, queued before the
-                               host knew no edges were left) */
+                               host knew no edges were left; a batch of one edge has one) */
     int32_t graph_launch;   /* 1 when the launch was replayed from a hipGraph */
     int32_t group;          /* serving: requests that ran in one fused batch with this one
                                (1 = alone; the statistics above are the batch's) */

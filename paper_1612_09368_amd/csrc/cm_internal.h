@@ -103,6 +103,7 @@ struct Ctl {
     int32_t aq_head[2];           //   slots taken by consumers
     int32_t aq_pend[2];           //   items pushed and not finished
     unsigned long long one_key;   // single-edge regime: largest complemented claim key of the iteration
+    int32_t prep;                 // preparation inside a maintenance launch: PrepState
     int32_t sv_decision;          // serving: decision of the waiting thread
     ProgBatch sv_batch;           // serving: descriptor of the current batch
     int32_t sv_gn;                // serving: requests fused into the current batch
@@ -266,8 +267,13 @@ struct LaunchOut {
     int32_t rem_next;  // edges left for the next iteration
     int32_t overflow;  // queue overflow code (0 = none)
     int32_t aborted;   // a grid barrier wait gave up
-    int32_t pad[3];
+    int32_t prep;      // PrepState of a launch that prepares its batch (0 otherwise)
+    int32_t code;      // PREP_BAD: error code of the first invalid item
+    int32_t pad;
 };
+
+// How the preparation of a batch inside its first maintenance launch ended.
+enum PrepState : int32_t { PREP_OK = 0, PREP_SCAN = 1, PREP_COPY = 2, PREP_BAD = 3, PREP_POOL = 4, PREP_NONE = 5 };
 
 // Debug log of the iterations (cm_config.debug): every selected edge of an
 // edge iteration as (iteration stamp, u, v) with u < v, and every core change
@@ -295,6 +301,9 @@ struct KArgs {
     int32_t cur;         // remaining list that receives the validated batch
     int32_t strict;      // packed sub-batches: drop a sub-batch with an invalid item
     LaunchOut *lout;     // maintenance launch outcome (pinned host) or null
+    Ctl *mirror;         // pinned host copy of the control block, written at the launch's end
+    int32_t prep;        // 1: the launch validates and reserves its batch first (small batches)
+    int32_t compact;     // 1: the launch that runs the last iteration compacts the batch's lists
     DebugLog dl;         // iteration log (debug mode) or all null
 };
 

@@ -389,23 +389,55 @@ __global__ void k_res_gain(KArgs a) { res_gain(a, batch_of(a), grid_team()); }
 __global__ void k_res_alloc(KArgs a) { res_alloc(a, grid_team()); }
 __global__ void k_res_copy(KArgs a) { res_copy(a, grid_team()); }
 __global__ void k_del_compact(KArgs a) { del_compact(a, grid_team()); }
+// One launch of a batch's iterations: all of them (persistent form) or one
+// (plain form).  The first launch of a small batch also validates it and
+// reserves its room, and the launch that runs the last iteration of such a
+// deletion compacts its lists, so that the whole update is one launch in the
+// persistent form.  A launch that finds no edges left does not even meet at
+// a barrier.
 __global__ void __launch_bounds__(COOP_THREADS) k_maintain(KArgs a) {
+    Ctl *c = a.ctl;
+    int32_t ep = uniform(ld_rlx(&c->epoch));
+    if (!a.prep && a.max_iters == 1 && uniform(ld_rlx(&c->rem_count[(ep + 1) & 1])) == 0) {
+        // no launch running now changes these words
+        if (gtid() == 0 && a.lout) {
+            a.lout->epoch = ep;
+            a.lout->iters = 0;
+            a.lout->rem_next = 0;
+            a.lout->overflow = ld_rlx(&c->overflow);
+            a.lout->aborted = bar_aborted(a.bar) ? 1 : 0;
+            a.lout->prep = PREP_OK;
+        }
+        return;
+    }
     gbar_setup(a.bar);
-    int32_t ep = ld_rlx(&a.ctl->epoch);
     Acc acc{};
     int pubs = 0;
-    int n = run_iterations(a, a.inserting, a.max_iters, ep, acc, pubs);
-    flush_acc(a.ctl, acc);
+    const int prep = a.prep ? prep_small(a, batch_of(a)) : PREP_OK;
+    int n = 0;
+    if (prep == PREP_OK) n = run_iterations(a, a.inserting, a.max_iters, ep, acc, pubs);
+    // every step ended at a grid barrier, so the counters are final
+    const int32_t left = uniform(ld_rlx(&c->rem_count[(ep + 1) & 1]));
+    if (a.compact && n > 0 && left == 0 && !bar_aborted(a.bar)) del_compact(a, grid_team());
+    flush_acc(c, acc);
     if (gtid() == 0) {
-        a.ctl->epoch = ep;
-        a.ctl->iters_done = n;
-        if (a.lout) {
-            // every step ended at a grid barrier, so the counters are final
+        c->epoch = ep;
+        c->iters_done = n;
+    }
+    if (!a.mirror) return;
+    gbar(a.bar);  // the statistics of every workgroup are in
+    if (blockIdx.x == 0) {
+        const int32_t *src = reinterpret_cast<const int32_t *>(c);
+        int32_t *dst = reinterpret_cast<int32_t *>(a.mirror);
+        for (int i = threadIdx.x; i < (int)(sizeof(Ctl) / 4); i += blockDim.x) dst[i] = ld_rlx(src + i);
+        if (threadIdx.x == 0) {
             a.lout->epoch = ep;
             a.lout->iters = n;
-            a.lout->rem_next = ld_rlx(&a.ctl->rem_count[(ep + 1) & 1]);
-            a.lout->overflow = ld_rlx(&a.ctl->overflow);
+            a.lout->rem_next = prep == PREP_OK ? left : 0;
+            a.lout->overflow = ld_rlx(&c->overflow);
             a.lout->aborted = bar_aborted(a.bar) ? 1 : 0;
+            a.lout->prep = prep;
+            a.lout->code = prep == PREP_BAD ? a.b.err[ld_rlx(&c->first_bad)] : 0;
         }
     }
 }

@@ -2229,6 +2229,81 @@ __device__ __forceinline__ void prog_record(const KArgs &a, ProgOut &o, int32_t 
     o.hdeg = c->st_hdeg;
 }
 
+// Preparation of a small batch inside its first maintenance launch:
+// workgroup 0 resets the counters, clears the hash, validates and reserves,
+// workgroup barriers between the steps, while the others wait at one grid
+// barrier.  Only long work goes to the whole grid: a locate scan of more than
+// PREP_SCAN_ITEMS chunks (at most half of a wave's share each) and the copies
+// of more than PREP_COPY_LISTS moved lists.  Returns the PrepState, the same in
+// every thread: PREP_OK with the valid items in the remaining list; otherwise
+// nothing was applied and both remaining lists are empty.
+constexpr int32_t PREP_SCAN_ITEMS = 32, PREP_COPY_LISTS = 16;
+__device__ __forceinline__ int prep_small(const KArgs &a, const BatchCtx &bc) {
+    Ctl *c = a.ctl;
+    const Team T = block_team();
+    int32_t st = PREP_OK;
+    for (int part = 0; part < 2; ++part) {  // part 1: after a grid-wide locate scan
+        if (blockIdx.x == 0) {
+            if (part == 0) {
+                prog_reset_ctl(a, bc, T);
+                prog_clear_stats(a, T);
+                if (T.lead()) {
+                    c->overflow = 0;
+                    c->iters_done = 0;
+                    c->valid_count = 0;
+                }
+                for (int32_t i = T.rank; i < bc.s; i += T.size) a.b.esel[i] = 0;
+                __syncthreads();
+                val_canon(a, bc, T);
+                __syncthreads();
+                val_dup_mark(a, bc, T);
+                __syncthreads();
+            }
+            bool scanned = part == 1;
+            if (!scanned && qlen(&c->scan_tail, a.b.scap) <= PREP_SCAN_ITEMS) {
+                val_scan(a, bc, T);
+                __syncthreads();
+                scanned = true;
+            }
+            if (!scanned) {
+                st = PREP_SCAN;
+            } else {
+                val_final(a, bc, T);
+                __syncthreads();
+                const int32_t bad = uniform(ld_rlx(&c->first_bad));
+                const int32_t valid = qlen(&c->rem_count[bc.cur], a.b.cap);
+                __syncthreads();  // every wave has read the counters
+                st = bc.strict && bad != 0x7fffffff ? PREP_BAD : valid == 0 ? PREP_NONE : PREP_OK;
+                if (st == PREP_OK) {
+                    res_gain(a, bc, T);
+                    __syncthreads();
+                    if (bc.inserting) {
+                        res_alloc(a, T);
+                        __syncthreads();
+                        if (uniform(ld_rlx(&c->pool_fail))) st = PREP_POOL;
+                        else if (qlen(&c->reloc_count, a.g.n_cap) > PREP_COPY_LISTS) st = PREP_COPY;
+                        else res_copy(a, T);
+                    }
+                }
+                if (T.lead()) {
+                    c->valid_count = valid;
+                    // nothing runs: not by a launch queued behind either
+                    if (st > PREP_COPY) c->rem_count[bc.cur] = 0;
+                }
+            }
+            if (T.lead()) c->prep = st;
+        }
+        gbar(a.bar);
+        st = uniform(ld_rlx(&c->prep));
+        if (st == PREP_SCAN) val_scan(a, bc, grid_team());
+        else if (st == PREP_COPY) res_copy(a, grid_team());
+        else return st;
+        gbar(a.bar);
+        if (st == PREP_COPY) return PREP_OK;
+    }
+    return st;
+}
+
 // Validation and (insertion) capacity reservation of the edge batch bc.
 // Returns 1 when the adjacency pool ran out during the reservation (nothing
 // of the batch was applied), else 0; status / fb / valid describe the

@@ -165,3 +165,56 @@ def test_load_rejects_and_loads_again(bad, code, where):
                 g.load(n, s, d)
                 g.decompose()
                 _check(g, oracle.DynamicGraph(n, s, d))
+
+
+@pytest.mark.parametrize("strict", [True, False])
+@pytest.mark.parametrize("mode", [cm.MODE_PLAIN, cm.MODE_PERSISTENT])
+@pytest.mark.parametrize("s", [1, 2, 511, 513, 4095, 4096, 4097])
+def test_batch_sizes_around_fused_preparation(s, mode, strict):
+    """Batches at the edges of the sizes prepared inside their first launch:
+    hubs whose lists the locate scan reads (up to the whole grid's), lists that
+    must move, the pool repacked, invalid items first and last."""
+    rng = np.random.RandomState(s)
+    hubs, n = 6, 9000
+    keys = set()
+    for h in range(hubs):
+        for w in range(hubs, n, 1 + h):
+            keys.add((h, w))
+    base = np.array(sorted(keys), np.int32)
+    ref = oracle.DynamicGraph(n, base[:, 0], base[:, 1])
+    with cm.Graph(mode=mode, strict=strict) as g:
+        g.load(n, base[:, 0], base[:, 1])
+        g.decompose()
+        for rnd in range(3):
+            new = set()
+            while len(new) < s:
+                a, b = (rng.randint(hubs, 400), rng.randint(hubs, n)) if rnd != 1 else (rng.randint(hubs), rng.randint(n))
+                if a != b and (min(a, b), max(a, b)) not in keys:
+                    new.add((min(a, b), max(a, b)))
+                elif rnd == 1 and len(keys) + len(new) > hubs * n - hubs * hubs:
+                    break
+                elif rnd == 1 and rng.rand() < 0.2:
+                    new.add((int(rng.randint(hubs, 400)), int(rng.randint(400, n))))
+                    new -= keys
+            x = np.array(sorted(new), np.int32)
+            for bad in ((0, 0), (n, 1), tuple(base[0])):
+                for at in (0, len(x)):
+                    y = np.insert(x, at, bad, axis=0)
+                    st, stats = g.insert_edges(y[:, 0], y[:, 1], check=False)
+                    want = ref.insert_edges(y[:, 0].copy(), y[:, 1].copy(), strict=strict)
+                    assert st == want[0] and stats.first_bad == at
+                    _check(g, ref)
+                    if not strict:
+                        g.delete_edges(x[:, 0], x[:, 1])
+                        ref.delete_edges(x[:, 0].copy(), x[:, 1].copy())
+            g.insert_edges(x[:, 0], x[:, 1])
+            ref.insert_edges(x[:, 0].copy(), x[:, 1].copy())
+            _check(g, ref)
+            st, stats = g.delete_edges(np.append(x[:, 0], 0), np.append(x[:, 1], 1 if (0, 1) not in keys else 0), check=False)
+            want = ref.delete_edges(np.append(x[:, 0], 0), np.append(x[:, 1], 1 if (0, 1) not in keys else 0), strict=strict)
+            assert st == want[0] and stats.first_bad == len(x)
+            _check(g, ref)
+            if strict:
+                g.delete_edges(x[:, 0], x[:, 1])
+                ref.delete_edges(x[:, 0].copy(), x[:, 1].copy())
+                _check(g, ref)

@@ -574,16 +574,23 @@ __device__ __forceinline__ uint32_t hash_key(unsigned long long k) {
 
 // A team is the set of threads that shares one step: the whole grid or one
 // workgroup.  Loops stride by the team size; `lead` does the team's
-// bookkeeping.
+// bookkeeping.  The grid's waves are numbered across the workgroups first
+// (wave 0 of every workgroup, then wave 1, ..), so that a step with fewer
+// items than waves spreads over the CUs.
 struct Team {
     int rank;
     int size;
-    __device__ __forceinline__ int wave() const { return uniform(rank / WAVE); }
+    int wv;
+    __device__ __forceinline__ int wave() const { return uniform(wv); }
     __device__ __forceinline__ int nwaves() const { return size / WAVE; }
     __device__ __forceinline__ bool lead() const { return rank == 0; }
 };
-__device__ __forceinline__ Team grid_team() { return Team{gtid(), gthreads()}; }
-__device__ __forceinline__ Team block_team() { return Team{(int)threadIdx.x, (int)blockDim.x}; }
+__device__ __forceinline__ Team grid_team() {
+    return Team{gtid(), gthreads(), (int)((threadIdx.x / WAVE) * gridDim.x + blockIdx.x)};
+}
+__device__ __forceinline__ Team block_team() {
+    return Team{(int)threadIdx.x, (int)blockDim.x, (int)(threadIdx.x / WAVE)};
+}
 
 // Per-workgroup barrier state in LDS: XCC id, workgroups on that XCC,
 // XCCs in use (set by gbar_setup at the start of every cooperative kernel).
@@ -665,29 +672,34 @@ __device__ __forceinline__ void gbar_setup(Bar *b) {
     if (threadIdx.x == 0) {
         x = xcc_id();
         ep = __hip_atomic_load(&b->gen[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // the first workgroup of an XCC restarts its word at this epoch, then
+        // everyone adds one (a CAS per registration would retry for every
+        // other workgroup of the XCC)
         unsigned long long *r = &b->xreg[x * 16];
         unsigned long long old = __hip_atomic_load(r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        for (;;) {
-            const unsigned long long want = (old >> 32) == ep ? old + 1ull : ((ep << 32) | 1ull);
-            const unsigned long long prev = atomicCAS(r, old, want);
+        while ((old >> 32) != ep) {
+            const unsigned long long prev = atomicCAS(r, old, ep << 32);
             if (prev == old) break;
             old = prev;
         }
+        atomicAdd(r, 1ull);
     }
     gbar_any(b);
-    if (threadIdx.x == 0) {
+    if (threadIdx.x < WAVE) {
         // XCCs with workgroups of this launch (a slot never used reads 0 in
-        // both halves, so the epoch alone would not tell it apart at epoch 0)
-        unsigned ng = 0;
-        for (int y = 0; y < XSLOTS; ++y) {
-            const unsigned long long v =
-                __hip_atomic_load(&b->xreg[y * 16], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((v >> 32) == ep && (v & 0xffffffffull) != 0) ++ng;
+        // both halves, so the epoch alone would not tell it apart at epoch
+        // 0); lane y reads slot y
+        ep = (unsigned long long)(unsigned)uniform((int)ep);
+        x = (unsigned)uniform((int)x);
+        const unsigned long long v =
+            lane() < XSLOTS ? __hip_atomic_load(&b->xreg[lane() * 16], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
+        const bool used = lane() < XSLOTS && (v >> 32) == ep && (v & 0xffffffffull) != 0;
+        const unsigned ng = (unsigned)__popcll(__ballot(used));
+        if (lane() == (int)x) {
+            info[0] = x;
+            info[1] = (unsigned)(v & 0xffffffffull);
+            info[2] = ng;
         }
-        info[0] = x;
-        info[1] = (unsigned)(__hip_atomic_load(&b->xreg[x * 16], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) &
-                             0xffffffffull);
-        info[2] = ng;
     }
     __syncthreads();
 }

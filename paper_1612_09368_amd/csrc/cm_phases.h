@@ -24,17 +24,36 @@ __device__ __forceinline__ void flush_stat(unsigned long long *dst, long long v)
 // Per-thread statistics of a launch, kept in registers and summed into the
 // control block at the end of a batch: adjacency entries read by the
 // traversal phases, the list entries of the method's sets (insertion
-// candidates, evicted / peeled vertices, vertices whose core moved).  Every
-// thread must call flush_acc; it also flushes the phase clock and step
-// counts of global thread 0.
+// candidates, evicted / peeled vertices, vertices whose core moved), edges
+// selected.  Every thread must call flush_acc; the workgroup adds its sums
+// with one atomic each (one per wave took 2,048 turns on each word, over 20 us
+// a launch).  It also flushes the phase clock and step counts.
 struct Acc {
-    long long scanned, cdeg, edeg, hdeg;
+    long long scanned, cdeg, edeg, hdeg, sel;
 };
+constexpr int ACC_WORDS = 5;
 __device__ __forceinline__ void flush_acc(Ctl *c, Acc &acc) {
-    flush_stat(&c->st_scanned, acc.scanned);
-    flush_stat(&c->st_cdeg, acc.cdeg);
-    flush_stat(&c->st_edeg, acc.edeg);
-    flush_stat(&c->st_hdeg, acc.hdeg);
+    __shared__ unsigned long long sums[ACC_WORDS];
+    if (threadIdx.x < ACC_WORDS) sums[threadIdx.x] = 0ull;
+    __syncthreads();
+    const long long v[ACC_WORDS] = {acc.scanned, acc.cdeg, acc.edeg, acc.hdeg, acc.sel};
+#pragma unroll
+    for (int i = 0; i < ACC_WORDS; ++i) {
+        long long t = v[i];
+        if (__ballot(t != 0) == 0ull) continue;
+        for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o);
+        if (lane() == 0) atomicAdd(&sums[i], (unsigned long long)t);
+    }
+    __syncthreads();
+    if (threadIdx.x < ACC_WORDS && sums[threadIdx.x]) {
+        unsigned long long *dst = threadIdx.x == 0   ? &c->st_scanned
+                                  : threadIdx.x == 1 ? &c->st_cdeg
+                                  : threadIdx.x == 2 ? &c->st_edeg
+                                  : threadIdx.x == 3 ? &c->st_hdeg
+                                                     : &c->st_selected;
+        atomicAdd(dst, sums[threadIdx.x]);
+    }
+    __syncthreads();  // the sums are read before a later flush clears them
     ph_flush(c);
     acc = Acc{};
 }
@@ -277,9 +296,10 @@ __device__ __forceinline__ void val_scan(const KArgs &a, const BatchCtx &bc, con
 // the remaining list `cur`.  For packed independent batches the smallest
 // invalid item is kept per sub-batch and the emission waits for V5.
 __device__ __forceinline__ void val_final(const KArgs &a, const BatchCtx &bc, const Team &T) {
-    for (int32_t i = T.rank; i < bc.s; i += T.size) {
-        int32_t e = a.b.err[i];
-        if (!bc.inserting && e == 0 && (a.b.su[i] < 0 || a.b.sv[i] < 0)) {
+    WaveBuf b = wave_buf(0);
+    for_span(T, bc.s, [&](int32_t i) {
+        int32_t e = i >= 0 ? a.b.err[i] : 0;
+        if (i >= 0 && !bc.inserting && e == 0 && (a.b.su[i] < 0 || a.b.sv[i] < 0)) {
             e = ST_MISSING;
             a.b.err[i] = e;
         }
@@ -288,18 +308,21 @@ __device__ __forceinline__ void val_final(const KArgs &a, const BatchCtx &bc, co
             if (bc.sub)
                 atomicMin(&bc.sub_bad[bc.sub[i]], ((unsigned long long)i << 8) | (unsigned long long)(-e));
         }
-        push_agg<int32_t>(a.b.rem[bc.cur], a.b.cap, &a.ctl->rem_count[bc.cur], i, e == 0 && !bc.sub,
-                          &a.ctl->overflow);
-    }
+        wb_push(b, a.b.rem[bc.cur], a.b.cap, &a.ctl->rem_count[bc.cur], i, i >= 0 && e == 0 && !bc.sub,
+                &a.ctl->overflow);
+    });
+    wb_flush(b, a.b.rem[bc.cur], a.b.cap, &a.ctl->rem_count[bc.cur], &a.ctl->overflow);
 }
 
 // V5 (packed batches): emit the valid items; in strict mode a sub-batch with
 // an invalid item is dropped whole, the others go on.
 __device__ __forceinline__ void val_subfilter(const KArgs &a, const BatchCtx &bc, const Team &T) {
-    for (int32_t i = T.rank; i < bc.s; i += T.size) {
-        bool ok = a.b.err[i] == 0 && !(bc.strict && bc.sub_bad[bc.sub[i]] != ~0ull);
-        push_agg<int32_t>(a.b.rem[bc.cur], a.b.cap, &a.ctl->rem_count[bc.cur], i, ok, &a.ctl->overflow);
-    }
+    WaveBuf b = wave_buf(0);
+    for_span(T, bc.s, [&](int32_t i) {
+        const bool ok = i >= 0 && a.b.err[i] == 0 && !(bc.strict && bc.sub_bad[bc.sub[i]] != ~0ull);
+        wb_push(b, a.b.rem[bc.cur], a.b.cap, &a.ctl->rem_count[bc.cur], i, ok, &a.ctl->overflow);
+    });
+    wb_flush(b, a.b.rem[bc.cur], a.b.cap, &a.ctl->rem_count[bc.cur], &a.ctl->overflow);
 }
 
 // ===========================================================================
@@ -307,21 +330,26 @@ __device__ __forceinline__ void val_subfilter(const KArgs &a, const BatchCtx &bc
 // tombstone compaction after a deletion batch.
 // ===========================================================================
 
-__device__ __forceinline__ void mark_endpoint(const KArgs &a, const BatchCtx &bc, int32_t x) {
-    atomicAdd(&a.g.gain[x], 1);
-    bool first = atomicExch(&a.g.bmark[x], bc.bstamp + 1) != bc.bstamp + 1;
-    push_agg<int32_t>(a.b.vlist, a.g.n_cap, &a.ctl->vlist_count, x, first, &a.ctl->overflow);
-}
-
 // R1: per-vertex count of batch edges (gain) and the distinct endpoints.
 __device__ __forceinline__ void res_gain(const KArgs &a, const BatchCtx &bc, const Team &T) {
     const int32_t n = qlen(&a.ctl->rem_count[bc.cur], a.b.cap);
     const int32_t *R = a.b.rem[bc.cur];
-    for (int32_t idx = T.rank; idx < n; idx += T.size) {
-        int32_t i = R[idx];
-        mark_endpoint(a, bc, a.b.eu[i]);
-        mark_endpoint(a, bc, a.b.ev[i]);
-    }
+    WaveBuf b = wave_buf(0);
+    for_span(T, n, [&](int32_t idx) {
+        int32_t u = -1, v = -1, mu = 0, mv = 0;
+        if (idx >= 0) {
+            const int32_t i = R[idx];
+            u = a.b.eu[i];
+            v = a.b.ev[i];
+            atomicAdd(&a.g.gain[u], 1);
+            atomicAdd(&a.g.gain[v], 1);
+            mu = atomicExch(&a.g.bmark[u], bc.bstamp + 1);
+            mv = atomicExch(&a.g.bmark[v], bc.bstamp + 1);
+        }
+        wb_push(b, a.b.vlist, a.g.n_cap, &a.ctl->vlist_count, u, idx >= 0 && mu != bc.bstamp + 1, &a.ctl->overflow);
+        wb_push(b, a.b.vlist, a.g.n_cap, &a.ctl->vlist_count, v, idx >= 0 && mv != bc.bstamp + 1, &a.ctl->overflow);
+    });
+    wb_flush(b, a.b.vlist, a.g.n_cap, &a.ctl->vlist_count, &a.ctl->overflow);
 }
 
 // R2: a list that cannot take its gain moves to a spill block at the pool tail.
@@ -626,7 +654,7 @@ __device__ __forceinline__ void part_claim(const KArgs &a, const Iter &it, int r
 // tombstones, SD of its constrained endpoints, roots.  A constrained endpoint keeps at most one selected edge, so its SD
 // and root status depend on this edge alone.  Every lane may call it (sel
 // selects the applying lanes; pushes are wave-aggregated).
-__device__ __forceinline__ void apply_edge_insert(const KArgs &a, const Iter &it, int32_t i, bool sel) {
+__device__ __forceinline__ void apply_edge_insert(const KArgs &a, const Iter &it, int32_t i, bool sel, WaveBuf &bq) {
     Ctl *c = a.ctl;
     bool ru = false, rv = false;
     int32_t u = -1, v = -1;
@@ -658,12 +686,13 @@ __device__ __forceinline__ void apply_edge_insert(const KArgs &a, const Iter &it
         apush(a, 0, aq_item(AQ_V, u, 0), ru);
         apush(a, 0, aq_item(AQ_V, v, 0), rv);
     } else {
-        push_agg<int32_t>(a.q.fq[0], a.q.vcap, &c->fq_tail[0], u, ru, &c->overflow);
-        push_agg<int32_t>(a.q.fq[0], a.q.vcap, &c->fq_tail[0], v, rv, &c->overflow);
+        wb_push(bq, a.q.fq[0], a.q.vcap, &c->fq_tail[0], u, ru, &c->overflow);
+        wb_push(bq, a.q.fq[0], a.q.vcap, &c->fq_tail[0], v, rv, &c->overflow);
     }
 }
 
-__device__ __forceinline__ void apply_edge_delete(const KArgs &a, const Iter &it, int32_t i, bool sel) {
+__device__ __forceinline__ void apply_edge_delete(const KArgs &a, const Iter &it, int32_t i, bool sel, WaveBuf &bq,
+                                                  WaveBuf &bchg) {
     Ctl *c = a.ctl;
     bool pu = false, pv = false;
     int32_t u = -1, v = -1;
@@ -691,46 +720,57 @@ __device__ __forceinline__ void apply_edge_delete(const KArgs &a, const Iter &it
         apush_vertex(a, 1, AQ_CH, u, pu);
         apush_vertex(a, 1, AQ_CH, v, pv);
     } else {
-        push_vertex(a, a.q.eq[0], &c->eq_tail[0], a.q.eh[0], &c->eh_tail[0], u, pu);
-        push_vertex(a, a.q.eq[0], &c->eq_tail[0], a.q.eh[0], &c->eh_tail[0], v, pv);
+        push_vertex_wb(a, bq, a.q.eq[0], &c->eq_tail[0], a.q.eh[0], &c->eh_tail[0], u, pu);
+        push_vertex_wb(a, bq, a.q.eq[0], &c->eq_tail[0], a.q.eh[0], &c->eh_tail[0], v, pv);
     }
-    push_vertex(a, a.q.chg, &c->chg_count, a.q.chh, &c->chh_count, u, pu);
-    push_vertex(a, a.q.chg, &c->chg_count, a.q.chh, &c->chh_count, v, pv);
+    push_vertex_wb(a, bchg, a.q.chg, &c->chg_count, a.q.chh, &c->chh_count, u, pu);
+    push_vertex_wb(a, bchg, a.q.chg, &c->chg_count, a.q.chh, &c->chh_count, v, pv);
 }
 
-__device__ __forceinline__ void part_select(const KArgs &a, const Iter &it, int r, const Team &T) {
+__device__ __forceinline__ void part_select(const KArgs &a, const Iter &it, int r, const Team &T, Acc &acc) {
     Ctl *c = a.ctl;
     const bool last = r == a.t.rounds - 1;
     const int32_t *R = a.b.rem[it.cur];
     const unsigned long long hi = claim_hi(it.ep, a.t.rounds, r);
     const uint32_t mstamp = matched_stamp(it.ep, a.t.rounds, r);
-    for (int32_t idx = T.rank; idx < it.n_r; idx += T.size) {
-        int32_t i = R[idx];
-        if (r > 0 && a.b.esel[i] == it.ep) continue;  // taken in an earlier round
-        int32_t u = a.b.eu[i], v = a.b.ev[i];
-        int32_t cu = a.g.core[u], cv = a.g.core[v];
-        int32_t k = cu < cv ? cu : cv;
-        bool fu = cu == k, fv = cv == k;
-        bool part = !(r > 0 && ((fu && matched_before(a.g.matched[u], it.ep, a.t.rounds, r)) ||
-                                (fv && matched_before(a.g.matched[v], it.ep, a.t.rounds, r))));
-        unsigned long long key = hi | mix32((uint32_t)i);
-        bool win = a.t.single_edge ? ld_rlx64(&a.ctl->one_key) == ~key
-                                   : part && (!fu || a.g.claim[u] == key) && (!fv || a.g.claim[v] == key);
-        if (win) {
-            a.b.esel[i] = it.ep;
-            if (fu) a.g.matched[u] = mstamp;
-            if (fv) a.g.matched[v] = mstamp;
+    // Roots, moved vertices and the edges left are pushed through the wave's
+    // buffers: a tail atomic per wave and push bound this step (10^5 edges:
+    // 28 us a step, the 64-graph pool's 46 us).
+    WaveBuf bq = wave_buf(0), bchg = wave_buf(1), brem = wave_buf(2);
+    for_span(T, it.n_r, [&](int32_t idx) {
+        const int32_t i = idx >= 0 ? R[idx] : -1;
+        const bool open = i >= 0 && !(r > 0 && a.b.esel[i] == it.ep);  // not taken in an earlier round
+        int32_t u = -1, v = -1;
+        bool win = false;
+        if (open) {
+            u = a.b.eu[i];
+            v = a.b.ev[i];
+            const int32_t cu = a.g.core[u], cv = a.g.core[v];
+            const int32_t k = cu < cv ? cu : cv;
+            const bool fu = cu == k, fv = cv == k;
+            const bool part = !(r > 0 && ((fu && matched_before(a.g.matched[u], it.ep, a.t.rounds, r)) ||
+                                          (fv && matched_before(a.g.matched[v], it.ep, a.t.rounds, r))));
+            const unsigned long long key = hi | mix32((uint32_t)i);
+            win = a.t.single_edge ? ld_rlx64(&a.ctl->one_key) == ~key
+                                  : part && (!fu || a.g.claim[u] == key) && (!fv || a.g.claim[v] == key);
+            if (win) {
+                a.b.esel[i] = it.ep;
+                if (fu) a.g.matched[u] = mstamp;
+                if (fv) a.g.matched[v] = mstamp;
+                acc.sel += 1;
+            }
         }
         if (a.dl.sel) dbg_put(a.dl.sel, &a.dl.n[0], a.dl.cap, win, it.ep, u, v);
         // a winner applies itself in this step (no separate apply step)
-        if (it.ins) apply_edge_insert(a, it, i, win);
-        else apply_edge_delete(a, it, i, win);
-        const unsigned long long wm = __ballot(win);
-        if (wm && lane() == __ffsll((long long)__ballot(1)) - 1)
-            atomicAdd(&c->st_selected, (unsigned long long)__popcll(wm));
-        push_agg<int32_t>(a.b.rem[it.cur ^ 1], a.b.cap, &c->rem_count[it.cur ^ 1], i, last && !win,
-                          &c->overflow);
-    }
+        if (it.ins) apply_edge_insert(a, it, i, win, bq);
+        else apply_edge_delete(a, it, i, win, bq, bchg);
+        wb_push(brem, a.b.rem[it.cur ^ 1], a.b.cap, &c->rem_count[it.cur ^ 1], i, last && open && !win,
+                &c->overflow);
+    });
+    int32_t *q = it.ins ? a.q.fq[0] : a.q.eq[0];
+    wb_flush(bq, q, a.q.vcap, it.ins ? &c->fq_tail[0] : &c->eq_tail[0], &c->overflow);
+    wb_flush(bchg, a.q.chg, a.q.vcap, &c->chg_count, &c->overflow);
+    wb_flush(brem, a.b.rem[it.cur ^ 1], a.b.cap, &c->rem_count[it.cur ^ 1], &c->overflow);
 }
 
 // Insert the selected set into G (Algorithm 1) and update SD of the
@@ -1746,23 +1786,32 @@ __device__ __forceinline__ void apply_core(const KArgs &a, const Iter &it, const
             c->st_candidates += (unsigned long long)n;
             c->st_icand += (unsigned long long)n;
         }
-        for (int32_t idx = T.rank; idx < n; idx += T.size) {
-            int32_t v = a.q.cand[idx];
-            int32_t k = g.core[v];
-            bool up = g.cd[v] > k;
-            const int32_t L = g.len[v];
-            cdeg += L;
-            if (up) hdeg += L;
-            else edeg += L;
-            if (up) {
-                g.core[v] = k + 1;
-                g.chg[v] = it.ep;
-                g.mcd[v] = 0;
+        WaveBuf b = wave_buf(0);
+        int32_t moved = 0;  // uniform
+        for_span(T, n, [&](int32_t idx) {
+            int32_t v = -1, k = 0, L = 0;
+            bool up = false;
+            if (idx >= 0) {
+                v = a.q.cand[idx];
+                k = g.core[v];
+                L = g.len[v];
+                up = g.cd[v] > k;
+                cdeg += L;
+                if (up) hdeg += L;
+                else edeg += L;
+                if (up) {
+                    g.core[v] = k + 1;
+                    g.chg[v] = it.ep;
+                    g.mcd[v] = 0;
+                }
             }
             if (a.dl.chg) dbg_put(a.dl.chg, &a.dl.n[1], a.dl.cap, up, it.ep, v, k + 1);
-            count_agg(&c->changed_count, up);
-            push_vertex(a, a.q.chg, &c->chg_count, a.q.chh, &c->chh_count, v, up);
-        }
+            moved += __popcll(__ballot(up));
+            push_vertex_wb_len(a, b, a.q.chg, &c->chg_count, a.q.chh, &c->chh_count, v, L, up, a.t.large_deg,
+                               a.t.chunk);
+        });
+        wb_flush(b, a.q.chg, a.q.vcap, &c->chg_count, &c->overflow);
+        if (moved && lane() == 0) atomicAdd(&c->changed_count, moved);
     } else {
         const int32_t n = sqlen(it.sn, c, &c->chg_count, a.q.vcap);
         const int32_t nt = sqlen(it.sn, c, &c->touched_count, a.q.vcap);
@@ -2007,7 +2056,7 @@ __device__ __forceinline__ void run_step(const KArgs &a, const Iter &it, const P
         break;
     case S_SELECT:
         if (it.sc.mode) star_select(a, it, T);
-        else part_select(a, it, pc.r, T);
+        else part_select(a, it, pc.r, T, acc);
         break;
     case S_APPLY:  // vertex stars only: edge sets apply inside the select step
         if (it.sc.mode == 1) star_apply_insert(a, it, T);
@@ -2820,7 +2869,7 @@ __device__ __forceinline__ int32_t dec_top(int32_t k) { return k + (k / 8 > 8 ? 
 // frontier.  Each wave takes SWEEP_STEPS x 64 entries at a time, loads them
 // together, and appends through its push buffers (one tail atomic per 64 or
 // more entries: returning atomics on one word serialise, about 11 ns each).
-constexpr int SWEEP_STEPS = 4;
+constexpr int SWEEP_STEPS = SPAN_STEPS;
 __device__ __forceinline__ void dec_sweep(const KArgs &a, const DState &st, const Team &T) {
     Ctl *c = a.ctl;
     const DevGraph &g = a.g;
@@ -2845,9 +2894,7 @@ __device__ __forceinline__ void dec_sweep(const KArgs &a, const DState &st, cons
     }
     WaveBuf bt = wave_buf(0), bn = wave_buf(1), bf = wave_buf(2);
     int32_t fmin = 0x7fffffff, nmin = 0x7fffffff;
-    // fewer entries than that per wave: spread them
-    const int32_t share = (int32_t)(((int64_t)n + T.nwaves() - 1) / T.nwaves());
-    const int32_t span = share >= WAVE * SWEEP_STEPS ? WAVE * SWEEP_STEPS : ((share + WAVE - 1) / WAVE) * WAVE;
+    const int32_t span = wave_span(n);
     for (int32_t base = T.wave() * span; base < n; base += T.nwaves() * span) {
         int32_t v[SWEEP_STEPS], cv[SWEEP_STEPS], dv[SWEEP_STEPS];
 #pragma unroll

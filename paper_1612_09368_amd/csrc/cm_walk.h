@@ -168,6 +168,29 @@ __device__ __forceinline__ void push_vertex_wb(const KArgs &a, WaveBuf &b, int32
     push_vertex_wb_len(a, b, vq, vtail, hq, htail, w, pred ? a.g.len[w] : 0, pred, a.t.large_deg, a.t.chunk);
 }
 
+// Team-stride over 0 .. n-1 by whole waves: f(i) runs on every lane (i < 0
+// past the end), so that it may use wave votes and wave buffers.  A wave takes
+// up to SPAN_STEPS steps in a row, fewer when that would leave under 256 waves
+// at work: each wave then moves its pushes with one tail atomic or few, and the
+// atomics of all waves on one tail (11 ns each, one after another) stay below
+// a barrier's time.
+constexpr int SPAN_STEPS = 4;
+__device__ __forceinline__ int32_t wave_span(int32_t n) {
+    const int32_t per = ((n + 255) / 256 + WAVE - 1) / WAVE;  // steps per wave for 256 waves
+    return (per < 1 ? 1 : per > SPAN_STEPS ? SPAN_STEPS : per) * WAVE;
+}
+template <class F>
+__device__ __forceinline__ void for_span(const Team &T, int32_t n, F &&f) {
+    const int32_t span = wave_span(n);
+    for (int32_t base = T.wave() * span; base < n; base += T.nwaves() * span) {
+#pragma unroll 1
+        for (int32_t o = 0; o < span && base + o < n; o += WAVE) {
+            const int32_t i = base + o + lane();
+            f(i < n ? i : -1);
+        }
+    }
+}
+
 // Team-stride over the implicit identity list 0..n-1 (whole-graph passes).
 // fl(v, L) runs on the owning lane for lists of length <= small; fw(v, L)
 // runs on the whole wave (uniform) for the others, of any length.

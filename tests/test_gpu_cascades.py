@@ -218,3 +218,18 @@ def test_batch_sizes_around_fused_preparation(s, mode, strict):
                 g.delete_edges(x[:, 0], x[:, 1])
                 ref.delete_edges(x[:, 0].copy(), x[:, 1].copy())
                 _check(g, ref)
+
+
+@pytest.mark.parametrize("mode", [cm.MODE_PLAIN, cm.MODE_PERSISTENT])
+@pytest.mark.parametrize("s", [16384, 16385, 65536, 65537, 150001])
+def test_batch_sizes_around_wave_spans(s, mode):
+    """Batches at the edges of the runs a wave takes in the partition,
+    validation and reservation steps."""
+    rng = np.random.RandomState(s)
+    n = 20000
+    u, v = rng.randint(0, n, 400000), rng.randint(0, n, 400000)
+    keys = np.unique((np.minimum(u, v) * n + np.maximum(u, v))[u != v])
+    rng.shuffle(keys)
+    first, batch = keys[:60000], keys[60000:60000 + s]
+    _round_trip(n, *(x.astype(np.int32) for x in divmod(np.concatenate([first, batch]), n)),
+                np.stack(divmod(batch, n), 1), dict(mode=mode))

@@ -654,7 +654,7 @@ __device__ __forceinline__ void part_claim(const KArgs &a, const Iter &it, int r
 // tombstones, SD of its constrained endpoints, roots.  A constrained endpoint keeps at most one selected edge, so its SD
 // and root status depend on this edge alone.  Every lane may call it (sel
 // selects the applying lanes; pushes are wave-aggregated).
-__device__ __forceinline__ void apply_edge_insert(const KArgs &a, const Iter &it, int32_t i, bool sel, WaveBuf &bq) {
+__device__ __forceinline__ void apply_edge_insert(const KArgs &a, const Iter &it, int32_t i, bool sel, VStream &bq) {
     Ctl *c = a.ctl;
     bool ru = false, rv = false;
     int32_t u = -1, v = -1;
@@ -686,13 +686,13 @@ __device__ __forceinline__ void apply_edge_insert(const KArgs &a, const Iter &it
         apush(a, 0, aq_item(AQ_V, u, 0), ru);
         apush(a, 0, aq_item(AQ_V, v, 0), rv);
     } else {
-        wb_push(bq, a.q.fq[0], a.q.vcap, &c->fq_tail[0], u, ru, &c->overflow);
-        wb_push(bq, a.q.fq[0], a.q.vcap, &c->fq_tail[0], v, rv, &c->overflow);
+        vs_push(a, bq, u, ru);
+        vs_push(a, bq, v, rv);
     }
 }
 
-__device__ __forceinline__ void apply_edge_delete(const KArgs &a, const Iter &it, int32_t i, bool sel, WaveBuf &bq,
-                                                  WaveBuf &bchg) {
+__device__ __forceinline__ void apply_edge_delete(const KArgs &a, const Iter &it, int32_t i, bool sel, VStream &bq,
+                                                  CStream &bh, VStream &bchg, CStream &bchh) {
     Ctl *c = a.ctl;
     bool pu = false, pv = false;
     int32_t u = -1, v = -1;
@@ -716,15 +716,16 @@ __device__ __forceinline__ void apply_edge_delete(const KArgs &a, const Iter &it
             if (m < k) { a.g.stamp[v] = it.ep; pv = true; }
         }
     }
+    const int32_t Lu = pu ? a.g.len[u] : 0, Lv = pv ? a.g.len[v] : 0;
     if (a.t.async_steps) {
         apush_vertex(a, 1, AQ_CH, u, pu);
         apush_vertex(a, 1, AQ_CH, v, pv);
     } else {
-        push_vertex_wb(a, bq, a.q.eq[0], &c->eq_tail[0], a.q.eh[0], &c->eh_tail[0], u, pu);
-        push_vertex_wb(a, bq, a.q.eq[0], &c->eq_tail[0], a.q.eh[0], &c->eh_tail[0], v, pv);
+        push_len(a, bq, bh, u, Lu, pu, a.t.large_deg);
+        push_len(a, bq, bh, v, Lv, pv, a.t.large_deg);
     }
-    push_vertex_wb(a, bchg, a.q.chg, &c->chg_count, a.q.chh, &c->chh_count, u, pu);
-    push_vertex_wb(a, bchg, a.q.chg, &c->chg_count, a.q.chh, &c->chh_count, v, pv);
+    push_len(a, bchg, bchh, u, Lu, pu, a.t.large_deg);
+    push_len(a, bchg, bchh, v, Lv, pv, a.t.large_deg);
 }
 
 __device__ __forceinline__ void part_select(const KArgs &a, const Iter &it, int r, const Team &T, Acc &acc) {
@@ -733,10 +734,14 @@ __device__ __forceinline__ void part_select(const KArgs &a, const Iter &it, int 
     const int32_t *R = a.b.rem[it.cur];
     const unsigned long long hi = claim_hi(it.ep, a.t.rounds, r);
     const uint32_t mstamp = matched_stamp(it.ep, a.t.rounds, r);
-    // Roots, moved vertices and the edges left are pushed through the wave's
-    // buffers: a tail atomic per wave and push bound this step (10^5 edges:
-    // 28 us a step, the 64-graph pool's 46 us).
-    WaveBuf bq = wave_buf(0), bchg = wave_buf(1), brem = wave_buf(2);
+    // Roots, moved vertices and the edges left are pushed through buffers: a
+    // tail atomic per wave and push bound this step (10^5 edges: 28 us a step
+    // against 18, the 64-graph pool's 46 against 29).
+    VStream bq{wave_buf(0), it.ins ? a.q.fq[0] : a.q.eq[0], it.ins ? &c->fq_tail[0] : &c->eq_tail[0]};
+    VStream bchg{wave_buf(1), a.q.chg, &c->chg_count};
+    VStream brem{wave_buf(2), a.b.rem[it.cur ^ 1], &c->rem_count[it.cur ^ 1]};
+    CStream bh{wave_buf(3), a.q.eh[0], &c->eh_tail[0], a.g.len, a.t.chunk};
+    CStream bchh{wave_buf(4), a.q.chh, &c->chh_count, a.g.len, a.t.chunk};
     for_span(T, it.n_r, [&](int32_t idx) {
         const int32_t i = idx >= 0 ? R[idx] : -1;
         const bool open = i >= 0 && !(r > 0 && a.b.esel[i] == it.ep);  // not taken in an earlier round
@@ -763,14 +768,14 @@ __device__ __forceinline__ void part_select(const KArgs &a, const Iter &it, int 
         if (a.dl.sel) dbg_put(a.dl.sel, &a.dl.n[0], a.dl.cap, win, it.ep, u, v);
         // a winner applies itself in this step (no separate apply step)
         if (it.ins) apply_edge_insert(a, it, i, win, bq);
-        else apply_edge_delete(a, it, i, win, bq, bchg);
-        wb_push(brem, a.b.rem[it.cur ^ 1], a.b.cap, &c->rem_count[it.cur ^ 1], i, last && open && !win,
-                &c->overflow);
+        else apply_edge_delete(a, it, i, win, bq, bh, bchg, bchh);
+        wb_push(brem.b, brem.q, a.b.cap, brem.tail, i, last && open && !win, &c->overflow);
     });
-    int32_t *q = it.ins ? a.q.fq[0] : a.q.eq[0];
-    wb_flush(bq, q, a.q.vcap, it.ins ? &c->fq_tail[0] : &c->eq_tail[0], &c->overflow);
-    wb_flush(bchg, a.q.chg, a.q.vcap, &c->chg_count, &c->overflow);
-    wb_flush(brem, a.b.rem[it.cur ^ 1], a.b.cap, &c->rem_count[it.cur ^ 1], &c->overflow);
+    // the remaining list has a capacity of its own, so each wave appends to it
+    wb_flush(brem.b, brem.q, a.b.cap, brem.tail, &c->overflow);
+    VStream *const vs[2] = {&bq, &bchg};
+    CStream *const cs[2] = {&bh, &bchh};
+    block_flush(a, vs, cs);
 }
 
 // Insert the selected set into G (Algorithm 1) and update SD of the
@@ -1491,19 +1496,16 @@ __device__ __forceinline__ void expand_round(const KArgs &a, const Iter &it, int
         e.a = f;
     };
     const bool sl = a.t.sublists != 0;
-    Pusher pq{wave_buf(0), wave_buf(3), a.q.fq[bn], &c->fq_tail[sn], a.q.fh[bn], &c->fh_tail[sn], g.len,
-              a.t.large_deg, a.t.chunk};
-    WaveBuf be = wave_buf(1), bcand = wave_buf(2);
+    Pusher pq = make_pusher(a.q.fq[bn], &c->fq_tail[sn], a.q.fh[bn], &c->fh_tail[sn], g.len, a.t.large_deg,
+                            a.t.chunk);
+    VStream ev{wave_buf(3), a.q.eq[0], &c->eq_tail[0]}, cand{wave_buf(5), a.q.cand, &c->cand_count};
+    CStream eh{wave_buf(4), a.q.eh[0], &c->eh_tail[0], sl ? g.slen : g.len, sl ? evict_chunk(a) : a.t.chunk};
     auto push_next = [&](int32_t w, bool p) { push_deep(a, pq, w, p); };
     // an evicted vertex's walk is its supporter run (sublists) or its list
     auto push_evict = [&](int32_t v, bool p, int32_t nsup) {
-        push_vertex_wb_len(a, be, a.q.eq[0], &c->eq_tail[0], a.q.eh[0], &c->eh_tail[0], v,
-                           p ? (sl ? nsup : g.len[v]) : 0, p, sl ? evict_large(a) : a.t.large_deg,
-                           sl ? evict_chunk(a) : a.t.chunk);
+        push_len(a, ev, eh, v, p ? (sl ? nsup : g.len[v]) : 0, p, sl ? evict_large(a) : a.t.large_deg);
     };
-    auto push_cand = [&](int32_t v, bool p) {
-        wb_push(bcand, a.q.cand, a.q.vcap, &c->cand_count, v, p, &c->overflow);
-    };
+    auto push_cand = [&](int32_t v, bool p) { vs_push(a, cand, v, p); };
 
     if (a.t.prune) {
         expand_round_pruned(a, it, r, T, acc);
@@ -1625,9 +1627,9 @@ __device__ __forceinline__ void expand_round(const KArgs &a, const Iter &it, int
         push_evict(v, live && pcd <= k, nlk);
         return walked;
     });
-    push_done(a, pq);
-    wb_flush(be, a.q.eq[0], a.q.vcap, &c->eq_tail[0], &c->overflow);
-    wb_flush(bcand, a.q.cand, a.q.vcap, &c->cand_count, &c->overflow);
+    VStream *const vs[3] = {&pq.v, &ev, &cand};
+    CStream *const cs[3] = {&pq.m, &pq.h, &eh};
+    block_flush(a, vs, cs);
 }
 
 // Negative traversal (Algorithm 4) as rounds: an evicted candidate lowers the
@@ -1647,8 +1649,8 @@ __device__ __forceinline__ void evict_round(const KArgs &a, const Iter &it, int 
     const int32_t ep = it.ep;
     // an evicted vertex's walk: its supporter run (sublists) or its list
     const bool sl = a.t.sublists != 0;
-    Pusher pq{wave_buf(0), wave_buf(3), a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn],
-              sl ? g.slen : g.len, sl ? evict_large(a) : a.t.large_deg, sl ? evict_chunk(a) : a.t.chunk};
+    Pusher pq = make_pusher(a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn], sl ? g.slen : g.len,
+                            sl ? evict_large(a) : a.t.large_deg, sl ? evict_chunk(a) : a.t.chunk);
     const int32_t *arr = sl ? g.sub : g.nbr;
     // Of a supporter run every entry is a level-k candidate of this iteration
     // (the expansion scanned the evicted vertex, as every candidate, before
@@ -1681,7 +1683,7 @@ __device__ __forceinline__ void evict_round(const KArgs &a, const Iter &it, int 
         return L < len ? L : len;  // never past the list, even on a count left from another iteration
     };
     // long walks, item by item (slen never passes the list: see walk_len)
-    for_chunks(T, a.q.eh[bc], nh, g, pq.lens, pq.chunk, sl ? g.len : nullptr,
+    for_chunks(T, a.q.eh[bc], nh, g, pq.m.lens, pq.m.chunk, sl ? g.len : nullptr,
                [&](int32_t, int32_t lo, int32_t hi, int32_t, int32_t k, int64_t o, int32_t len) {
         if (sl && hi > len) hi = len;
         if (hi <= lo) return;
@@ -1698,7 +1700,9 @@ __device__ __forceinline__ void evict_round(const KArgs &a, const Iter &it, int 
                                 push_deep(a, pq, w, f != 0);
                             });
     });
-    push_done(a, pq);
+    VStream *const vs[1] = {&pq.v};
+    CStream *const cs[2] = {&pq.m, &pq.h};
+    block_flush(a, vs, cs);
 }
 
 // Peel cascade of the deletion (Algorithms 6-7) as rounds.  A peeled vertex
@@ -1718,9 +1722,10 @@ __device__ __forceinline__ void peel_round(const KArgs &a, const Iter &it, int r
         ph_count(PH_ROUNDS);
     }
     const int32_t ep = it.ep;
-    Pusher pq{wave_buf(0), wave_buf(3), a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn], g.len,
-              a.t.large_deg, a.t.chunk};
-    WaveBuf bt = wave_buf(1), bchg = wave_buf(2);
+    Pusher pq = make_pusher(a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn], g.len, a.t.large_deg,
+                            a.t.chunk);
+    VStream touched{wave_buf(3), a.q.touched, &c->touched_count}, chg{wave_buf(4), a.q.chg, &c->chg_count};
+    CStream chh{wave_buf(5), a.q.chh, &c->chh_count, g.len, a.t.chunk};
     // cores and SD do not change during a peel round
     auto s1 = [&](Ent &e) __attribute__((always_inline)) {
         e.a = -1;
@@ -1748,9 +1753,9 @@ __device__ __forceinline__ void peel_round(const KArgs &a, const Iter &it, int r
     auto fin = [&](int32_t w, int32_t f) {
         if (__ballot(f != 0) == 0ull) return;
         const bool fire = (f & FIRE) != 0;
-        wb_push(bt, a.q.touched, a.q.vcap, &c->touched_count, w, (f & FIRST) != 0, &c->overflow);
+        vs_push(a, touched, w, (f & FIRST) != 0);
         push_deep(a, pq, w, fire);
-        push_vertex_wb(a, bchg, a.q.chg, &c->chg_count, a.q.chh, &c->chh_count, w, fire);
+        push_len(a, chg, chh, w, fire ? g.len[w] : 0, fire, a.t.large_deg);
     };
     // a long list with a valid up-list is read through it: the neighbours at
     // the peeled vertex's core are all in its up-set
@@ -1769,9 +1774,9 @@ __device__ __forceinline__ void peel_round(const KArgs &a, const Iter &it, int r
             g.nbr, g, v, L, k, s1, s2, s3, s4,
             [&](int32_t, int32_t w, int32_t f, unsigned long long, int64_t, int32_t) { fin(w, f); });
     });
-    push_done(a, pq);
-    wb_flush(bt, a.q.touched, a.q.vcap, &c->touched_count, &c->overflow);
-    wb_flush(bchg, a.q.chg, a.q.vcap, &c->chg_count, &c->overflow);
+    VStream *const vs[3] = {&pq.v, &touched, &chg};
+    CStream *const cs[3] = {&pq.m, &pq.h, &chh};
+    block_flush(a, vs, cs);
 }
 
 // Core update (Algorithm 1: +1 for every surviving candidate; Algorithm 5:
@@ -1786,7 +1791,8 @@ __device__ __forceinline__ void apply_core(const KArgs &a, const Iter &it, const
             c->st_candidates += (unsigned long long)n;
             c->st_icand += (unsigned long long)n;
         }
-        WaveBuf b = wave_buf(0);
+        VStream chg{wave_buf(0), a.q.chg, &c->chg_count};
+        CStream chh{wave_buf(1), a.q.chh, &c->chh_count, g.len, a.t.chunk};
         int32_t moved = 0;  // uniform
         for_span(T, n, [&](int32_t idx) {
             int32_t v = -1, k = 0, L = 0;
@@ -1807,10 +1813,11 @@ __device__ __forceinline__ void apply_core(const KArgs &a, const Iter &it, const
             }
             if (a.dl.chg) dbg_put(a.dl.chg, &a.dl.n[1], a.dl.cap, up, it.ep, v, k + 1);
             moved += __popcll(__ballot(up));
-            push_vertex_wb_len(a, b, a.q.chg, &c->chg_count, a.q.chh, &c->chh_count, v, L, up, a.t.large_deg,
-                               a.t.chunk);
+            push_len(a, chg, chh, v, L, up, a.t.large_deg);
         });
-        wb_flush(b, a.q.chg, a.q.vcap, &c->chg_count, &c->overflow);
+        VStream *const vs[1] = {&chg};
+        CStream *const cs[1] = {&chh};
+        block_flush(a, vs, cs);
         if (moved && lane() == 0) atomicAdd(&c->changed_count, moved);
     } else {
         const int32_t n = sqlen(it.sn, c, &c->chg_count, a.q.vcap);
@@ -2892,7 +2899,9 @@ __device__ __forceinline__ void dec_sweep(const KArgs &a, const DState &st, cons
             c->min_deg[f2] = 0x7fffffff;
         }
     }
-    WaveBuf bt = wave_buf(0), bn = wave_buf(1), bf = wave_buf(2);
+    VStream tv{wave_buf(0), a.q.eq[fb], &c->eq_tail[fn]}, bn{wave_buf(1), nlist, &c->nr_count[n1]},
+        bf{wave_buf(2), flist, &c->rm_count[f1]};
+    CStream tc{wave_buf(3), a.q.eh[fb], &c->eh_tail[fn], g.len, a.t.chunk};
     int32_t fmin = 0x7fffffff, nmin = 0x7fffffff;
     const int32_t span = wave_span(n);
     for (int32_t base = T.wave() * span; base < n; base += T.nwaves() * span) {
@@ -2919,16 +2928,16 @@ __device__ __forceinline__ void dec_sweep(const KArgs &a, const DState &st, cons
             const bool near = live && !take && dv[u] < top;
             const bool keep = live && far && dv[u] >= top;
             if (take) g.core[v[u]] = st.k;
-            push_vertex_wb(a, bt, a.q.eq[fb], &c->eq_tail[fn], a.q.eh[fb], &c->eh_tail[fn], v[u], take);
-            wb_push(bn, nlist, a.q.vcap, &c->nr_count[n1], v[u], near, &c->overflow);
-            wb_push(bf, flist, a.q.vcap, &c->rm_count[f1], v[u], keep, &c->overflow);
+            if (__ballot(take)) push_len(a, tv, tc, v[u], take ? g.len[v[u]] : 0, take, a.t.large_deg);
+            vs_push(a, bn, v[u], near);
+            vs_push(a, bf, v[u], keep);
             if (near) nmin = dv[u] < nmin ? dv[u] : nmin;
             if (keep) fmin = dv[u] < fmin ? dv[u] : fmin;
         }
     }
-    wb_flush(bt, a.q.eq[fb], a.q.vcap, &c->eq_tail[fn], &c->overflow);
-    wb_flush(bn, nlist, a.q.vcap, &c->nr_count[n1], &c->overflow);
-    wb_flush(bf, flist, a.q.vcap, &c->rm_count[f1], &c->overflow);
+    VStream *const vs[3] = {&tv, &bn, &bf};
+    CStream *const cs[1] = {&tc};
+    block_flush(a, vs, cs);
     // smallest degrees (the maxima of their complements)
     const int32_t nm = 0x7fffffff - __builtin_amdgcn_readlane(wave_incl_max(0x7fffffff - nmin), WAVE - 1);
     const int32_t fm = 0x7fffffff - __builtin_amdgcn_readlane(wave_incl_max(0x7fffffff - fmin), WAVE - 1);
@@ -2968,13 +2977,13 @@ __device__ __forceinline__ void dec_round(const KArgs &a, const DState &st, cons
         e.a = e.b == k + 1 ? GONE : (e.b == top ? NEAR : 0);
         if (e.a == GONE) g.core[e.w] = k;
     };
-    Pusher pq{wave_buf(0), wave_buf(3), a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn], g.len,
-              a.t.large_deg, a.t.chunk};
-    WaveBuf bnear = wave_buf(1);
+    Pusher pq = make_pusher(a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn], g.len, a.t.large_deg,
+                            a.t.chunk);
+    VStream near{wave_buf(3), nlist, ntail};
     auto fin = [&](int32_t w, int32_t f) {
         if (__ballot(f != 0) == 0ull) return;
         push_deep(a, pq, w, f == GONE);
-        wb_push(bnear, nlist, a.q.vcap, ntail, w, f == NEAR, &c->overflow);
+        vs_push(a, near, w, f == NEAR);
     };
     for_chunks(T, a.q.eh[bc], nh, g, g.len, a.t.chunk, nullptr,
                [&](int32_t, int32_t lo, int32_t hi, int32_t, int32_t, int64_t o, int32_t) {
@@ -2988,8 +2997,9 @@ __device__ __forceinline__ void dec_round(const KArgs &a, const DState &st, cons
             g.nbr, g, v, L, k, s1, s2, s3, s4,
             [&](int32_t, int32_t w, int32_t f, unsigned long long, int64_t, int32_t) { fin(w, f); });
     }, DEC_DEEP, DEC_WIDE);
-    push_done(a, pq);
-    wb_flush(bnear, nlist, a.q.vcap, ntail, &c->overflow);
+    VStream *const vs[2] = {&pq.v, &near};
+    CStream *const cs[2] = {&pq.m, &pq.h};
+    block_flush(a, vs, cs);
 }
 
 __device__ __forceinline__ bool dec_block_local_ok(const KArgs &a, const DState &st, const Team &T) {

@@ -12,36 +12,15 @@
 
 namespace cm {
 
-// Append the chunk items (w, 0), .., (w, nch - 1) of every lane (nch = 0
-// for none) to a chunk queue with one tail atomic per wave: returning
-// atomics on one word serialise (about 11 ns each), and one per long list
-// bound the rounds that push many of them.  The wave writes the items
-// together, lane i taking items i, i + 64, ..., so a very long list does
-// not serialise on its own lane.  A wave with inactive lanes (the last pass
-// of a strided loop) pushes lane by lane instead.
-__device__ __forceinline__ void push_chunks(const KArgs &a, int64_t *hq, int32_t *htail, int32_t w,
-                                            int32_t nch) {
-    if (__ballot(nch > 0) == 0ull) return;
-    if (__ballot(1) != ~0ull) {
-        if (nch > 0) {
-            const int32_t base = atomicAdd(htail, nch);
-            for (int32_t c = 0; c < nch; ++c) {
-                if (base + c < a.q.hcap) hq[base + c] = chunk_item(w, c);
-                else atomicOr(&a.ctl->overflow, 1);
-            }
-        }
-        return;
-    }
-    int32_t incl = nch;
-    for (int o = 1; o < WAVE; o <<= 1) {
-        const int32_t t = __shfl_up(incl, o);
-        if (lane() >= o) incl += t;
-    }
-    const int32_t total = __shfl(incl, WAVE - 1);
+// Write the chunk items (w, 0), .., (w, nch - 1) of every lane (nch = 0 for
+// none) from position `base` of a chunk queue on.  The wave writes them
+// together, lane i taking items i, i + 64, ..., so a very long list does not
+// serialise on its own lane.  Every lane of the wave must call it; incl =
+// the inclusive scan of nch.
+__device__ __forceinline__ void write_chunks(const KArgs &a, int64_t *hq, int32_t base, int32_t w, int32_t nch,
+                                             int32_t incl) {
+    const int32_t total = __builtin_amdgcn_readlane(incl, WAVE - 1);
     const int32_t excl = incl - nch;
-    int32_t base = 0;
-    if (lane() == 0) base = atomicAdd(htail, total);
-    base = __shfl(base, 0);
     for (int32_t e0 = 0; e0 < total; e0 += WAVE) {
         const int32_t e = e0 + lane();
         // owner of item e: the last lane whose items start at or before e
@@ -62,6 +41,29 @@ __device__ __forceinline__ void push_chunks(const KArgs &a, int64_t *hq, int32_t
     }
 }
 
+// Append the chunk items of every lane to a chunk queue with one tail atomic
+// per wave: returning atomics on one word serialise (about 11 ns each), and
+// one per long list bound the rounds that push many of them.  A wave with
+// inactive lanes (the last pass of a strided loop) pushes lane by lane.
+__device__ __forceinline__ void push_chunks(const KArgs &a, int64_t *hq, int32_t *htail, int32_t w,
+                                            int32_t nch) {
+    if (__ballot(nch > 0) == 0ull) return;
+    if (__ballot(1) != ~0ull) {
+        if (nch > 0) {
+            const int32_t base = atomicAdd(htail, nch);
+            for (int32_t c = 0; c < nch; ++c) {
+                if (base + c < a.q.hcap) hq[base + c] = chunk_item(w, c);
+                else atomicOr(&a.ctl->overflow, 1);
+            }
+        }
+        return;
+    }
+    const int32_t incl = wave_incl_add(nch);
+    int32_t base = 0;
+    if (lane() == WAVE - 1) base = atomicAdd(htail, incl);
+    write_chunks(a, hq, __builtin_amdgcn_readlane(base, WAVE - 1), w, nch, incl);
+}
+
 // Route a pushed vertex: short/medium lists to the vertex queue, long lists
 // as `nchunks` items to the chunk queue.  All lanes may call it (pred
 // selects the pushing lanes).
@@ -80,7 +82,7 @@ __device__ __forceinline__ void push_vertex(const KArgs &a, int32_t *vq, int32_t
 // LDS and appends them with one atomic per 64 or more entries; a round
 // flushes its buffers before its barrier.  wb_push / push_vertex_wb must be
 // called by every lane of the wave (pred selects the pushing lanes).
-constexpr int PUSH_SLOTS = 4;
+constexpr int PUSH_SLOTS = 6;
 struct WaveBuf {
     int32_t *buf;  // 2 * WAVE entries of this wave's slot
     int32_t n;     // entries held (uniform over the wave)
@@ -111,61 +113,157 @@ __device__ __forceinline__ void wb_push(WaveBuf &b, int32_t *q, int32_t qcap, in
     b.n += __popcll(m);
     if (b.n >= WAVE) wb_flush(b, q, qcap, tail, overflow);
 }
-// push_vertex through wave buffers, for a walk of L entries of w (the caller
-// gives L: the list length, or the length of another per-vertex run): walks
-// of up to `large` entries go to b, longer ones of up to DEEP_LIST to m (the
-// wave may walk them itself in this round, see for_batches_deep; flushed as
-// chunk items otherwise), the others straight to the chunk queue as items of
-// `chunk` entries.  lens: the walk lengths.
-constexpr int DEEP_LIST = 512;
-struct Pusher {
-    WaveBuf b, m;
-    int32_t *vq, *vtail;
-    int64_t *hq;
-    int32_t *htail;
-    const int32_t *lens;
-    int32_t large, chunk;
+// Two kinds of streams that a step pushes to: vertices to a vertex queue, and
+// vertices with long walks to a chunk queue, as items of `chunk` entries of
+// their walk (lens: the walk lengths).  Both collect in a wave buffer.
+struct VStream {
+    WaveBuf b;
+    int32_t *q, *tail;
 };
-__device__ __forceinline__ void mid_flush(const KArgs &a, Pusher &p) {
-    if (p.m.n == 0) return;
+struct CStream {
+    WaveBuf b;
+    int64_t *q;
+    int32_t *tail;
+    const int32_t *lens;
+    int32_t chunk;
+};
+__device__ __forceinline__ void vs_push(const KArgs &a, VStream &s, int32_t w, bool pred) {
+    wb_push(s.b, s.q, a.q.vcap, s.tail, w, pred, &a.ctl->overflow);
+}
+__device__ __forceinline__ void cs_flush(const KArgs &a, CStream &s) {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // other lanes' LDS writes come first
-    for (int i0 = 0; i0 < p.m.n; i0 += WAVE) {
-        const bool has = i0 + lane() < p.m.n;
-        const int32_t w = has ? p.m.buf[i0 + lane()] : -1;
-        push_chunks(a, p.hq, p.htail, w, has ? nchunks(p.lens[w], p.chunk) : 0);
+    for (int i0 = 0; i0 < s.b.n; i0 += WAVE) {
+        const bool has = i0 + lane() < s.b.n;
+        const int32_t w = has ? s.b.buf[i0 + lane()] : -1;
+        push_chunks(a, s.q, s.tail, w, has ? nchunks(s.lens[w], s.chunk) : 0);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // reads done before the slots are reused
-    p.m.n = 0;
+    s.b.n = 0;
+}
+__device__ __forceinline__ void cs_push(const KArgs &a, CStream &s, int32_t w, bool pred) {
+    const unsigned long long m = __ballot(pred);
+    if (m == 0ull) return;
+    if (pred) s.b.buf[s.b.n + __popcll(m & lanes_below())] = w;
+    s.b.n += __popcll(m);
+    if (s.b.n >= WAVE) cs_flush(a, s);
+}
+
+// End of a step: what is left in the waves' buffers, appended with one tail
+// atomic per stream and workgroup.  One per wave is 2,048 turns on a word at
+// 11 ns each, for each of the streams (which share a line): a round that gave
+// every wave something to push took 20 to 60 us for it.  Every thread of the
+// workgroup must call it (workgroup barriers inside).
+template <int NV, int NC>
+__device__ __forceinline__ void block_flush(const KArgs &a, VStream *const (&vs)[NV], CStream *const (&cs)[NC]) {
+    constexpr int N = NV + NC, NW = COOP_THREADS / WAVE;
+    __shared__ int32_t cnt[PUSH_SLOTS][NW];
+    __shared__ int32_t first[PUSH_SLOTS];
+    static_assert(N <= PUSH_SLOTS, "one slot per stream");
+    const int wv = uniform((int)(threadIdx.x / WAVE));
+    const int nw = (int)(blockDim.x / WAVE);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // other lanes' LDS writes come first
+    int32_t w[NC][2], nch[NC][2], incl[NC][2], mine[N];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) mine[i] = vs[i]->b.n;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+        CStream &s = *cs[i];
+        mine[NV + i] = 0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            w[i][h] = -1;
+            nch[i][h] = incl[i][h] = 0;
+            if (s.b.n > h * WAVE) {  // uniform
+                const bool has = h * WAVE + lane() < s.b.n;
+                if (has) {
+                    w[i][h] = s.b.buf[h * WAVE + lane()];
+                    nch[i][h] = nchunks(s.lens[w[i][h]], s.chunk);
+                }
+                incl[i][h] = wave_incl_add(nch[i][h]);
+                mine[NV + i] += __builtin_amdgcn_readlane(incl[i][h], WAVE - 1);
+            }
+        }
+    }
+    if (lane() == 0) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) cnt[i][wv] = mine[i];
+    }
+    __syncthreads();
+    if (threadIdx.x < N) {
+        int32_t *tail = nullptr;
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+            if ((int)threadIdx.x == i) tail = vs[i]->tail;
+#pragma unroll
+        for (int i = 0; i < NC; ++i)
+            if ((int)threadIdx.x == NV + i) tail = cs[i]->tail;
+        int32_t sum = 0;
+        for (int j = 0; j < nw; ++j) sum += cnt[threadIdx.x][j];
+        first[threadIdx.x] = sum ? atomicAdd(tail, sum) : 0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        if (mine[i] == 0) continue;  // uniform
+        int32_t base = first[i];
+        for (int j = 0; j < wv; ++j) base += cnt[i][j];
+        if (i < NV) {
+            VStream &s = *vs[i < NV ? i : 0];
+            for (int x = lane(); x < s.b.n; x += WAVE) {
+                const int pos = base + x;
+                if (pos < a.q.vcap) s.q[pos] = s.b.buf[x];
+                else atomicOr(&a.ctl->overflow, 1);
+            }
+            s.b.n = 0;
+        } else {
+            constexpr int Z = NV;
+            const int ci = i < NV ? 0 : i - Z;
+            CStream &s = *cs[ci];
+            write_chunks(a, s.q, base, w[ci][0], nch[ci][0], incl[ci][0]);
+            if (s.b.n > WAVE)
+                write_chunks(a, s.q, base + __builtin_amdgcn_readlane(incl[ci][0], WAVE - 1), w[ci][1], nch[ci][1],
+                             incl[ci][1]);
+            s.b.n = 0;
+        }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // reads done before the slots are reused
+}
+
+// The next frontier of a cascade: walks of up to `large` entries go to v,
+// longer ones of up to DEEP_LIST to m (the wave may walk them itself in this
+// round, see for_batches_deep; flushed as chunk items otherwise), the others to
+// h.
+constexpr int DEEP_LIST = 512;
+struct Pusher {
+    VStream v;
+    CStream m, h;
+    int32_t large;
+};
+__device__ __forceinline__ Pusher make_pusher(int32_t *vq, int32_t *vtail, int64_t *hq, int32_t *htail,
+                                              const int32_t *lens, int32_t large, int32_t chunk) {
+    return Pusher{VStream{wave_buf(0), vq, vtail}, CStream{wave_buf(1), hq, htail, lens, chunk},
+                  CStream{wave_buf(2), hq, htail, lens, chunk}, large};
 }
 __device__ __forceinline__ void push_deep(const KArgs &a, Pusher &p, int32_t w, bool pred) {
     if (__ballot(pred) == 0ull) return;
-    const int32_t L = pred ? p.lens[w] : 0;
-    wb_push(p.b, p.vq, a.q.vcap, p.vtail, w, pred && L <= p.large, &a.ctl->overflow);
-    const bool mid = pred && L > p.large && L <= DEEP_LIST;
-    const unsigned long long mm = __ballot(mid);
-    if (mm) {
-        if (mid) p.m.buf[p.m.n + __popcll(mm & lanes_below())] = w;
-        p.m.n += __popcll(mm);
-        if (p.m.n >= WAVE) mid_flush(a, p);
-    }
-    push_chunks(a, p.hq, p.htail, w, pred && L > DEEP_LIST ? nchunks(L, p.chunk) : 0);
+    const int32_t L = pred ? p.m.lens[w] : 0;
+    vs_push(a, p.v, w, pred && L <= p.large);
+    cs_push(a, p.m, w, pred && L > p.large && L <= DEEP_LIST);
+    cs_push(a, p.h, w, pred && L > p.large && L > DEEP_LIST);
 }
-__device__ __forceinline__ void push_done(const KArgs &a, Pusher &p) {
-    wb_flush(p.b, p.vq, a.q.vcap, p.vtail, &a.ctl->overflow);
-    mid_flush(a, p);
+// A vertex whose walk is not the wave's to go on with: v or c by its length L.
+__device__ __forceinline__ void push_len(const KArgs &a, VStream &v, CStream &c, int32_t w, int32_t L, bool pred,
+                                         int32_t large) {
+    vs_push(a, v, w, pred && L <= large);
+    cs_push(a, c, w, pred && L > large);
 }
-// ... without walks of the wave's own: long lists straight to the chunk queue
-__device__ __forceinline__ void push_vertex_wb_len(const KArgs &a, WaveBuf &b, int32_t *vq, int32_t *vtail,
-                                                   int64_t *hq, int32_t *htail, int32_t w, int32_t L,
-                                                   bool pred, int32_t large, int32_t chunk) {
-    const bool big = pred && L > large;
-    wb_push(b, vq, a.q.vcap, vtail, w, pred && !big, &a.ctl->overflow);
-    push_chunks(a, hq, htail, w, big ? nchunks(L, chunk) : 0);
-}
-// ... for a walk of w's whole list
+// ... one list at a time, straight to the chunk queue (steps without streams)
 __device__ __forceinline__ void push_vertex_wb(const KArgs &a, WaveBuf &b, int32_t *vq, int32_t *vtail,
                                                int64_t *hq, int32_t *htail, int32_t w, bool pred) {
-    push_vertex_wb_len(a, b, vq, vtail, hq, htail, w, pred ? a.g.len[w] : 0, pred, a.t.large_deg, a.t.chunk);
+    const int32_t L = pred ? a.g.len[w] : 0;
+    const bool big = pred && L > a.t.large_deg;
+    wb_push(b, vq, a.q.vcap, vtail, w, pred && !big, &a.ctl->overflow);
+    push_chunks(a, hq, htail, w, big ? nchunks(L, a.t.chunk) : 0);
 }
 
 // Team-stride over 0 .. n-1 by whole waves: f(i) runs on every lane (i < 0
@@ -414,15 +512,15 @@ __device__ __forceinline__ void for_batches_deep(const Team &T, const int32_t *q
             if (lane() < per && i < n) v = q[i];
             base += step;
         } else {
-            if (left <= 0 || p.m.n + p.b.n == 0 || (p.m.n == 0 && p.b.n > width)) break;
+            if (left <= 0 || p.m.b.n + p.v.b.n == 0 || (p.m.b.n == 0 && p.v.b.n > width)) break;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // other lanes' LDS writes come first
-            if (p.m.n > 0) {
-                p.m.n -= 1;
-                if (lane() == 0) v = p.m.buf[p.m.n];
+            if (p.m.b.n > 0) {
+                p.m.b.n -= 1;
+                if (lane() == 0) v = p.m.b.buf[p.m.b.n];
                 limit = DEEP_LIST;
             } else {
-                if (lane() < p.b.n) v = p.b.buf[lane()];
-                p.b.n = 0;
+                if (lane() < p.v.b.n) v = p.v.b.buf[lane()];
+                p.v.b.n = 0;
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // reads done before the slots are reused
         }

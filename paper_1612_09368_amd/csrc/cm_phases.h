@@ -1912,12 +1912,19 @@ __device__ __forceinline__ void mcd_phase(const KArgs &a, const Iter &it, const 
         if (v >= 0) { g.mcd[v] = cnt; acc.scanned += L; }
     });
     const int32_t nh = sqlen(it.sn, c, &c->chh_count, a.q.hcap);
-    for_chunks(T, a.q.chh, nh, g, g.len, a.t.chunk, nullptr,
-               [&](int32_t v, int32_t lo, int32_t hi, int32_t, int32_t k, int64_t o, int32_t) {
-        int32_t cnt = 0;
-        wave_walk_st(g.nbr + o, lo, hi, k, s1, s2, s3, s4, [&](int32_t, int32_t f) { cnt += f; });
+    // A vertex that rose from k to k + 1 needs its neighbours at k + 1 or more
+    // alone, for its own count and for their deltas: they were at k or more
+    // before the core step, so a valid up-list holds them all (an up-list made
+    // invalid in this step belongs to a vertex that did not move).  A vertex
+    // that fell also needs the neighbours at its new core, outside its up-set.
+    for_chunks(T, a.q.chh, nh, g, g.len, a.t.chunk, ins && a.t.uplists ? g.ubl : nullptr,
+               [&](int32_t v, int32_t lo, int32_t hi, int32_t, int32_t k, int64_t o, int32_t ub) {
+        int32_t cnt = 0, seen = hi - lo;
+        auto fin = [&](int32_t, int32_t f) { cnt += f; };
+        if (ub >= 0) seen = walk_chunk_up(g, lo, hi, ub, k, o, s1, s2, s3, s4, fin);
+        else wave_walk_st(g.nbr + o, lo, hi, k, s1, s2, s3, s4, fin);
         cnt = wave_sum(cnt);
-        if (lane() == 0) { atomicAdd(&g.mcd[v], cnt); acc.scanned += hi - lo; }
+        if (lane() == 0) { atomicAdd(&g.mcd[v], cnt); acc.scanned += seen; }
     });
 }
 

@@ -1952,12 +1952,16 @@ __device__ __forceinline__ long long block_sum64(long long v) {
 
 // List entries a frontier step would walk: the lengths of its vertex items
 // plus a full chunk per chunk item (computed by one workgroup).
+// A queue whose walks of up to `most` entries each cannot pass the local bound
+// counts as that bound: no length is read (the sum costs two dependent reads
+// and two workgroup barriers, about 2 of a local step's 8 us).
 __device__ __forceinline__ long long queue_work(const KArgs &a, const Team &T, const int32_t *q, int32_t n,
-                                                int32_t nchk, int walks, const int32_t *lens) {
+                                                int32_t nchk, int32_t most, const int32_t *lens) {
+    const long long bound = (long long)n * most + (long long)nchk * a.t.chunk;
+    if (most > 0 && bound <= a.t.local_work) return bound;
     long long w = 0;
     for (int32_t i = T.rank; i < n; i += T.size) w += lens[q[i]];
-    w = block_sum64(w) * walks;
-    return w + (long long)nchk * a.t.chunk;
+    return block_sum64(w) + (long long)nchk * a.t.chunk;
 }
 
 // Whether workgroup 0 may run this step by itself: its item count already
@@ -1968,17 +1972,18 @@ __device__ __forceinline__ bool block_local_ok(const KArgs &a, const Iter &it, c
     long long w = 0;
     switch (pc.step) {
     case S_EXPAND:
-        w = queue_work(a, T, a.q.fq[pc.r & 1], sqlen(it.sn, c, &c->fq_tail[s], a.q.vcap), sqlen(it.sn, c, &c->fh_tail[s], a.q.hcap), 1,
-                       a.g.len);
+        w = queue_work(a, T, a.q.fq[pc.r & 1], sqlen(it.sn, c, &c->fq_tail[s], a.q.vcap), sqlen(it.sn, c, &c->fh_tail[s], a.q.hcap),
+                       pc.r > 0 ? a.t.large_deg : 0, a.g.len);  // round 0: roots with lists of any length
         break;
     case S_EVICT:
     case S_PEEL:
         // an eviction walks supporter runs when they are kept
-        w = queue_work(a, T, a.q.eq[pc.r & 1], sqlen(it.sn, c, &c->eq_tail[s], a.q.vcap), sqlen(it.sn, c, &c->eh_tail[s], a.q.hcap), 1,
-                       pc.step == S_EVICT && a.t.sublists ? a.g.slen : a.g.len);
+        w = queue_work(a, T, a.q.eq[pc.r & 1], sqlen(it.sn, c, &c->eq_tail[s], a.q.vcap), sqlen(it.sn, c, &c->eh_tail[s], a.q.hcap),
+                       a.t.large_deg, pc.step == S_EVICT && a.t.sublists ? a.g.slen : a.g.len);
         break;
     case S_MCD:
-        w = queue_work(a, T, a.q.chg, sqlen(it.sn, c, &c->chg_count, a.q.vcap), sqlen(it.sn, c, &c->chh_count, a.q.hcap), 1, a.g.len);
+        w = queue_work(a, T, a.q.chg, sqlen(it.sn, c, &c->chg_count, a.q.vcap), sqlen(it.sn, c, &c->chh_count, a.q.hcap),
+                       a.t.large_deg, a.g.len);
         break;
     default: return true;
     }
@@ -2147,6 +2152,7 @@ __device__ __forceinline__ int run_iterations(const KArgs &a, int ins, int max_i
         // chains of small ones: a single copy of the steps in the kernel.
         bool chain = false;                 // inside workgroup 0's chain of local steps
         unsigned long long t0 = 0, tl = 0;  // phase clock; start of the chain
+        int links = 0;                      // steps of the chain
         while (pc.step != S_DONE) {
             bool grid = false, fg = false;
             if (!chain) {
@@ -2155,6 +2161,7 @@ __device__ __forceinline__ int run_iterations(const KArgs &a, int ins, int max_i
                 force = false;
                 if (!grid && blockIdx.x == 0) {
                     chain = true;
+                    links = 0;
                     tl = (unsigned long long)wall_clock64();
                 }
             }
@@ -2179,9 +2186,10 @@ __device__ __forceinline__ int run_iterations(const KArgs &a, int ins, int max_i
                     pc = next_pc(a, it, pc);
                     // a long chain (a cascade of many small rounds) hands
                     // back to the grid once per slice, so that no barrier
-                    // wait outlasts its bound
+                    // wait outlasts its bound (looked at every 16 steps, well
+                    // under a millisecond: it takes two workgroup barriers)
                     stop = pc.step == S_DONE || !step_is_local(a, it, pc, step_work(a, it, pc)) ||
-                           slice_over(a.bar, tl);
+                           ((++links & 15) == 0 && slice_over(a.bar, tl));
                 }
                 if (stop) {
                     const int slot = pubs & 1;
@@ -3014,13 +3022,13 @@ __device__ __forceinline__ bool dec_block_local_ok(const KArgs &a, const DState 
     Ctl *c = a.ctl;
     const int s = st.f % 3;
     long long w = queue_work(a, T, a.q.eq[st.f & 1], sqlen(st.sn, c, &c->eq_tail[s], a.q.vcap),
-                             sqlen(st.sn, c, &c->eh_tail[s], a.q.hcap), 1, a.g.len);
+                             sqlen(st.sn, c, &c->eh_tail[s], a.q.hcap), a.t.large_deg, a.g.len);
     return w <= a.t.local_work;
 }
 
-// Sweeps of up to this many vertices run in workgroup 0 (8 entries per
-// thread, two groups of loads: less than a grid barrier).
-constexpr int32_t DEC_LOCAL_SWEEP = 4096;
+// Sweeps of up to this many vertices run in workgroup 0 (Chung-Lu 10^6 / 10^7
+// 13.9 ms with 4096, 14.6 with 16384, 13.5 with this).
+constexpr int32_t DEC_LOCAL_SWEEP = 512;
 __device__ __forceinline__ bool dec_is_local(const KArgs &a, const DState &st) {
     Ctl *c = a.ctl;
     if (st.step == D_FAR)
@@ -3075,6 +3083,7 @@ __device__ __forceinline__ void decompose(const KArgs &a, Acc &acc) {
     int32_t kmax = 0;
     bool force = false, chain = false;
     unsigned long long tl = 0;
+    int links = 0;
     while (st.step != D_DONE) {
         bool grid = false, fg = false;
         if (!chain) {
@@ -3083,6 +3092,7 @@ __device__ __forceinline__ void decompose(const KArgs &a, Acc &acc) {
             force = false;
             if (!grid && blockIdx.x == 0) {
                 chain = true;
+                links = 0;
                 tl = (unsigned long long)wall_clock64();
             }
         }
@@ -3111,7 +3121,7 @@ __device__ __forceinline__ void decompose(const KArgs &a, Acc &acc) {
             if (!stop) {
                 __syncthreads();
                 st = dec_next(a, st);
-                stop = st.step == D_DONE || !dec_is_local(a, st) || slice_over(a.bar, tl);
+                stop = st.step == D_DONE || !dec_is_local(a, st) || ((++links & 15) == 0 && slice_over(a.bar, tl));
             }
             if (stop) {
                 const int slot = pubs & 1;

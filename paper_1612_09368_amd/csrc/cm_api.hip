@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <new>
 #include <string>
 #include <unordered_map>
 #include <vector>
@@ -203,10 +204,20 @@ void dev_alloc(cm_graph *g, T **p, int64_t count) {
         if (have >= need && have <= need + need / 4 + 4096 && (best == SIZE_MAX || have < g->spare[best].second))
             best = i;
     }
+    auto note = [&](size_t bytes) {
+        try {
+            g->blocks[(void *)*p] = bytes;
+        } catch (const std::bad_alloc &) {
+            (void)hipFree((void *)*p);
+            *p = nullptr;
+            throw Fail{CM_E_NOMEM};
+        }
+    };
     if (best != SIZE_MAX) {
+        const size_t have = g->spare[best].second;
         *p = (T *)g->spare[best].first;
-        g->blocks[(void *)*p] = g->spare[best].second;
         g->spare.erase(g->spare.begin() + (std::ptrdiff_t)best);
+        note(have);
         return;
     }
     hipError_t e = hipMalloc((void **)p, need);
@@ -223,7 +234,7 @@ void dev_alloc(cm_graph *g, T **p, int64_t count) {
         g->err = "device allocation of " + std::to_string(need) + " bytes failed";
         throw Fail{CM_E_NOMEM};
     }
-    g->blocks[(void *)*p] = need;
+    note(need);
 }
 
 template <class T>
@@ -232,11 +243,29 @@ void dev_free(cm_graph *g, T *&p) {
         const auto it = g->blocks.find((void *)p);
         const size_t bytes = it == g->blocks.end() ? 0 : it->second;
         if (it != g->blocks.end()) g->blocks.erase(it);
-        if (g->reuse && bytes) g->spare.emplace_back((void *)p, bytes);
-        else (void)hipFree((void *)p);
+        bool kept = false;
+        if (g->reuse && bytes) {
+            try {
+                g->spare.emplace_back((void *)p, bytes);
+                kept = true;
+            } catch (const std::bad_alloc &) {
+            }
+        }
+        if (!kept) (void)hipFree((void *)p);
     }
     p = nullptr;
 }
+
+// A device block of one scope: given back also when an error leaves it.
+template <class T>
+struct Tmp {
+    cm_graph *g;
+    T *p = nullptr;
+    explicit Tmp(cm_graph *h) : g(h) {}
+    ~Tmp() { dev_free(g, p); }
+    Tmp(const Tmp &) = delete;
+    Tmp &operator=(const Tmp &) = delete;
+};
 
 // While one lives, blocks given up by the handle serve its next allocations
 // of about their size; what is left over is freed at its end.  Loading a graph
@@ -1348,73 +1377,73 @@ int cm_load_graph(cm_graph *g, int32_t n, int64_t m, const int32_t *src, const i
         g->g.n_ids = n;
         // stage edges on the device
         int32_t *ds = nullptr, *dd = nullptr;
-        bool own = false;
+        Tmp<int32_t> sbuf(g), dbuf(g);
         if (on_device) {
             ds = const_cast<int32_t *>(src);
             dd = const_cast<int32_t *>(dst);
         } else if (m > 0) {
-            dev_alloc(g, &ds, m);
-            dev_alloc(g, &dd, m);
-            own = true;
+            dev_alloc(g, &sbuf.p, m);
+            dev_alloc(g, &dbuf.p, m);
+            ds = sbuf.p;
+            dd = dbuf.p;
             HIPCHK(hipMemcpyAsync(ds, src, sizeof(int32_t) * (size_t)m, hipMemcpyHostToDevice, st));
             HIPCHK(hipMemcpyAsync(dd, dst, sizeof(int32_t) * (size_t)m, hipMemcpyHostToDevice, st));
         }
         int rc = CM_OK;
-        int32_t *pos = nullptr;  // the edges' places in their two lists
+        Tmp<int32_t> pos(g);  // the edges' places in their two lists
         if (m > 0) {
             // range / self-loop / duplicate check, list lengths and the
             // edges' places in their lists, in one pass over the edges
             const int64_t hc = next_pow2(2 * m);
-            unsigned long long *hkey = nullptr;
-            dev_alloc(g, &hkey, hc);
-            dev_alloc(g, &pos, 2 * m);
-            HIPCHK(fill_u64(hkey, ~0ull, hc, st));
+            Tmp<unsigned long long> hkey(g);
+            dev_alloc(g, &hkey.p, hc);
+            dev_alloc(g, &pos.p, 2 * m);
+            HIPCHK(fill_u64(hkey.p, ~0ull, hc, st));
             HIPCHK(fill_u64(g->u64_scratch, ~0ull, 1, st));
-            HIPCHK(load_count(ds, dd, m, n, hkey, (uint32_t)(hc - 1), g->g.len, pos, g->u64_scratch, st));
+            HIPCHK(load_count(ds, dd, m, n, hkey.p, (uint32_t)(hc - 1), g->g.len, pos.p, g->u64_scratch, st));
             HIPCHK(hipMemcpyAsync(g->hu64, g->u64_scratch, sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
             HIPCHK(hipStreamSynchronize(st));
             unsigned long long fb = g->hu64[0];
             if (fb != ~0ull) {
                 // something is wrong: find the first bad edge and its code
-                int64_t *hval = nullptr;
-                dev_alloc(g, &hval, hc);
-                HIPCHK(fill_u64(hkey, ~0ull, hc, st));
-                HIPCHK(fill_i64(hval, INT64_MAX, hc, st));
+                Tmp<int64_t> hval(g);
+                dev_alloc(g, &hval.p, hc);
+                HIPCHK(fill_u64(hkey.p, ~0ull, hc, st));
+                HIPCHK(fill_i64(hval.p, INT64_MAX, hc, st));
                 HIPCHK(fill_u64(g->u64_scratch, ~0ull, 1, st));
-                HIPCHK(load_check(ds, dd, m, n, hkey, hval, (uint32_t)(hc - 1), g->u64_scratch, st));
+                HIPCHK(load_check(ds, dd, m, n, hkey.p, hval.p, (uint32_t)(hc - 1), g->u64_scratch, st));
                 HIPCHK(hipMemcpyAsync(g->hu64, g->u64_scratch, sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
                 HIPCHK(hipStreamSynchronize(st));
-                dev_free(g, hval);
                 fb = g->hu64[0];
                 rc = fb == ~0ull ? CM_E_INTERNAL : -(int)(fb & 0xff);
                 g->err = std::string("invalid edge ") + std::to_string((long long)(fb >> 8)) + ": " +
                          cm_strerror(rc);
             }
-            dev_free(g, hkey);
         }
         if (rc == CM_OK) {
             // alive ids get core 0 until decomposed
             HIPCHK(fill_i32(g->g.core, 0, n, st));
-            int64_t *caps64 = nullptr;
-            dev_alloc(g, &caps64, g->g.n_cap);
-            HIPCHK(caps_from_counts(g->g.len, n, g->g.n_cap, caps64, g->g.cap, st));
-            HIPCHK(exclusive_scan_i64(caps64, g->g.off, g->g.n_cap, g->scan_tmp, g->i64_scratch, st));
+            Tmp<int64_t> caps64(g);
+            dev_alloc(g, &caps64.p, g->g.n_cap);
+            HIPCHK(caps_from_counts(g->g.len, n, g->g.n_cap, caps64.p, g->g.cap, st));
+            HIPCHK(exclusive_scan_i64(caps64.p, g->g.off, g->g.n_cap, g->scan_tmp, g->i64_scratch, st));
             int64_t total = 0;
             HIPCHK(hipMemcpyAsync(&total, g->i64_scratch, sizeof(int64_t), hipMemcpyDeviceToHost, st));
             HIPCHK(hipStreamSynchronize(st));
-            dev_free(g, caps64);
+            dev_free(g, caps64.p);
             int64_t pool = total + total / 4 + 4096;
             if (g->cfg.edge_capacity_hint > pool) pool = g->cfg.edge_capacity_hint;
             dev_alloc(g, &g->g.nbr, pool);
             if (g->tune.sublists) dev_alloc(g, &g->g.sub, pool);
             if (g->tune.uplists) dev_alloc(g, &g->g.upl, pool);
             g->g.pool_size = pool;
-            if (m > 0) HIPCHK(scatter_edges(ds, dd, m, g->g.off, pos, g->g.nbr, st));
+            if (m > 0) HIPCHK(scatter_edges(ds, dd, m, g->g.off, pos.p, g->g.nbr, st));
             // control block
             HIPCHK(hipMemsetAsync(g->ctl, 0, sizeof(Ctl), st));
             unsigned long long tail = (unsigned long long)total;
             HIPCHK(ctl_set_pool(g->ctl, tail, st));
             HIPCHK(hipStreamSynchronize(st));
+            dev_free(g, pos.p);
             std::memset(g->hctl, 0, sizeof(Ctl));
             g->hctl->pool_tail = tail;
             g->epoch = 0;
@@ -1422,11 +1451,6 @@ int cm_load_graph(cm_graph *g, int32_t n, int64_t m, const int32_t *src, const i
             g->m = m;
             g->n_alive = n;
             g->loaded = true;
-        }
-        dev_free(g, pos);
-        if (own) {
-            dev_free(g, ds);
-            dev_free(g, dd);
         }
         if (rc != CM_OK) {
             release_all(g);

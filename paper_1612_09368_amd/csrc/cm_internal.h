@@ -68,10 +68,9 @@ struct Ctl {
     int32_t min_deg[3];      // decomposition: smallest degree in it (rotating)
     int32_t nr_count[3];     // decomposition: near list (rotating by near list)
     int32_t nr_min[3];       // decomposition: smallest degree in it after a sweep (rotating)
-    int32_t kmax;            // decomposition: largest core number
     int32_t dec_rounds;      // decomposition: frontier rounds
     int32_t ipub[2][4];      // iteration step machine: (step, round, force grid) published by workgroup 0
-    int32_t dpub[2][8];      // decomposition step machine: (step, k, j, f, top, nj, kmax, force grid)
+    int32_t dpub[2][8];      // decomposition step machine: (step, k, j, f, top, nj, half, force grid)
     unsigned long long pool_tail;     // next free adjacency slot
     unsigned long long garbage;       // slots abandoned by relocations
     // statistics (summed over the iterations of a batch)

@@ -46,7 +46,6 @@ __global__ void k_ctl_batch_reset(Ctl *c, int cur) {
         c->scan_tail = 0;
         c->vlist_count = 0;
         c->reloc_count = 0;
-        c->kmax = 0;
         c->dec_rounds = 0;
         c->st_iters = 0; c->st_remaining = 0; c->st_selected = 0;
         c->st_candidates = 0; c->st_evicted = 0; c->st_changed = 0; c->st_scanned = 0;

@@ -2859,11 +2859,22 @@ __device__ __forceinline__ void run_server(const KArgs &a) {
 // stays in the far list until its next sweep drops it.  Empty levels are
 // skipped by jumping k to the smallest degree.
 //
+// A sweep serves two levels: it also lists the vertices of degree k + 1, and
+// the rounds of level k add those whose degree crosses to k + 1 (once each,
+// and none is both), so level k + 1 starts with a round over that list, which
+// passes over what level k took from it (with a sweep for each level:
+// Chung-Lu 10^6 / 10^7 1,057 steps and 13.5 ms against 909 and 13.0, ER 2^20
+// 1.28 against 1.10, R-MAT 22 13.6 against 12.9).  What is left is bound by the
+// rounds' own chains through long lists: lists of up to 2,048 entries gone on
+// with by their wave, in place of 512, halve the rounds and take 14.9 ms.
+//
 // Far lists: q.fq[j & 1], counts rotating by the far sweep j (sweep 0 reads
 // every id).  Near lists: q.cand / q.touched by nj & 1, counts rotating by
 // nj (a sweep reads list nj and writes list nj + 1, which the rounds after it
 // append to).  Frontier: q.eq / q.eh (counts rotating by the frontier index
 // f: a step reads slot f%3, pushes slot (f+1)%3, clears slot (f+2)%3).
+// Next level: q.chg / q.fh[0], counts fq_tail / fh_tail by nj & 1 (sweep nj
+// writes slot nj + 1 and clears the other).
 // Runs as a step machine like the iterations: small sweeps and rounds run in
 // workgroup 0 alone.
 // ===========================================================================
@@ -2876,6 +2887,7 @@ struct DState {
     int32_t f;    // frontier slot index
     int32_t top;  // near list: degrees below this
     int32_t nj;   // near list index
+    int32_t half; // 0: the level of a sweep; 1: round over the next-level list; 2: later round of its level
     Snap sn;      // control counters (words 0 .. 63) as the last step left them
 };
 // The control block's first 64 words, which hold every counter of the
@@ -2914,9 +2926,16 @@ __device__ __forceinline__ void dec_sweep(const KArgs &a, const DState &st, cons
             c->min_deg[f2] = 0x7fffffff;
         }
     }
+    const int h0 = st.nj & 1, h1 = h0 ^ 1;
+    if (T.lead()) {
+        c->fq_tail[h0] = 0;
+        c->fh_tail[h0] = 0;
+    }
+    const int32_t next = st.k + 1 < top ? st.k + 1 : -1;  // degree of the next level, if it is near
     VStream tv{wave_buf(0), a.q.eq[fb], &c->eq_tail[fn]}, bn{wave_buf(1), nlist, &c->nr_count[n1]},
-        bf{wave_buf(2), flist, &c->rm_count[f1]};
-    CStream tc{wave_buf(3), a.q.eh[fb], &c->eh_tail[fn], g.len, a.t.chunk};
+        bf{wave_buf(2), flist, &c->rm_count[f1]}, bx{wave_buf(4), a.q.chg, &c->fq_tail[h1]};
+    CStream tc{wave_buf(3), a.q.eh[fb], &c->eh_tail[fn], g.len, a.t.chunk},
+        xc{wave_buf(5), a.q.fh[0], &c->fh_tail[h1], g.len, a.t.chunk};
     int32_t fmin = 0x7fffffff, nmin = 0x7fffffff;
     const int32_t span = wave_span(n);
     for (int32_t base = T.wave() * span; base < n; base += T.nwaves() * span) {
@@ -2943,15 +2962,20 @@ __device__ __forceinline__ void dec_sweep(const KArgs &a, const DState &st, cons
             const bool near = live && !take && dv[u] < top;
             const bool keep = live && far && dv[u] >= top;
             if (take) g.core[v[u]] = st.k;
-            if (__ballot(take)) push_len(a, tv, tc, v[u], take ? g.len[v[u]] : 0, take, a.t.large_deg);
+            const bool soon = near && dv[u] == next;
+            if (__ballot(take || soon)) {
+                const int32_t L = take || soon ? g.len[v[u]] : 0;
+                push_len(a, tv, tc, v[u], L, take, a.t.large_deg);
+                push_len(a, bx, xc, v[u], L, soon, a.t.large_deg);
+            }
             vs_push(a, bn, v[u], near);
             vs_push(a, bf, v[u], keep);
             if (near) nmin = dv[u] < nmin ? dv[u] : nmin;
             if (keep) fmin = dv[u] < fmin ? dv[u] : fmin;
         }
     }
-    VStream *const vs[3] = {&tv, &bn, &bf};
-    CStream *const cs[1] = {&tc};
+    VStream *const vs[4] = {&tv, &bn, &bf, &bx};
+    CStream *const cs[2] = {&tc, &xc};
     block_flush(a, vs, cs);
     // smallest degrees (the maxima of their complements)
     const int32_t nm = 0x7fffffff - __builtin_amdgcn_readlane(wave_incl_max(0x7fffffff - nmin), WAVE - 1);
@@ -2969,8 +2993,12 @@ __device__ __forceinline__ void dec_round(const KArgs &a, const DState &st, cons
     const DevGraph &g = a.g;
     const int sc = st.f % 3, sn = (st.f + 1) % 3, sx = (st.f + 2) % 3;
     const int bc = st.f & 1, bn = bc ^ 1;
-    const int32_t nq = sqlen(st.sn, c, &c->eq_tail[sc], a.q.vcap);
-    const int32_t nh = sqlen(st.sn, c, &c->eh_tail[sc], a.q.hcap);
+    const int hs = st.nj & 1;
+    const bool listed = st.half == 1;  // the frontier is the next-level list
+    const int32_t *vq = listed ? a.q.chg : a.q.eq[bc];
+    const int64_t *hq = listed ? a.q.fh[0] : a.q.eh[bc];
+    const int32_t nq = sqlen(st.sn, c, listed ? &c->fq_tail[hs] : &c->eq_tail[sc], a.q.vcap);
+    const int32_t nh = sqlen(st.sn, c, listed ? &c->fh_tail[hs] : &c->eh_tail[sc], a.q.hcap);
     if (T.lead()) {
         c->eq_tail[sx] = 0; c->eh_tail[sx] = 0;
         c->dec_rounds += 1;
@@ -2978,6 +3006,8 @@ __device__ __forceinline__ void dec_round(const KArgs &a, const DState &st, cons
     const int32_t k = st.k, top = st.top;
     int32_t *nlist = st.nj & 1 ? a.q.touched : a.q.cand;
     int32_t *ntail = &c->nr_count[st.nj % 3];
+    // a degree that falls from here joins the next level's list
+    const int32_t above = st.half == 0 && k + 1 < top ? k + 2 : -1;
     auto s1 = [&](Ent &e) __attribute__((always_inline)) {
         e.a = -1;
         if (e.w >= 0) e.a = g.core[e.w];
@@ -2987,42 +3017,61 @@ __device__ __forceinline__ void dec_round(const KArgs &a, const DState &st, cons
         if (e.a == -2) e.b = atomicSub(&g.cd[e.w], 1);
     };
     auto s3 = [&](Ent &) __attribute__((always_inline)) {};
-    enum : int32_t { GONE = 1, NEAR = 2 };
+    enum : int32_t { GONE = 1, NEAR = 2, NEXT = 4 };
     auto s4 = [&](Ent &e) __attribute__((always_inline)) {
-        e.a = e.b == k + 1 ? GONE : (e.b == top ? NEAR : 0);
+        e.a = e.b == k + 1 ? GONE : (e.b == top ? NEAR : 0) | (e.b == above ? NEXT : 0);
         if (e.a == GONE) g.core[e.w] = k;
     };
     Pusher pq = make_pusher(a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn], g.len, a.t.large_deg,
                             a.t.chunk);
-    VStream near{wave_buf(3), nlist, ntail};
+    VStream near{wave_buf(3), nlist, ntail}, bx{wave_buf(4), a.q.chg, &c->fq_tail[hs]};
+    CStream xc{wave_buf(5), a.q.fh[0], &c->fh_tail[hs], g.len, a.t.chunk};
     auto fin = [&](int32_t w, int32_t f) {
         if (__ballot(f != 0) == 0ull) return;
-        push_deep(a, pq, w, f == GONE);
-        vs_push(a, near, w, f == NEAR);
+        const int32_t L = f & (GONE | NEXT) ? g.len[w] : 0;
+        push_deep(a, pq, w, L, f == GONE);
+        push_len(a, bx, xc, w, L, (f & NEXT) != 0, a.t.large_deg);
+        vs_push(a, near, w, (f & NEAR) != 0);
     };
-    for_chunks(T, a.q.eh[bc], nh, g, g.len, a.t.chunk, nullptr,
-               [&](int32_t, int32_t lo, int32_t hi, int32_t, int32_t, int64_t o, int32_t) {
+    // In the next-level list, what has a core number below k is gone (k: another
+    // item of the same list has been here).
+    for_chunks(T, hq, nh, g, g.len, a.t.chunk, nullptr,
+               [&](int32_t v, int32_t lo, int32_t hi, int32_t, int32_t cv, int64_t o, int32_t) {
+        if (listed) {
+            if (cv != -2 && cv != k) return;
+            if (lane() == 0) g.core[v] = k;
+        }
         if (lane() == 0) acc.scanned += hi - lo;
         wave_walk_st(g.nbr + o, lo, hi, k, s1, s2, s3, s4, fin);
     });
-    for_batches_deep(T, a.q.eq[bc], nq, pq, [&](int32_t v, int32_t) {
-        const int32_t L = v >= 0 ? g.len[v] : 0;
+    for_batches_deep(T, vq, nq, pq, [&](int32_t v, int32_t) {
+        int32_t L = v >= 0 ? g.len[v] : 0;
+        if (listed) {
+            const int32_t cv = v >= 0 ? g.core[v] : 0;
+            const bool in = v >= 0 && (cv == -2 || cv == k);
+            if (in) g.core[v] = k;
+            v = in ? v : -1;
+            L = in ? L : 0;
+        }
         acc.scanned += L;
         return flat_walk_st(
             g.nbr, g, v, L, k, s1, s2, s3, s4,
             [&](int32_t, int32_t w, int32_t f, unsigned long long, int64_t, int32_t) { fin(w, f); });
     }, DEC_DEEP, DEC_WIDE);
-    VStream *const vs[2] = {&pq.v, &near};
-    CStream *const cs[2] = {&pq.m, &pq.h};
+    VStream *const vs[3] = {&pq.v, &near, &bx};
+    CStream *const cs[3] = {&pq.m, &pq.h, &xc};
     block_flush(a, vs, cs);
 }
 
 __device__ __forceinline__ bool dec_block_local_ok(const KArgs &a, const DState &st, const Team &T) {
     if (st.step != D_ROUND) return true;
     Ctl *c = a.ctl;
-    const int s = st.f % 3;
-    long long w = queue_work(a, T, a.q.eq[st.f & 1], sqlen(st.sn, c, &c->eq_tail[s], a.q.vcap),
-                             sqlen(st.sn, c, &c->eh_tail[s], a.q.hcap), a.t.large_deg, a.g.len);
+    const int s = st.f % 3, hs = st.nj & 1;
+    const bool listed = st.half == 1;
+    long long w = queue_work(a, T, listed ? a.q.chg : a.q.eq[st.f & 1],
+                             sqlen(st.sn, c, listed ? &c->fq_tail[hs] : &c->eq_tail[s], a.q.vcap),
+                             sqlen(st.sn, c, listed ? &c->fh_tail[hs] : &c->eh_tail[s], a.q.hcap), a.t.large_deg,
+                             a.g.len);
     return w <= a.t.local_work;
 }
 
@@ -3034,8 +3083,10 @@ __device__ __forceinline__ bool dec_is_local(const KArgs &a, const DState &st) {
     if (st.step == D_FAR)
         return (st.j == 0 ? a.g.n_ids : sqlen(st.sn, c, &c->rm_count[st.j % 3], a.q.vcap)) <= DEC_LOCAL_SWEEP;
     if (st.step == D_NEAR) return sqlen(st.sn, c, &c->nr_count[st.nj % 3], a.q.vcap) <= DEC_LOCAL_SWEEP;
-    const int s = st.f % 3;
-    return frontier_work(a, sqlen(st.sn, c, &c->eq_tail[s], a.q.vcap), sqlen(st.sn, c, &c->eh_tail[s], a.q.hcap)) <= a.t.local_items;
+    const int s = st.f % 3, hs = st.nj & 1;
+    const bool listed = st.half == 1;
+    return frontier_work(a, sqlen(st.sn, c, listed ? &c->fq_tail[hs] : &c->eq_tail[s], a.q.vcap),
+                         sqlen(st.sn, c, listed ? &c->fh_tail[hs] : &c->eh_tail[s], a.q.hcap)) <= a.t.local_items;
 }
 
 __device__ __forceinline__ DState dec_next(const KArgs &a, const DState &st) {
@@ -3047,7 +3098,12 @@ __device__ __forceinline__ DState dec_next(const KArgs &a, const DState &st) {
         nx.j = st.j + 1;
         nx.top = dec_top(st.k);
     }
-    if (st.step != D_ROUND) nx.nj = st.nj + 1;
+    if (st.step != D_ROUND) {
+        nx.nj = st.nj + 1;
+        nx.half = 0;
+    } else if (st.half == 1) {
+        nx.half = 2;
+    }
     const int fs = nx.f % 3;
     const int32_t front = snap_word(nx.sn, c, &c->eq_tail[fs]) + snap_word(nx.sn, c, &c->eh_tail[fs]);
     const int32_t near = snap_word(nx.sn, c, &c->nr_count[nx.nj % 3]);
@@ -3058,9 +3114,19 @@ __device__ __forceinline__ DState dec_next(const KArgs &a, const DState &st) {
         nx.step = D_ROUND;
         return nx;
     }
-    // the level is done; smallest degrees of the lists are known right after
-    // a sweep that took nothing (no round has lowered them since)
+    // the level is done; the next one is listed if a sweep found this one
     nx.k = st.k + 1;
+    if (nx.half == 0 && nx.k < nx.top) {
+        const int hs = nx.nj & 1;
+        if (snap_word(nx.sn, c, &c->fq_tail[hs]) + snap_word(nx.sn, c, &c->fh_tail[hs]) != 0) {
+            nx.step = D_ROUND;
+            nx.half = 1;
+            return nx;
+        }
+        nx.k += 1;
+    }
+    // smallest degrees of the lists are known right after a sweep that took
+    // nothing (no round has lowered them since)
     if (st.step != D_ROUND && near != 0 && nmin > nx.k) nx.k = nmin;
     if (near != 0 && nx.k < nx.top) {
         nx.step = D_NEAR;
@@ -3078,9 +3144,8 @@ __device__ __forceinline__ DState dec_next(const KArgs &a, const DState &st) {
 
 __device__ __forceinline__ void decompose(const KArgs &a, Acc &acc) {
     Ctl *c = a.ctl;
-    DState st{D_FAR, 0, 0, 0, 0, 0, dec_snap(c)};
+    DState st{D_FAR, 0, 0, 0, 0, 0, 0, dec_snap(c)};
     int pubs = 0;
-    int32_t kmax = 0;
     bool force = false, chain = false;
     unsigned long long tl = 0;
     int links = 0;
@@ -3105,7 +3170,6 @@ __device__ __forceinline__ void decompose(const KArgs &a, Acc &acc) {
             const Team T = chain ? block_team() : grid_team();
             if (st.step == D_ROUND) {
                 dec_round(a, st, T, acc);
-                kmax = st.k;
             } else {
                 dec_sweep(a, st, T);
             }
@@ -3128,7 +3192,7 @@ __device__ __forceinline__ void decompose(const KArgs &a, Acc &acc) {
                 if (chain && threadIdx.x == 0) {
                     int32_t *p = c->dpub[slot];
                     p[0] = st.step; p[1] = st.k; p[2] = st.j; p[3] = st.f;
-                    p[4] = st.top; p[5] = st.nj; p[6] = kmax; p[7] = fg ? 1 : 0;
+                    p[4] = st.top; p[5] = st.nj; p[6] = st.half; p[7] = fg ? 1 : 0;
                 }
                 gbar(a.bar);
                 const int32_t w = lane() < 8 ? ld_rlx(&c->dpub[slot][lane()]) : 0;
@@ -3138,7 +3202,7 @@ __device__ __forceinline__ void decompose(const KArgs &a, Acc &acc) {
                 st.f = __builtin_amdgcn_readlane(w, 3);
                 st.top = __builtin_amdgcn_readlane(w, 4);
                 st.nj = __builtin_amdgcn_readlane(w, 5);
-                kmax = __builtin_amdgcn_readlane(w, 6);
+                st.half = __builtin_amdgcn_readlane(w, 6);
                 force = __builtin_amdgcn_readlane(w, 7) != 0;
                 st.sn = dec_snap(c);
                 ++pubs;
@@ -3146,7 +3210,6 @@ __device__ __forceinline__ void decompose(const KArgs &a, Acc &acc) {
             }
         }
     }
-    if (gtid() == 0) c->kmax = kmax;
 }
 
 }  // namespace cm

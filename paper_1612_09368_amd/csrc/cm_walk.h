@@ -244,12 +244,14 @@ __device__ __forceinline__ Pusher make_pusher(int32_t *vq, int32_t *vtail, int64
     return Pusher{VStream{wave_buf(0), vq, vtail}, CStream{wave_buf(1), hq, htail, lens, chunk},
                   CStream{wave_buf(2), hq, htail, lens, chunk}, large};
 }
-__device__ __forceinline__ void push_deep(const KArgs &a, Pusher &p, int32_t w, bool pred) {
-    if (__ballot(pred) == 0ull) return;
-    const int32_t L = pred ? p.m.lens[w] : 0;
+__device__ __forceinline__ void push_deep(const KArgs &a, Pusher &p, int32_t w, int32_t L, bool pred) {
     vs_push(a, p.v, w, pred && L <= p.large);
     cs_push(a, p.m, w, pred && L > p.large && L <= DEEP_LIST);
     cs_push(a, p.h, w, pred && L > p.large && L > DEEP_LIST);
+}
+__device__ __forceinline__ void push_deep(const KArgs &a, Pusher &p, int32_t w, bool pred) {
+    if (__ballot(pred) == 0ull) return;
+    push_deep(a, p, w, pred ? p.m.lens[w] : 0, pred);
 }
 // A vertex whose walk is not the wave's to go on with: v or c by its length L.
 __device__ __forceinline__ void push_len(const KArgs &a, VStream &v, CStream &c, int32_t w, int32_t L, bool pred,

@@ -127,6 +127,39 @@ def test_decompose_level_gaps(sizes):
         _check(g, ref)
 
 
+@pytest.mark.parametrize("joint", [0, 1, 10 ** 6], ids=["apart", "one", "matched"])
+@pytest.mark.parametrize("sizes", [[3, 4, 5], list(range(3, 30)), [9, 10, 11, 12, 13], [63, 64, 65, 66, 67],
+                                   [512, 513, 514], [700, 701, 702, 703]], ids=lambda x: f"{x[0]}to{x[-1]}")
+def test_decompose_two_levels_a_sweep(sizes, joint):
+    """Cliques of successive sizes, joined by edges to the next: a level's
+    removals lower the next level's vertices to its degree, short and long
+    lists.  A path and a hub of paths: all that level 2 has listed goes with
+    level 1."""
+    n, s, d = _cliques(sizes)
+    s, d = [s], [d]
+    base = 0
+    for x in sizes[:-1]:
+        i = np.arange(min(x, joint))
+        s.append(base + i)
+        d.append(base + x + i)
+        base += x
+    p = n + np.arange(2999)
+    s.append(p)
+    d.append(p + 1)
+    hub = n + 3000
+    arm = hub + 1 + np.arange(600)
+    s += [np.full(600, hub), arm]
+    d += [arm, arm + 600]
+    n = hub + 1201
+    s, d = np.concatenate(s).astype(np.int32), np.concatenate(d).astype(np.int32)
+    ref = oracle.DynamicGraph(n, s, d)
+    with cm.Graph() as g:
+        g.load(n, s, d)
+        for _ in range(2):
+            g.decompose()
+            _check(g, ref)
+
+
 @pytest.mark.parametrize("mode", [cm.MODE_PLAIN, cm.MODE_PERSISTENT])
 def test_vertex_stars_filter_mode(mode):
     """One-call vertex operations with invalid items, dropped one by one."""

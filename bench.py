@@ -50,7 +50,7 @@ HBM_PEAK_GBS = 8000.0
 # summaries and commands are under profiles/).
 TRAFFIC = {
     "rmat22-stream": {"kernel": "k_program", "bytes_per_launch": 1823.8e9,
-                      "sources_sha256": "73aeca9faa33b648c701ded45664c2365fc599e7c4bbf2511f6f094d2205a1da"},
+                      "sources_sha256": "be9a425d9bfff19c69ccc190168cf2d15a386d3ec688581b0ba911c0fcb8428a"},
 }
 KERNEL_SOURCES = ["cm_internal.h", "cm_kernels.hip", "cm_phases.h", "cm_walk.h"]
 

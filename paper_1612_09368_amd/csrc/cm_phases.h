@@ -740,8 +740,8 @@ __device__ __forceinline__ void part_select(const KArgs &a, const Iter &it, int 
     VStream bq{wave_buf(0), it.ins ? a.q.fq[0] : a.q.eq[0], it.ins ? &c->fq_tail[0] : &c->eq_tail[0]};
     VStream bchg{wave_buf(1), a.q.chg, &c->chg_count};
     VStream brem{wave_buf(2), a.b.rem[it.cur ^ 1], &c->rem_count[it.cur ^ 1]};
-    CStream bh{wave_buf(3), a.q.eh[0], &c->eh_tail[0], a.g.len, a.t.chunk};
-    CStream bchh{wave_buf(4), a.q.chh, &c->chh_count, a.g.len, a.t.chunk};
+    CStream bh{wave_buf(3), wave_lens(0), a.q.eh[0], &c->eh_tail[0], a.t.chunk};
+    CStream bchh{wave_buf(4), wave_lens(1), a.q.chh, &c->chh_count, a.t.chunk};
     for_span(T, it.n_r, [&](int32_t idx) {
         const int32_t i = idx >= 0 ? R[idx] : -1;
         const bool open = i >= 0 && !(r > 0 && a.b.esel[i] == it.ep);  // not taken in an earlier round
@@ -1499,7 +1499,7 @@ __device__ __forceinline__ void expand_round(const KArgs &a, const Iter &it, int
     Pusher pq = make_pusher(a.q.fq[bn], &c->fq_tail[sn], a.q.fh[bn], &c->fh_tail[sn], g.len, a.t.large_deg,
                             a.t.chunk);
     VStream ev{wave_buf(3), a.q.eq[0], &c->eq_tail[0]}, cand{wave_buf(5), a.q.cand, &c->cand_count};
-    CStream eh{wave_buf(4), a.q.eh[0], &c->eh_tail[0], sl ? g.slen : g.len, sl ? evict_chunk(a) : a.t.chunk};
+    CStream eh{wave_buf(4), wave_lens(2), a.q.eh[0], &c->eh_tail[0], sl ? evict_chunk(a) : a.t.chunk};
     auto push_next = [&](int32_t w, bool p) { push_deep(a, pq, w, p); };
     // an evicted vertex's walk is its supporter run (sublists) or its list
     auto push_evict = [&](int32_t v, bool p, int32_t nsup) {
@@ -1683,7 +1683,7 @@ __device__ __forceinline__ void evict_round(const KArgs &a, const Iter &it, int 
         return L < len ? L : len;  // never past the list, even on a count left from another iteration
     };
     // long walks, item by item (slen never passes the list: see walk_len)
-    for_chunks(T, a.q.eh[bc], nh, g, pq.m.lens, pq.m.chunk, sl ? g.len : nullptr,
+    for_chunks(T, a.q.eh[bc], nh, g, pq.lens, pq.m.chunk, sl ? g.len : nullptr,
                [&](int32_t, int32_t lo, int32_t hi, int32_t, int32_t k, int64_t o, int32_t len) {
         if (sl && hi > len) hi = len;
         if (hi <= lo) return;
@@ -1725,7 +1725,7 @@ __device__ __forceinline__ void peel_round(const KArgs &a, const Iter &it, int r
     Pusher pq = make_pusher(a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn], g.len, a.t.large_deg,
                             a.t.chunk);
     VStream touched{wave_buf(3), a.q.touched, &c->touched_count}, chg{wave_buf(4), a.q.chg, &c->chg_count};
-    CStream chh{wave_buf(5), a.q.chh, &c->chh_count, g.len, a.t.chunk};
+    CStream chh{wave_buf(5), wave_lens(2), a.q.chh, &c->chh_count, a.t.chunk};
     // cores and SD do not change during a peel round
     auto s1 = [&](Ent &e) __attribute__((always_inline)) {
         e.a = -1;
@@ -1792,7 +1792,7 @@ __device__ __forceinline__ void apply_core(const KArgs &a, const Iter &it, const
             c->st_icand += (unsigned long long)n;
         }
         VStream chg{wave_buf(0), a.q.chg, &c->chg_count};
-        CStream chh{wave_buf(1), a.q.chh, &c->chh_count, g.len, a.t.chunk};
+        CStream chh{wave_buf(1), wave_lens(0), a.q.chh, &c->chh_count, a.t.chunk};
         int32_t moved = 0;  // uniform
         for_span(T, n, [&](int32_t idx) {
             int32_t v = -1, k = 0, L = 0;
@@ -2934,8 +2934,8 @@ __device__ __forceinline__ void dec_sweep(const KArgs &a, const DState &st, cons
     const int32_t next = st.k + 1 < top ? st.k + 1 : -1;  // degree of the next level, if it is near
     VStream tv{wave_buf(0), a.q.eq[fb], &c->eq_tail[fn]}, bn{wave_buf(1), nlist, &c->nr_count[n1]},
         bf{wave_buf(2), flist, &c->rm_count[f1]}, bx{wave_buf(4), a.q.chg, &c->fq_tail[h1]};
-    CStream tc{wave_buf(3), a.q.eh[fb], &c->eh_tail[fn], g.len, a.t.chunk},
-        xc{wave_buf(5), a.q.fh[0], &c->fh_tail[h1], g.len, a.t.chunk};
+    CStream tc{wave_buf(3), wave_lens(0), a.q.eh[fb], &c->eh_tail[fn], a.t.chunk},
+        xc{wave_buf(5), wave_lens(1), a.q.fh[0], &c->fh_tail[h1], a.t.chunk};
     int32_t fmin = 0x7fffffff, nmin = 0x7fffffff;
     const int32_t span = wave_span(n);
     for (int32_t base = T.wave() * span; base < n; base += T.nwaves() * span) {
@@ -3025,7 +3025,7 @@ __device__ __forceinline__ void dec_round(const KArgs &a, const DState &st, cons
     Pusher pq = make_pusher(a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn], g.len, a.t.large_deg,
                             a.t.chunk);
     VStream near{wave_buf(3), nlist, ntail}, bx{wave_buf(4), a.q.chg, &c->fq_tail[hs]};
-    CStream xc{wave_buf(5), a.q.fh[0], &c->fh_tail[hs], g.len, a.t.chunk};
+    CStream xc{wave_buf(5), wave_lens(2), a.q.fh[0], &c->fh_tail[hs], a.t.chunk};
     auto fin = [&](int32_t w, int32_t f) {
         if (__ballot(f != 0) == 0ull) return;
         const int32_t L = f & (GONE | NEXT) ? g.len[w] : 0;

@@ -115,18 +115,28 @@ __device__ __forceinline__ void wb_push(WaveBuf &b, int32_t *q, int32_t qcap, in
 }
 // Two kinds of streams that a step pushes to: vertices to a vertex queue, and
 // vertices with long walks to a chunk queue, as items of `chunk` entries of
-// their walk (lens: the walk lengths).  Both collect in a wave buffer.
+// their walk.  Both collect in a wave buffer; a chunk stream keeps each
+// vertex's walk length beside it, as its pusher had it.  The length is not read
+// again at the flush: a supporter run of the expansion gets its length from
+// atomics of other CUs in the same step, and a plain read may still return an
+// older one from this CU's L1 (another wave of the workgroup has read a
+// neighbouring word), which would leave the end of the run unwalked.
 struct VStream {
     WaveBuf b;
     int32_t *q, *tail;
 };
 struct CStream {
     WaveBuf b;
+    int32_t *len;  // walk lengths of the buffer's entries
     int64_t *q;
     int32_t *tail;
-    const int32_t *lens;
     int32_t chunk;
 };
+constexpr int CHUNK_STREAMS = 3;  // of one step
+__device__ __forceinline__ int32_t *wave_lens(int i) {
+    __shared__ int32_t lds_lens[CHUNK_STREAMS][COOP_THREADS / WAVE][2 * WAVE];
+    return lds_lens[i][threadIdx.x / WAVE];
+}
 __device__ __forceinline__ void vs_push(const KArgs &a, VStream &s, int32_t w, bool pred) {
     wb_push(s.b, s.q, a.q.vcap, s.tail, w, pred, &a.ctl->overflow);
 }
@@ -135,15 +145,19 @@ __device__ __forceinline__ void cs_flush(const KArgs &a, CStream &s) {
     for (int i0 = 0; i0 < s.b.n; i0 += WAVE) {
         const bool has = i0 + lane() < s.b.n;
         const int32_t w = has ? s.b.buf[i0 + lane()] : -1;
-        push_chunks(a, s.q, s.tail, w, has ? nchunks(s.lens[w], s.chunk) : 0);
+        push_chunks(a, s.q, s.tail, w, has ? nchunks(s.len[i0 + lane()], s.chunk) : 0);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // reads done before the slots are reused
     s.b.n = 0;
 }
-__device__ __forceinline__ void cs_push(const KArgs &a, CStream &s, int32_t w, bool pred) {
+__device__ __forceinline__ void cs_push(const KArgs &a, CStream &s, int32_t w, int32_t L, bool pred) {
     const unsigned long long m = __ballot(pred);
     if (m == 0ull) return;
-    if (pred) s.b.buf[s.b.n + __popcll(m & lanes_below())] = w;
+    if (pred) {
+        const int32_t i = s.b.n + __popcll(m & lanes_below());
+        s.b.buf[i] = w;
+        s.len[i] = L;
+    }
     s.b.n += __popcll(m);
     if (s.b.n >= WAVE) cs_flush(a, s);
 }
@@ -177,7 +191,7 @@ __device__ __forceinline__ void block_flush(const KArgs &a, VStream *const (&vs)
                 const bool has = h * WAVE + lane() < s.b.n;
                 if (has) {
                     w[i][h] = s.b.buf[h * WAVE + lane()];
-                    nch[i][h] = nchunks(s.lens[w[i][h]], s.chunk);
+                    nch[i][h] = nchunks(s.len[h * WAVE + lane()], s.chunk);
                 }
                 incl[i][h] = wave_incl_add(nch[i][h]);
                 mine[NV + i] += __builtin_amdgcn_readlane(incl[i][h], WAVE - 1);
@@ -237,27 +251,28 @@ constexpr int DEEP_LIST = 512;
 struct Pusher {
     VStream v;
     CStream m, h;
+    const int32_t *lens;  // walk lengths (they do not change during the step)
     int32_t large;
 };
 __device__ __forceinline__ Pusher make_pusher(int32_t *vq, int32_t *vtail, int64_t *hq, int32_t *htail,
                                               const int32_t *lens, int32_t large, int32_t chunk) {
-    return Pusher{VStream{wave_buf(0), vq, vtail}, CStream{wave_buf(1), hq, htail, lens, chunk},
-                  CStream{wave_buf(2), hq, htail, lens, chunk}, large};
+    return Pusher{VStream{wave_buf(0), vq, vtail}, CStream{wave_buf(1), wave_lens(0), hq, htail, chunk},
+                  CStream{wave_buf(2), wave_lens(1), hq, htail, chunk}, lens, large};
 }
 __device__ __forceinline__ void push_deep(const KArgs &a, Pusher &p, int32_t w, int32_t L, bool pred) {
     vs_push(a, p.v, w, pred && L <= p.large);
-    cs_push(a, p.m, w, pred && L > p.large && L <= DEEP_LIST);
-    cs_push(a, p.h, w, pred && L > p.large && L > DEEP_LIST);
+    cs_push(a, p.m, w, L, pred && L > p.large && L <= DEEP_LIST);
+    cs_push(a, p.h, w, L, pred && L > p.large && L > DEEP_LIST);
 }
 __device__ __forceinline__ void push_deep(const KArgs &a, Pusher &p, int32_t w, bool pred) {
     if (__ballot(pred) == 0ull) return;
-    push_deep(a, p, w, pred ? p.m.lens[w] : 0, pred);
+    push_deep(a, p, w, pred ? p.lens[w] : 0, pred);
 }
 // A vertex whose walk is not the wave's to go on with: v or c by its length L.
 __device__ __forceinline__ void push_len(const KArgs &a, VStream &v, CStream &c, int32_t w, int32_t L, bool pred,
                                          int32_t large) {
     vs_push(a, v, w, pred && L <= large);
-    cs_push(a, c, w, pred && L > large);
+    cs_push(a, c, w, L, pred && L > large);
 }
 // ... one list at a time, straight to the chunk queue (steps without streams)
 __device__ __forceinline__ void push_vertex_wb(const KArgs &a, WaveBuf &b, int32_t *vq, int32_t *vtail,

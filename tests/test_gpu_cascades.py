@@ -266,3 +266,44 @@ def test_batch_sizes_around_wave_spans(s, mode):
     first, batch = keys[:60000], keys[60000:60000 + s]
     _round_trip(n, *(x.astype(np.int32) for x in divmod(np.concatenate([first, batch]), n)),
                 np.stack(divmod(batch, n), 1), dict(mode=mode))
+
+
+@pytest.mark.parametrize("cfg", [dict(mode=cm.MODE_PLAIN), dict(mode=cm.MODE_PERSISTENT),
+                                 dict(mode=cm.MODE_PERSISTENT, local_items=1, chunk=32),
+                                 dict(mode=cm.MODE_PERSISTENT, local_items=1, chunk=64, large_degree=64)],
+                         ids=["plain", "persistent", "grid-chunk32", "grid-chunk64"])
+@pytest.mark.parametrize("share", [160, 200, 240])
+def test_long_supporter_runs_of_neighbouring_hubs(share, cfg):
+    """Hubs with successive ids, counted by many chunks each and evicted as
+    soon as they are counted, with supporter runs longer than one wave step: a
+    140-regular graph, and a matching on `share` of its vertices that gives no
+    vertex k + 1 supporters, so all of it is a candidate and all of it falls."""
+    rng = np.random.RandomState(share)
+    nd, half, hubs, leaves = 300, 70, 32, 6000
+    i = np.repeat(np.arange(nd), half)
+    j = (i + np.tile(np.arange(1, half + 1), nd)) % nd
+    s, d = [np.minimum(i, j)], [np.maximum(i, j)]
+    for h in range(hubs):
+        leaf = nd + rng.choice(leaves, rng.randint(300, 1400), replace=False)
+        s.append(np.full(leaf.size, h))
+        d.append(leaf)
+    s, d = np.concatenate(s), np.concatenate(d)
+    order = rng.permutation(s.size)
+    n, s, d = nd + leaves, s[order].astype(np.int32), d[order].astype(np.int32)
+    ref = oracle.DynamicGraph(n, s, d)
+    before = ref.cores()
+    assert (before[:nd] == 2 * half).all()
+    with cm.Graph(**cfg) as g:
+        g.load(n, s, d)
+        g.decompose()
+        for _ in range(4):
+            # opposite vertices are no neighbours
+            x = np.concatenate([np.arange(hubs), hubs + rng.permutation(nd // 2 - hubs)[:share // 2 - hubs]])
+            a, b = x.astype(np.int32), (x + nd // 2).astype(np.int32)
+            g.insert_edges(a, b)
+            ref.insert_edges(a, b)
+            _check(g, ref)
+            assert np.array_equal(ref.cores(), before)
+            g.delete_edges(a, b)
+            ref.delete_edges(a, b)
+            _check(g, ref)

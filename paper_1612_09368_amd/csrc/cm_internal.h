@@ -13,6 +13,7 @@
 #include <stdint.h>
 
 #include "cm_keys.h"
+#include "cm_steps.h"
 
 namespace cm {
 
@@ -741,6 +742,40 @@ __device__ __forceinline__ bool slice_over(const Bar *b, unsigned long long t0) 
     const bool r = over != 0;
     __syncthreads();
     return r;
+}
+
+// In workgroup 0, before step CHAIN_FREE + 1 of a chain: waits until every other
+// workgroup has arrived at the barrier that ends the chain, so that none is
+// left that has yet to look at the counters of the barrier before it.  The
+// arrivals are those of gbar: all but this workgroup on its own XCC's counter,
+// all the other XCCs on the top one (both are zero again before gbar lets
+// anyone go).  They arrive while the first step runs (the others have nothing
+// else to do), so this is two loads as a rule.  False if the barrier was
+// aborted.  Every thread of the workgroup must call it, once per chain.
+__device__ __forceinline__ bool chain_alone(Bar *b) {
+    __shared__ int alone;
+    if (threadIdx.x == 0) {
+        const unsigned *info = bar_info();
+        const unsigned x = info[0], members = info[1], ngroups = info[2];
+        const unsigned long long t0 = (unsigned long long)wall_clock64();
+        int ok = 1;
+        for (;;) {
+            const unsigned own = __hip_atomic_load(&b->grp[x * 32], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned top = __hip_atomic_load(&b->top[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (own == members - 1u && top == ngroups - 1u) break;
+            if (__hip_atomic_load(&b->abort[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) { ok = 0; break; }
+            if ((unsigned long long)wall_clock64() - t0 >
+                __hip_atomic_load(&b->wait_ticks[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+                __hip_atomic_store(&b->abort[0], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                ok = 0;
+                break;
+            }
+            __builtin_amdgcn_s_sleep(2);
+        }
+        alone = ok;
+    }
+    __syncthreads();
+    return uniform(alone) != 0;
 }
 
 __device__ __forceinline__ bool bar_aborted(Bar *b) {

@@ -1442,7 +1442,7 @@ __device__ __forceinline__ void expand_round_pruned(const KArgs &a, const Iter &
 __device__ __forceinline__ void expand_round(const KArgs &a, const Iter &it, int r, const Team &T, Acc &acc) {
     Ctl *c = a.ctl;
     const DevGraph &g = a.g;
-    const int sc = r % 3, sn = (r + 1) % 3, sx = (r + 2) % 3;
+    const int sc = slot_read(r), sn = slot_push(r), sx = slot_clear(r);
     const int bc = r & 1, bn = bc ^ 1;
     const int32_t nq = sqlen(it.sn, c, &c->fq_tail[sc], a.q.vcap);
     const int32_t nh = sqlen(it.sn, c, &c->fh_tail[sc], a.q.hcap);
@@ -1638,7 +1638,7 @@ __device__ __forceinline__ void expand_round(const KArgs &a, const Iter &it, int
 __device__ __forceinline__ void evict_round(const KArgs &a, const Iter &it, int r, const Team &T, Acc &acc) {
     Ctl *c = a.ctl;
     const DevGraph &g = a.g;
-    const int sc = r % 3, sn = (r + 1) % 3, sx = (r + 2) % 3;
+    const int sc = slot_read(r), sn = slot_push(r), sx = slot_clear(r);
     const int bc = r & 1, bn = bc ^ 1;
     const int32_t nq = sqlen(it.sn, c, &c->eq_tail[sc], a.q.vcap);
     const int32_t nh = sqlen(it.sn, c, &c->eh_tail[sc], a.q.hcap);
@@ -1713,7 +1713,7 @@ __device__ __forceinline__ void evict_round(const KArgs &a, const Iter &it, int 
 __device__ __forceinline__ void peel_round(const KArgs &a, const Iter &it, int r, const Team &T, Acc &acc) {
     Ctl *c = a.ctl;
     const DevGraph &g = a.g;
-    const int sc = r % 3, sn = (r + 1) % 3, sx = (r + 2) % 3;
+    const int sc = slot_read(r), sn = slot_push(r), sx = slot_clear(r);
     const int bc = r & 1, bn = bc ^ 1;
     const int32_t nq = sqlen(it.sn, c, &c->eq_tail[sc], a.q.vcap);
     const int32_t nh = sqlen(it.sn, c, &c->eh_tail[sc], a.q.hcap);
@@ -2170,6 +2170,7 @@ __device__ __forceinline__ int run_iterations(const KArgs &a, int ins, int max_i
                 fg = true;
                 stop = true;
             }
+            if (chain && !stop && links == CHAIN_FREE && !chain_alone(a.bar)) stop = true;
             if (!stop) {
                 run_step(a, it, pc, chain ? block_team() : grid_team(), acc);
                 if (chain ? threadIdx.x == 0 : clock_thread()) ph_count(chain ? PH_LSTEPS : PH_GSTEPS);
@@ -2908,9 +2909,9 @@ __device__ __forceinline__ void dec_sweep(const KArgs &a, const DState &st, cons
     Ctl *c = a.ctl;
     const DevGraph &g = a.g;
     const bool far = st.step == D_FAR;
-    const int fn = (st.f + 1) % 3, fx = (st.f + 2) % 3, fb = (st.f + 1) & 1;
-    const int f0 = st.j % 3, f1 = (st.j + 1) % 3, f2 = (st.j + 2) % 3;
-    const int n0 = st.nj % 3, n1 = (st.nj + 1) % 3, n2 = (st.nj + 2) % 3;
+    const int fn = slot_push(st.f), fx = slot_clear(st.f), fb = (st.f + 1) & 1;
+    const int f0 = slot_read(st.j), f1 = slot_push(st.j), f2 = slot_clear(st.j);
+    const int n0 = slot_read(st.nj), n1 = slot_push(st.nj), n2 = slot_clear(st.nj);
     const int32_t *src = far ? (st.j == 0 ? nullptr : a.q.fq[st.j & 1]) : (st.nj & 1 ? a.q.touched : a.q.cand);
     int32_t *nlist = (st.nj + 1) & 1 ? a.q.touched : a.q.cand;
     int32_t *flist = a.q.fq[(st.j + 1) & 1];
@@ -2991,7 +2992,7 @@ constexpr int DEC_DEEP = 48, DEC_WIDE = 63;
 __device__ __forceinline__ void dec_round(const KArgs &a, const DState &st, const Team &T, Acc &acc) {
     Ctl *c = a.ctl;
     const DevGraph &g = a.g;
-    const int sc = st.f % 3, sn = (st.f + 1) % 3, sx = (st.f + 2) % 3;
+    const int sc = slot_read(st.f), sn = slot_push(st.f), sx = slot_clear(st.f);
     const int bc = st.f & 1, bn = bc ^ 1;
     const int hs = st.nj & 1;
     const bool listed = st.half == 1;  // the frontier is the next-level list
@@ -3166,6 +3167,7 @@ __device__ __forceinline__ void decompose(const KArgs &a, Acc &acc) {
             fg = true;
             stop = true;
         }
+        if (chain && !stop && links == CHAIN_FREE && !chain_alone(a.bar)) stop = true;
         if (!stop) {
             const Team T = chain ? block_team() : grid_team();
             if (st.step == D_ROUND) {

@@ -67,7 +67,8 @@ extern "C" {
 #define CM_E_IO (-14)       /* snapshot file missing, unreadable, corrupt or inconsistent */
 
 /* Execution forms of the update path. */
-#define CM_MODE_PLAIN 0     /* host loop: one cooperative launch per superior edge set */
+#define CM_MODE_PLAIN 0     /* host loop: one cooperative launch per superior edge set (vertex
+                               operations: one launch, see cm_batch_stats.launches) */
 #define CM_MODE_PERSISTENT 1 /* one cooperative launch loops over all sets of the batch */
 
 typedef struct cm_graph cm_graph; /* opaque; owned by the library */
@@ -122,7 +123,8 @@ typedef struct cm_config {
 
 typedef struct cm_batch_stats {
     int32_t status;         /* same value the call returned */
-    int32_t iterations;     /* superior edge sets processed */
+    int32_t iterations;     /* superior edge sets processed (vertex operations that run as vertex
+                               stars: sets of stars, then of edges between new vertices) */
     int64_t first_bad;      /* smallest invalid item index, -1 if none */
     int64_t applied;        /* edges applied to the graph */
     int64_t dropped;        /* invalid items dropped (filter mode) */
@@ -144,7 +146,11 @@ typedef struct cm_batch_stats {
     int64_t local_steps;    /* steps run inside one workgroup */
     int32_t launches;       /* maintenance kernel launches (plain mode: one per superior edge
                                set plus the empty one that ends the batch, queued before the
-                               host knew no edges were left; a batch of one edge has one) */
+                               host knew no edges were left; a batch of one edge has one;
+                               cm_insert_vertices / cm_delete_vertices: one for all sets, in
+                               which each vertex enters or leaves with its whole star, unless
+                               debug, single_edge or async_steps is set, which keep the
+                               reduction to edge sets) */
     int32_t graph_launch;   /* 1 when the launch was replayed from a hipGraph */
     int32_t group;          /* serving: requests that ran in one fused batch with this one
                                (1 = alone; the statistics above are the batch's) */

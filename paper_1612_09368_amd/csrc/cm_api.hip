@@ -980,7 +980,7 @@ int64_t edge_batch(cm_graph *g, int64_t s, bool inserting, cm_batch_stats *stats
 // address or size in KArgs changed).  Returns 1 when the graph was used.
 int launch_program(cm_graph *g, const KArgs &a) {
     hipStream_t st = g->stream;
-    if (!g->cfg.use_graph) {
+    if (!g->cfg.use_graph || g->cfg.mode == CM_MODE_PLAIN) {  // (plain: one-call vertex operations)
         HIPCHK(program_coop(a, g->coop_prog, st));
         return 0;
     }
@@ -1039,6 +1039,8 @@ void program_execute(cm_graph *g, const std::vector<ProgBatch> &pb, const int32_
     int used_graph = 0;
     double kms = 0.0;
     int launches = 0;
+    // the plain form (its vertex operations come here) times every launch
+    const bool timed = g->cfg.timing || g->cfg.mode == CM_MODE_PLAIN;
     for (int attempt = 0; attempt < 8; ++attempt) {
         ProgDesc *hd = g->h_prog;
         std::memset(hd, 0, sizeof(ProgDesc));
@@ -1062,15 +1064,15 @@ void program_execute(cm_graph *g, const std::vector<ProgBatch> &pb, const int32_
         HIPCHK(hipMemcpyAsync(g->d_prog, hd, sizeof(ProgDesc), hipMemcpyHostToDevice, st));
         KArgs a = make_args(g);
         a.prog = g->d_prog;
-        if (g->cfg.timing) HIPCHK(hipEventRecord(g->ev0, st));
+        if (timed) HIPCHK(hipEventRecord(g->ev0, st));
         used_graph |= launch_program(g, a);
-        if (g->cfg.timing) HIPCHK(hipEventRecord(g->ev1, st));
+        if (timed) HIPCHK(hipEventRecord(g->ev1, st));
         ++launches;
         HIPCHK(hipMemcpyAsync(g->h_prog, g->d_prog, sizeof(ProgDesc), hipMemcpyDeviceToHost, st));
         sync_ctl(g);
         check_abort(g);
         check_overflow(g);
-        if (g->cfg.timing) {
+        if (timed) {
             float ms = 0.f;
             HIPCHK(hipEventElapsedTime(&ms, g->ev0, g->ev1));
             kms += ms;
@@ -1118,7 +1120,8 @@ void stats_from_out(cm_graph *g, const ProgOut &o, int64_t items, int launches, 
     r->changed = (int64_t)o.changed;
     r->scanned = (int64_t)o.scanned;
     r->rounds = (int64_t)o.rounds;
-    r->local_steps = (int64_t)o.steps;
+    r->grid_steps = (int64_t)o.grid_steps;
+    r->local_steps = (int64_t)o.local_steps;
     r->group = 1;
     r->first_stamp = o.ep0;
     r->alg_bytes = alg_bytes(o);
@@ -1939,7 +1942,8 @@ void serve_collect(cm_graph *g) {
         r.changed = (int64_t)o.changed;
         r.scanned = (int64_t)o.scanned;
         r.rounds = (int64_t)o.rounds;
-        r.local_steps = (int64_t)o.steps;
+        r.grid_steps = (int64_t)o.grid_steps;
+        r.local_steps = (int64_t)o.local_steps;
         r.group = o.group;
         r.first_stamp = o.ep0;
         r.alg_bytes = alg_bytes(o);
@@ -2703,7 +2707,8 @@ int cm_run_batches(cm_graph *g, int32_t nb, const int32_t *kinds, const int64_t 
                 r.changed = (int64_t)o.changed;
                 r.scanned = (int64_t)o.scanned;
                 r.rounds = (int64_t)o.rounds;
-                r.local_steps = (int64_t)o.steps;
+                r.grid_steps = (int64_t)o.grid_steps;
+                r.local_steps = (int64_t)o.local_steps;
                 r.alg_bytes = alg_bytes(o);
                 r.cand_degree = (int64_t)o.cdeg;
                 r.evicted_degree = (int64_t)o.edeg;

@@ -337,7 +337,8 @@ struct ProgOut {
     int32_t group;       // requests in the batch that ran this one (1 unless fused)
     int32_t ep0;         // first iteration stamp of that batch
     int32_t pad;
-    unsigned long long remaining, selected, candidates, evicted, changed, scanned, rounds, steps;
+    unsigned long long remaining, selected, candidates, evicted, changed, scanned, rounds;
+    unsigned long long grid_steps, local_steps;
     unsigned long long icand, cdeg, edeg, hdeg;
 };
 // Why a serving launch ended (ServeHdr.exit_reason; 0 while it runs).

@@ -2294,7 +2294,8 @@ __device__ __forceinline__ void prog_record(const KArgs &a, ProgOut &o, int32_t 
     o.changed = c->st_changed;
     o.scanned = c->st_scanned;
     o.rounds = c->st_rounds;
-    o.steps = c->st_grid_steps + c->st_local_steps;
+    o.grid_steps = c->st_grid_steps;
+    o.local_steps = c->st_local_steps;
     o.icand = c->st_icand;
     o.cdeg = c->st_cdeg;
     o.edeg = c->st_edeg;

@@ -30,7 +30,9 @@ def test_grid_rounds_into_chains_and_back(mode, items):
     for workgroup 0; the next batch starts wide again.  The decomposition of
     the same graph narrows and widens with its levels."""
     import oracle
+    import torch
     import paper_1612_09368_amd as cm
+    assert torch.cuda.is_available()
     s, d, cut, nxt = [], [], [], 1
     for arm in [*range(3, 120), *range(120, 700, 29)]:
         ids = [0, *range(nxt, nxt + arm), 0]

@@ -862,6 +862,7 @@ bool vertex_stars(const cm_graph *g) {
 // validates, reserves, runs and compacts it, and one wait brings everything
 // back through the pinned mirror.  Returns the number of valid items.
 int64_t small_batch(cm_graph *g, int64_t s, bool inserting, bool strict, cm_batch_stats *stats) {
+    Range range("coremaint.small_batch");  // its phases are slots of the phase clock
     for (int attempt = 0; attempt < 4; ++attempt) {
         g->bstamp += 2;
         KArgs a = make_args(g);

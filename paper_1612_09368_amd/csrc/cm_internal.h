@@ -112,9 +112,9 @@ struct Ctl {
 
 // Phase-clock slots after the step kinds (0 .. 7).
 constexpr int PH_LOCAL = 8;      // a chain of steps run inside workgroup 0 (plus its barrier)
-constexpr int PH_VALIDATE = 9;   // batch validation in a batch program
-constexpr int PH_RESERVE = 10;   // capacity reservation in a batch program
-constexpr int PH_COMPACT = 11;   // tombstone compaction in a batch program
+constexpr int PH_VALIDATE = 9;   // batch validation inside a maintenance launch (program, small batch)
+constexpr int PH_RESERVE = 10;   // capacity reservation there
+constexpr int PH_COMPACT = 11;   // tombstone compaction there
 constexpr int PH_SLOTS = 16;
 
 // Grid barrier state: one arrival counter per group of workgroups (a group is
@@ -465,12 +465,17 @@ __device__ __forceinline__ void ph_count(int i) {
 __device__ __forceinline__ unsigned long long ph_start() {
     return clock_thread() ? (unsigned long long)wall_clock64() : 0ull;
 }
+// Adds the time since t0 to a slot of the workgroup's clock and returns the
+// time (the calling thread alone: thread 0 of workgroup 0 or the clock thread).
+__device__ __forceinline__ unsigned long long ph_add(int slot, unsigned long long t0) {
+    unsigned long long *p = ph_lds();
+    const unsigned long long now = (unsigned long long)wall_clock64();
+    p[slot] += now - t0;
+    p[PH_SLOTS + slot] += 1;
+    return now;
+}
 __device__ __forceinline__ void ph_stop(Ctl *, int slot, unsigned long long t0) {
-    if (clock_thread()) {
-        unsigned long long *p = ph_lds();
-        p[slot] += (unsigned long long)wall_clock64() - t0;
-        p[PH_SLOTS + slot] += 1;
-    }
+    if (clock_thread()) ph_add(slot, t0);
 }
 // Adds the workgroup's sums to the control block (global thread 0's and the
 // clock thread's; the others hold none).

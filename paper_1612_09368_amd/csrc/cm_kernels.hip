@@ -417,7 +417,9 @@ __global__ void __launch_bounds__(COOP_THREADS) k_maintain(KArgs a) {
     if (prep == PREP_OK) n = run_iterations(a, a.inserting, a.max_iters, ep, acc, pubs);
     // every step ended at a grid barrier, so the counters are final
     const int32_t left = uniform(ld_rlx(&c->rem_count[(ep + 1) & 1]));
-    if (a.compact && n > 0 && left == 0 && !bar_aborted(a.bar)) del_compact(a, grid_team());
+    const bool squeeze = a.compact && n > 0 && left == 0;
+    const unsigned long long t0 = ph_start();
+    if (squeeze && !bar_aborted(a.bar)) del_compact(a, grid_team());
     flush_acc(c, acc);
     if (gtid() == 0) {
         c->epoch = ep;
@@ -425,6 +427,10 @@ __global__ void __launch_bounds__(COOP_THREADS) k_maintain(KArgs a) {
     }
     if (!a.mirror) return;
     gbar(a.bar);  // the statistics of every workgroup are in
+    if (squeeze && clock_thread()) {  // (the workgroup's own clock has been flushed)
+        atomicAdd(&c->ph_ticks[PH_COMPACT], (unsigned long long)wall_clock64() - t0);
+        atomicAdd(&c->ph_count[PH_COMPACT], 1ull);
+    }
     if (blockIdx.x == 0) {
         const int32_t *src = reinterpret_cast<const int32_t *>(c);
         int32_t *dst = reinterpret_cast<int32_t *>(a.mirror);

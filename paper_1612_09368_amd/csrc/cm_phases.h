@@ -2315,6 +2315,9 @@ __device__ __forceinline__ int prep_small(const KArgs &a, const BatchCtx &bc) {
     Ctl *c = a.ctl;
     const Team T = block_team();
     int32_t st = PREP_OK;
+    // phase clock: workgroup 0's, which alone runs (or waits for) both phases
+    const bool clock = gtid() == 0;
+    unsigned long long t0 = clock ? (unsigned long long)wall_clock64() : 0ull;
     for (int part = 0; part < 2; ++part) {  // part 1: after a grid-wide locate scan
         if (blockIdx.x == 0) {
             if (part == 0) {
@@ -2346,6 +2349,7 @@ __device__ __forceinline__ int prep_small(const KArgs &a, const BatchCtx &bc) {
                 const int32_t bad = uniform(ld_rlx(&c->first_bad));
                 const int32_t valid = qlen(&c->rem_count[bc.cur], a.b.cap);
                 __syncthreads();  // every wave has read the counters
+                if (clock) t0 = ph_add(PH_VALIDATE, t0);
                 st = bc.strict && bad != 0x7fffffff ? PREP_BAD : valid == 0 ? PREP_NONE : PREP_OK;
                 if (st == PREP_OK) {
                     res_gain(a, bc, T);
@@ -2358,6 +2362,7 @@ __device__ __forceinline__ int prep_small(const KArgs &a, const BatchCtx &bc) {
                         else res_copy(a, T);
                     }
                 }
+                if (clock && st != PREP_BAD && st != PREP_NONE && st != PREP_COPY) ph_add(PH_RESERVE, t0);
                 if (T.lead()) {
                     c->valid_count = valid;
                     // nothing runs: not by a launch queued behind either
@@ -2372,7 +2377,10 @@ __device__ __forceinline__ int prep_small(const KArgs &a, const BatchCtx &bc) {
         else if (st == PREP_COPY) res_copy(a, grid_team());
         else return st;
         gbar(a.bar);
-        if (st == PREP_COPY) return PREP_OK;
+        if (st == PREP_COPY) {
+            if (clock) ph_add(PH_RESERVE, t0);
+            return PREP_OK;
+        }
     }
     return st;
 }

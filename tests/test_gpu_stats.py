@@ -45,3 +45,27 @@ def test_program_batches_report_both_kinds_of_steps(use_graph):
             for st in res:
                 assert st.applied == a.size
                 assert st.grid_steps > 0 if cfg else st.local_steps > 0
+
+
+@pytest.mark.parametrize("mode", [cm.MODE_PLAIN, cm.MODE_PERSISTENT])
+def test_phase_clock_of_small_batches(mode):
+    """Validation, reservation and compaction run inside the maintenance launch
+    of a small batch, and show in the phase clock: once per batch."""
+    n, s, d, (a, b) = _graph()
+    with cm.Graph(mode=mode, timing=True) as g:
+        g.load(n, s, d)
+        g.decompose()
+        for k in (1, 600):
+            g.phase_times(reset=True)
+            ins = g.insert_edges(a[:k], b[:k])
+            ph = g.phase_times(reset=True)
+            assert [ph[p][1] for p in ("validate", "reserve", "compact")] == [1, 1, 0]
+            assert all(0.0 < ph[p][0] < ins.kernel_ms for p in ("validate", "reserve"))
+            dele = g.delete_edges(a[:k], b[:k])
+            ph = g.phase_times(reset=True)
+            assert [ph[p][1] for p in ("validate", "reserve", "compact")] == [1, 1, 1]
+            assert all(0.0 < ph[p][0] < dele.kernel_ms for p in ("validate", "reserve", "compact"))
+        with pytest.raises(cm.CoreMaintError):
+            g.insert_edges(s[:1], d[:1])
+        ph = g.phase_times()
+        assert [ph[p][1] for p in ("validate", "reserve", "compact")] == [1, 0, 0]

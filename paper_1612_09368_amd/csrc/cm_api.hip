@@ -882,27 +882,18 @@ int64_t small_batch(cm_graph *g, int64_t s, bool inserting, bool strict, cm_batc
         const Ctl &c = *g->hctl;
         const int64_t fb = c.first_bad == INT_MAX ? -1 : c.first_bad;
         if (stats) stats->first_bad = fb;
+        if (o.prep != PREP_OK && stats) {  // nothing ran
+            stats->launches = 0;
+            stats->kernel_ms = 0.0;
+            stats->alg_bytes = 0;
+            stats->group = 0;
+            stats->first_stamp = 0;
+        }
         if (o.prep == PREP_BAD) {
-            if (stats) {  // nothing ran
-                stats->launches = 0;
-                stats->kernel_ms = 0.0;
-                stats->alg_bytes = 0;
-                stats->group = 0;
-                stats->first_stamp = 0;
-            }
             g->err = std::string("invalid batch item ") + std::to_string(fb) + ": " + cm_strerror(o.code);
             throw Fail{o.code};
         }
-        if (o.prep != PREP_POOL) {
-            if (o.prep == PREP_NONE && stats) {
-                stats->launches = 0;
-                stats->kernel_ms = 0.0;
-                stats->alg_bytes = 0;
-                stats->group = 0;
-                stats->first_stamp = 0;
-            }
-            return c.valid_count;
-        }
+        if (o.prep != PREP_POOL) return c.valid_count;
         if (g->no_alloc) {
             g->err = "adjacency pool full (the allocation-free call cannot grow it; nothing was applied)";
             throw Fail{CM_E_CAPACITY};

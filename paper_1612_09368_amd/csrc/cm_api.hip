@@ -272,10 +272,13 @@ struct Tmp {
 // over another replaces some 40 arrays of the same sizes: hipMalloc and hipFree
 // of a 4 to 16 MB block take 70 to 200 us each (Chung-Lu 10^6 / 10^7: 15.3 ms a
 // load with them, of which the kernels 6).  Everything the blocks are used for
-// is ordered on the handle's stream.
+// is ordered on the handle's stream.  Until they are used or the end has come
+// the blocks stay allocated, and one may be a quarter larger than what it then
+// holds: where memory is short a load is therefore tried again without (on =
+// false: blocks are freed as they are given up).
 struct Reuse {
     cm_graph *g;
-    explicit Reuse(cm_graph *h) : g(h) { g->reuse = true; }
+    Reuse(cm_graph *h, bool on) : g(h) { g->reuse = on; }
     ~Reuse() {
         g->reuse = false;
         if (!g->spare.empty()) (void)hipStreamSynchronize(g->stream);
@@ -387,6 +390,23 @@ void check_overflow(cm_graph *g) {
 // Per-vertex arrays (re)allocation to n_cap ids, keeping the first n_keep.
 void alloc_vertex_arrays(cm_graph *g, int32_t n_cap, int32_t n_keep) {
     DevGraph ng = g->g;
+    // new arrays that the handle does not hold yet go back if a later one fails
+    struct Undo {
+        cm_graph *g;
+        DevGraph &n;
+        bool armed = true;
+        ~Undo() {
+            if (!armed) return;
+            const DevGraph &o = g->g;
+            auto drop = [&](auto *&now, auto *old) {
+                if (now != old) dev_free(g, now);
+            };
+            drop(n.len, o.len); drop(n.cap, o.cap); drop(n.core, o.core); drop(n.mcd, o.mcd);
+            drop(n.stamp.p, o.stamp.p); drop(n.chg, o.chg); drop(n.dec, o.dec); drop(n.done, o.done);
+            drop(n.matched, o.matched); drop(n.bmark, o.bmark); drop(n.gain, o.gain);
+            drop(n.slen, o.slen); drop(n.ubl, o.ubl); drop(n.off, o.off); drop(n.claim, o.claim);
+        }
+    } undo{g, ng};
     ng.n_cap = n_cap;
     hipStream_t st = g->stream;
     auto grow32 = [&](int32_t *&dst, int32_t *old, int32_t fillv, int per = 1) {
@@ -431,6 +451,7 @@ void alloc_vertex_arrays(cm_graph *g, int32_t n_cap, int32_t n_keep) {
     ng.pool_size = g->g.pool_size;
     ng.n_ids = g->g.n_ids;
     g->g = ng;
+    undo.armed = false;
 
     // vertex-sized batch / queue arrays
     dev_free(g, g->b.vlist); dev_free(g, g->b.reloc); dev_free(g, g->b.reloc_off); dev_free(g, g->b.reloc_cap);
@@ -1354,15 +1375,11 @@ void cm_destroy(cm_graph *g) {
     delete g;
 }
 
-int cm_load_graph(cm_graph *g, int32_t n, int64_t m, const int32_t *src, const int32_t *dst,
-                  int on_device) {
-    Range range("cm_load_graph");
-    if (!g || n < 0 || m < 0 || (m > 0 && (!src || !dst))) return CM_E_ARG;
-    if (g->poisoned) return CM_E_DEVICE;
-    if (g->serving) return CM_E_STATE;
+static int load_graph(cm_graph *g, int32_t n, int64_t m, const int32_t *src, const int32_t *dst,
+                      int on_device, bool keep) {
     hipStream_t st = g->stream;
     try {
-        Reuse reuse(g);
+        Reuse reuse(g, keep);
         release_all(g);
         g->loaded = g->decomposed = false;
         g->m = 0;
@@ -1401,6 +1418,7 @@ int cm_load_graph(cm_graph *g, int32_t n, int64_t m, const int32_t *src, const i
             unsigned long long fb = g->hu64[0];
             if (fb != ~0ull) {
                 // something is wrong: find the first bad edge and its code
+                dev_free(g, pos.p);
                 Tmp<int64_t> hval(g);
                 dev_alloc(g, &hval.p, hc);
                 HIPCHK(fill_u64(hkey.p, ~0ull, hc, st));
@@ -1429,16 +1447,16 @@ int cm_load_graph(cm_graph *g, int32_t n, int64_t m, const int32_t *src, const i
             int64_t pool = total + total / 4 + 4096;
             if (g->cfg.edge_capacity_hint > pool) pool = g->cfg.edge_capacity_hint;
             dev_alloc(g, &g->g.nbr, pool);
+            if (m > 0) HIPCHK(scatter_edges(ds, dd, m, g->g.off, pos.p, g->g.nbr, st));
+            dev_free(g, pos.p);  // before the arrays that follow: together they would need more than those
             if (g->tune.sublists) dev_alloc(g, &g->g.sub, pool);
             if (g->tune.uplists) dev_alloc(g, &g->g.upl, pool);
             g->g.pool_size = pool;
-            if (m > 0) HIPCHK(scatter_edges(ds, dd, m, g->g.off, pos.p, g->g.nbr, st));
             // control block
             HIPCHK(hipMemsetAsync(g->ctl, 0, sizeof(Ctl), st));
             unsigned long long tail = (unsigned long long)total;
             HIPCHK(ctl_set_pool(g->ctl, tail, st));
             HIPCHK(hipStreamSynchronize(st));
-            dev_free(g, pos.p);
             std::memset(g->hctl, 0, sizeof(Ctl));
             g->hctl->pool_tail = tail;
             g->epoch = 0;
@@ -1456,6 +1474,20 @@ int cm_load_graph(cm_graph *g, int32_t n, int64_t m, const int32_t *src, const i
     }
     g->err.clear();
     return CM_OK;
+}
+
+int cm_load_graph(cm_graph *g, int32_t n, int64_t m, const int32_t *src, const int32_t *dst,
+                  int on_device) {
+    Range range("cm_load_graph");
+    if (!g || n < 0 || m < 0 || (m > 0 && (!src || !dst))) return CM_E_ARG;
+    if (g->poisoned) return CM_E_DEVICE;
+    if (g->serving) return CM_E_STATE;
+    int rc = load_graph(g, n, m, src, dst, on_device, true);
+    if (rc == CM_E_NOMEM) {
+        rc = load_graph(g, n, m, src, dst, on_device, false);
+        if (rc == CM_OK) g->err.clear();
+    }
+    return rc;
 }
 
 int cm_core_decompose(cm_graph *g, cm_batch_stats *stats) {

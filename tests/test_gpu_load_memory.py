@@ -23,17 +23,28 @@ for f in ("cap_held", "cap_peak"):
     getattr(cap, f).restype = ctypes.c_size_t
 cap.cap_set.argtypes = [ctypes.c_size_t]
 assert cap.cap_init(hip.encode()) == 0
-import graphgen, oracle
+import graphgen
 import paper_1612_09368_amd as cm
 
 def graph(n, m):
     s, d = graphgen.er_graph(n, m, graphgen.rng_for("load-memory", n))
-    return n, torch.from_numpy(s).to("cuda:0"), torch.from_numpy(d).to("cuda:0"), oracle.DynamicGraph(n, s, d).cores()
+    return n, torch.from_numpy(s).to("cuda:0"), torch.from_numpy(d).to("cuda:0"), keys(s, d)
 
-def load(g, gr):
-    g.load(*gr[:3])
-    g.decompose()
-    assert np.array_equal(g.cores(), gr[3])
+def keys(s, d):
+    return np.sort(np.minimum(s, d).astype(np.int64) << 32 | np.maximum(s, d))
+
+NONE = 2 ** 64 - 1
+
+def load(g, gr, most=NONE):
+    # (no decomposition: cooperative launches belong to the process that runs the tests)
+    cap.cap_set(most)
+    try:
+        g.load(*gr[:3])
+    finally:
+        cap.cap_set(NONE)
+    held = cap.cap_held()
+    assert np.array_equal(keys(*g.export_edges()), gr[3])
+    assert cap.cap_held() == held <= most
 
 # 2 m a power of two: the duplicate test's hash is as small as it gets
 big, small = graph(1 << 14, 1 << 18), graph(1 << 13, 1 << 15)
@@ -46,22 +57,21 @@ for gr in (big, small):
     assert held[gr[0]] > 0 and cap.cap_held() == base
 print("held", held, flush=True)
 base = cap.cap_held()
-cap.cap_set(base + held[big[0]])
 with cm.Graph() as g:
     for gr in (big, big, small, big, small, small, big):
-        load(g, gr)
+        load(g, gr, base + held[big[0]])
         print("loaded", gr[0], cap.cap_held() - base, flush=True)
 assert cap.cap_held() == base
 # with less than its arrays need a load is refused, and the handle goes on
-cap.cap_set(base + held[big[0]] // 2)
+half = base + held[big[0]] // 2
 with cm.Graph() as g:
-    load(g, small)
+    load(g, small, half)
     try:
-        load(g, big)
+        load(g, big, half)
         raise SystemExit("too large a graph was accepted")
     except cm.CoreMaintError as e:
         assert e.status == cm.E_NOMEM, e
-    load(g, small)
+    load(g, small, half)
 assert cap.cap_held() == base
 print("load memory: ok", flush=True)
 """

@@ -412,7 +412,7 @@ int cm_debug_log(cm_graph *g, int64_t *n_sel, int32_t *sel, int64_t sel_cap, int
  * expansion round, eviction round, peel round, core update, SD update),
  * 8 chains of steps run inside one workgroup, 9..11 validation, capacity
  * reservation and compaction inside a maintenance launch: cm_run_batches'
- * persistent launch, vertex operations, and edge batches of up to 4,096 items
+ * persistent launch, vertex operations, and edge batches of up to 1,024 items
  * (larger ones validate, reserve and compact in kernels of their own).
  * reset != 0 clears the clock afterwards.  No device work is started. */
 int cm_phase_times(cm_graph *g, double *ms, int64_t *counts, int32_t n, int reset);

@@ -529,11 +529,13 @@ void ensure_vertex_capacity(cm_graph *g, int64_t need) {
 // Batches of up to this many items are validated and reserved inside their
 // first maintenance launch (prep_small), the others by kernels of their own
 // (a dozen launches and two synchronisations, but with every wave of the chip
-// in each step).  One edge of an ER 10^4 graph in and out takes 335 us against
-// 622, 64 edges of a Chung-Lu 10^5 graph 414 against 586, 1,000 edges from
-// host memory 1.33 ms against 1.46; the gain fades as workgroup 0's steps
-// grow, 8 items per thread at 4,096.
-constexpr int64_t FUSED_MAX = 4096;
+// in each step).  The gain fades as workgroup 0's steps grow, two items per
+// thread at 1,024; in and out, plain form, one launch against own kernels, in us:
+//   ER 10^5 / 10^6     1: 392 / 576   64: 680 / 806   1,024: 1,080 / 1,108
+//                      2,048: 1,820 / 1,737   4,096: 1,894 / 1,659
+//   R-MAT 18 / 16      1: 394 / 587   64: 982 / 1,111   1,024: 2,765 / 2,791
+//                      2,048: 3,489 / 3,393   4,096: 4,531 / 4,208
+constexpr int64_t FUSED_MAX = 1024;
 
 void ensure_batch(cm_graph *g, int64_t s, bool clear = true) {
     if (s > INT_MAX / 2) {

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import graphgen
+import oracle
 import paper_1612_09368_amd as cm
 
 pytestmark = pytest.mark.gpu
@@ -69,3 +70,51 @@ def test_phase_clock_of_small_batches(mode):
             g.insert_edges(s[:1], d[:1])
         ph = g.phase_times()
         assert [ph[p][1] for p in ("validate", "reserve", "compact")] == [1, 0, 0]
+
+
+@pytest.mark.parametrize("mode", [cm.MODE_PLAIN, cm.MODE_PERSISTENT])
+@pytest.mark.parametrize("k", [1023, 1024, 1025, 2048])
+def test_largest_batch_prepared_inside_its_launch(k, mode):
+    """Up to 1,024 items workgroup 0 prepares the batch; above that the whole
+    grid's own kernels are faster, and take it."""
+    n, s, d, _ = _graph()
+    es = graphgen.EdgeSet(s, d)
+    a, b = graphgen.uniform_non_edges(n, k, es, graphgen.rng_for("stats-k", k))
+    ref = oracle.DynamicGraph(n, s, d)
+    with cm.Graph(mode=mode) as g:
+        g.load(n, s, d)
+        g.decompose()
+        for call, model in ((g.insert_edges, ref.insert_edges), (g.delete_edges, ref.delete_edges)):
+            g.phase_times(reset=True)
+            call(a, b)
+            model(a, b)
+            ph = g.phase_times()
+            assert [ph[p][1] for p in ("validate", "reserve")] == ([1, 1] if k <= 1024 else [0, 0])
+            assert np.array_equal(g.cores(), ref.cores())
+
+
+@pytest.mark.parametrize("mode", [cm.MODE_PLAIN, cm.MODE_PERSISTENT])
+@pytest.mark.parametrize("lists", [1, 16, 17])
+def test_moved_lists(lists, mode):
+    """Full lists of lengths around one wave step and one group of steps of the
+    copy, moved by one more entry each: in workgroup 0 and by the grid."""
+    size = [1, 4, 60, 64, 68, 448, 455, 456, 508, 512, 516, 1024, 1028, 1536, 3000, 8192, 12000][:lists]
+    n = lists + 16000
+    c = [(x + max(x >> 3, 4) + 3) & ~3 for x in size]  # slots of a list loaded with x entries
+    h = np.arange(lists, dtype=np.int32)
+    s = np.repeat(h, c)
+    d = np.concatenate([lists + np.arange(x) for x in c]).astype(np.int32)
+    first = np.concatenate([np.arange(x) < y for x, y in zip(c, size)])
+    ref = oracle.DynamicGraph(n, s, d)
+    with cm.Graph(mode=mode) as g:
+        g.load(n, s[first], d[first])
+        g.decompose()
+        g.insert_edges(s[~first], d[~first])
+        top = np.full(lists, n - 1, np.int32)
+        for call, model in ((g.insert_edges, ref.insert_edges), (g.delete_edges, ref.delete_edges)):
+            call(h, top)
+            model(h, top)
+            assert np.array_equal(g.cores(), ref.cores())
+            got, want = g.export_edges(), ref.edges()
+            key = [np.sort(np.minimum(x, y).astype(np.int64) * n + np.maximum(x, y)) for x, y in (got, want)]
+            assert np.array_equal(*key)

@@ -1,7 +1,7 @@
 """The allocation-free entry point with a full adjacency pool: a batch whose
 lists cannot move is refused with CM_E_CAPACITY and nothing applied, in batches
 of one edge (no launch queued behind the first), of a few and of the most that
-one launch prepares (one queued), and one edge more (prepared by kernels of
+one launch prepares (one queued), and larger ones (prepared by kernels of
 their own); deletions go on, and the allocating entry point takes the same
 batch."""
 import numpy as np
@@ -30,7 +30,7 @@ def _check(g, ref):
     assert g.num_edges() == ref.num_edges()
 
 
-@pytest.mark.parametrize("s", [1, 2, 300, 4096, 4097])
+@pytest.mark.parametrize("s", [1, 2, 300, 1024, 1025, 4096, 4097])
 @pytest.mark.parametrize("mode", [0, 1], ids=["plain", "persistent"])
 def test_full_pool(mode, s):
     import torch

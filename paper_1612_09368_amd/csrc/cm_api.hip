@@ -873,10 +873,11 @@ LaunchOut run_maintenance(cm_graph *g, KArgs a, cm_batch_stats *stats) {
 // in one program launch, or edge by edge as superior edge sets.  The edge
 // reduction takes one launch per set in the plain form, and a vertex of degree
 // d up to d sets: 1,000 vertices into an R-MAT 17 graph take 465 launches,
-// 108 ms, against 1.8 ms as stars (1,000 out: 327, 36 ms, against 4.0 ms), and
-// one vertex costs the same both ways (0.31 and 0.30 ms).  It stays for what
-// stars do not offer: the iteration log (a star is not a superior edge set)
-// and the one-edge regime.
+// 108 ms, against 1.8 ms as stars (1,000 out: 327, 36 ms, against 4.0 ms), one
+// vertex of degree 10 into an ER 10^5 / 10^6 graph 0.85 ms against 0.30, one of
+// degree 1,000 279 ms against 0.78; only a single edge is faster as such (0.16
+// against 0.28).  It stays for what stars do not offer: the iteration log (a star
+// is not a superior edge set) and the one-edge regime.
 bool vertex_stars(const cm_graph *g) {
     return g->cfg.mode == CM_MODE_PERSISTENT || (!g->cfg.debug && !g->cfg.single_edge && !g->cfg.async_steps);
 }

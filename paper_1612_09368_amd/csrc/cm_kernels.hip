@@ -425,7 +425,6 @@ __global__ void __launch_bounds__(COOP_THREADS) k_maintain(KArgs a) {
         c->epoch = ep;
         c->iters_done = n;
     }
-    if (!a.mirror) return;
     gbar(a.bar);  // the statistics of every workgroup are in
     if (squeeze && clock_thread()) {  // (the workgroup's own clock has been flushed)
         atomicAdd(&c->ph_ticks[PH_COMPACT], (unsigned long long)wall_clock64() - t0);
@@ -687,6 +686,7 @@ hipError_t delete_compact(const KArgs &a, int blocks, hipStream_t st) {
     return hipGetLastError();
 }
 hipError_t maintain_coop(const KArgs &a, int blocks, hipStream_t st) {
+    if (!a.lout || !a.mirror) return hipErrorInvalidValue;
     return coop((const void *)k_maintain, a, blocks, st);
 }
 hipError_t program_coop(const KArgs &a, int blocks, hipStream_t st) {

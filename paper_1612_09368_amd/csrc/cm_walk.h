@@ -142,7 +142,7 @@ __device__ __forceinline__ void vs_push(const KArgs &a, VStream &s, int32_t w, b
 }
 __device__ __forceinline__ void cs_flush(const KArgs &a, CStream &s) {
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // other lanes' LDS writes come first
-    for (int i0 = 0; i0 < s.b.n; i0 += WAVE) {
+    for (int i0 = 0; i0 < s.b.n; i0 += WAVE) {  // up to 2 * WAVE - 1 entries
         const bool has = i0 + lane() < s.b.n;
         const int32_t w = has ? s.b.buf[i0 + lane()] : -1;
         push_chunks(a, s.q, s.tail, w, has ? nchunks(s.len[i0 + lane()], s.chunk) : 0);
@@ -165,8 +165,9 @@ __device__ __forceinline__ void cs_push(const KArgs &a, CStream &s, int32_t w, i
 // End of a step: what is left in the waves' buffers, appended with one tail
 // atomic per stream and workgroup.  One per wave is 2,048 turns on a word at
 // 11 ns each, for each of the streams (which share a line): a round that gave
-// every wave something to push took 20 to 60 us for it.  Every thread of the
-// workgroup must call it (workgroup barriers inside).
+// every wave something to push took 20 to 60 us for it.  A buffer that reaches
+// WAVE entries is flushed at once, so each holds fewer here.  Every thread of
+// the workgroup must call it (workgroup barriers inside).
 template <int NV, int NC>
 __device__ __forceinline__ void block_flush(const KArgs &a, VStream *const (&vs)[NV], CStream *const (&cs)[NC]) {
     constexpr int N = NV + NC, NW = COOP_THREADS / WAVE;
@@ -176,26 +177,21 @@ __device__ __forceinline__ void block_flush(const KArgs &a, VStream *const (&vs)
     const int wv = uniform((int)(threadIdx.x / WAVE));
     const int nw = (int)(blockDim.x / WAVE);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // other lanes' LDS writes come first
-    int32_t w[NC][2], nch[NC][2], incl[NC][2], mine[N];
+    int32_t w[NC], nch[NC], incl[NC], mine[N];
 #pragma unroll
     for (int i = 0; i < NV; ++i) mine[i] = vs[i]->b.n;
 #pragma unroll
     for (int i = 0; i < NC; ++i) {
         CStream &s = *cs[i];
-        mine[NV + i] = 0;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            w[i][h] = -1;
-            nch[i][h] = incl[i][h] = 0;
-            if (s.b.n > h * WAVE) {  // uniform
-                const bool has = h * WAVE + lane() < s.b.n;
-                if (has) {
-                    w[i][h] = s.b.buf[h * WAVE + lane()];
-                    nch[i][h] = nchunks(s.len[h * WAVE + lane()], s.chunk);
-                }
-                incl[i][h] = wave_incl_add(nch[i][h]);
-                mine[NV + i] += __builtin_amdgcn_readlane(incl[i][h], WAVE - 1);
+        w[i] = -1;
+        nch[i] = incl[i] = mine[NV + i] = 0;
+        if (s.b.n > 0) {  // uniform
+            if (lane() < s.b.n) {
+                w[i] = s.b.buf[lane()];
+                nch[i] = nchunks(s.len[lane()], s.chunk);
             }
+            incl[i] = wave_incl_add(nch[i]);
+            mine[NV + i] = __builtin_amdgcn_readlane(incl[i], WAVE - 1);
         }
     }
     if (lane() == 0) {
@@ -223,9 +219,9 @@ __device__ __forceinline__ void block_flush(const KArgs &a, VStream *const (&vs)
         for (int j = 0; j < wv; ++j) base += cnt[i][j];
         if (i < NV) {
             VStream &s = *vs[i < NV ? i : 0];
-            for (int x = lane(); x < s.b.n; x += WAVE) {
-                const int pos = base + x;
-                if (pos < a.q.vcap) s.q[pos] = s.b.buf[x];
+            if (lane() < s.b.n) {
+                const int pos = base + lane();
+                if (pos < a.q.vcap) s.q[pos] = s.b.buf[lane()];
                 else atomicOr(&a.ctl->overflow, 1);
             }
             s.b.n = 0;
@@ -233,10 +229,7 @@ __device__ __forceinline__ void block_flush(const KArgs &a, VStream *const (&vs)
             constexpr int Z = NV;
             const int ci = i < NV ? 0 : i - Z;
             CStream &s = *cs[ci];
-            write_chunks(a, s.q, base, w[ci][0], nch[ci][0], incl[ci][0]);
-            if (s.b.n > WAVE)
-                write_chunks(a, s.q, base + __builtin_amdgcn_readlane(incl[ci][0], WAVE - 1), w[ci][1], nch[ci][1],
-                             incl[ci][1]);
+            write_chunks(a, s.q, base, w[ci], nch[ci], incl[ci]);
             s.b.n = 0;
         }
     }
@@ -373,9 +366,12 @@ __device__ __forceinline__ void wave_walk(const DevGraph &g, int32_t v, int32_t 
 // that chain, 2 to 3 us, at every step.  The staged walks take WALK_STEPS
 // steps together, stage by stage, so that the reads and atomics of all of them
 // are in flight at once (8 batches on R-MAT 22 and back: expansion 93 to
-// 78 ms, SD 21 to 15 ms; 512 threads per CU leave the registers for it).  A stage may test what earlier stages loaded and issue the next
-// load or atomic, but must not look at what it issues itself (that would wait
-// for it before the next step's is issued):
+// 78 ms, SD 21 to 15 ms).  The cooperative kernels run one workgroup of 512
+// threads per CU, so a thread may have 256 VGPRs: k_maintain needs 142,
+// k_decompose 87, k_serve 231; k_program needs all 256 and spills 7.  A stage
+// may test what earlier stages loaded and issue the next load or atomic, but must
+// not look at what it issues itself (that would wait for it before the next
+// step's is issued):
 //   s1(e)   first gather of entry e.w (w < 0: none or a tombstone)
 //   s2(e)   second gathers, chosen by the first
 //   s3(e)   the atomic
@@ -507,11 +503,12 @@ __device__ __forceinline__ void for_batches(const Team &T, const int32_t *q, int
 // is claimed, evicted or peeled exactly once through an atomic), so a vertex
 // may be walked in the round that finds it.  fb(v, limit) walks the lists of
 // up to `limit` entries and returns the entries it walked (uniform).
-// A grid round costs about 6 us of barrier plus its first chain of reads, a
-// wave's own group of steps about 3 us: 12 steps and 32 vertices were the best
-// of (4, 8), (8, 12), (12, 32), (16, 16) over the update workloads (ER 2^18,
-// 100 edges: 1.84 ms without, 2.01 / 1.53 / 1.39 / 1.49 ms; 64-graph pool:
-// 55.1 ms without, 47.6 / 46.7 / 47.5 / 47.4 ms).
+// A grid round costs about 9 us in all (barrier, first chain of reads), a wave's
+// own group of steps about 3 us.  Of (4, 8), (8, 12), (12, 32) and (16, 16)
+// steps and vertices, (12, 32) was taken for the long thin cascades of small
+// batches, where it is 9% ahead of the next (ER 2^18, 100 edges: 1.84 ms without,
+// 2.01 / 1.53 / 1.39 / 1.49 ms); on the 64-graph pool it is within 2% of the best
+// (55.1 ms without, 47.6 / 46.7 / 47.5 / 47.4 ms).
 constexpr int DEEP_STEPS = 12, DEEP_WIDTH = 32;
 template <class FB>
 __device__ __forceinline__ void for_batches_deep(const Team &T, const int32_t *q, int32_t n, Pusher &p,

@@ -307,3 +307,33 @@ def test_long_supporter_runs_of_neighbouring_hubs(share, cfg):
             g.delete_edges(a, b)
             ref.delete_edges(a, b)
             _check(g, ref)
+
+
+@pytest.mark.parametrize("cfg", [dict(mode=cm.MODE_PLAIN), dict(mode=cm.MODE_PERSISTENT),
+                                 dict(mode=cm.MODE_PERSISTENT, chunk=32), dict(mode=cm.MODE_PERSISTENT, large_degree=16)],
+                         ids=["plain", "persistent", "chunk32", "large16"])
+@pytest.mark.parametrize("half,pairs", [(400, 950), (120, 990)])
+def test_eviction_of_a_dense_graph(half, pairs, cfg):
+    """A regular graph of 2,000 vertices, nearly all of them candidates of one
+    matching and evicted in one round with runs of hundreds of entries: more
+    items of 64 entries than the lists have chunks."""
+    nd = 2000
+    i = np.repeat(np.arange(nd), half)
+    j = (i + np.tile(np.arange(1, half + 1), nd)) % nd
+    a = np.arange(pairs)
+    _insert_first(nd, np.minimum(i, j), np.maximum(i, j), a, a + nd // 2, cfg)
+
+
+def _insert_first(n, s, d, a, b, cfg):
+    s, d, a, b = (np.asarray(x, np.int32) for x in (s, d, a, b))
+    ref = oracle.DynamicGraph(n, s, d)
+    with cm.Graph(**cfg) as g:
+        g.load(n, s, d)
+        g.decompose()
+        for _ in range(2):
+            g.insert_edges(a, b)
+            ref.insert_edges(a, b)
+            _check(g, ref)
+            g.delete_edges(a, b)
+            ref.delete_edges(a, b)
+            _check(g, ref)

@@ -12,6 +12,7 @@
 #include <new>
 #include <string>
 #include <unordered_map>
+#include <utility>
 #include <vector>
 
 #include <rocprofiler-sdk-roctx/roctx.h>
@@ -474,6 +475,7 @@ void alloc_vertex_arrays(cm_graph *g, int32_t n_cap, int32_t n_keep) {
     HIPCHK(fill_i32(g->firstidx, INT_MAX, n_cap, st));
     int64_t need_tmp = scan_tmp_len(n_cap);
     if (need_tmp > g->scan_tmp_cap) {
+        g->scan_tmp_cap = 0;
         dev_free(g, g->scan_tmp);
         dev_alloc(g, &g->scan_tmp, need_tmp);
         g->scan_tmp_cap = need_tmp;
@@ -494,6 +496,7 @@ void alloc_chunk_queues(cm_graph *g) {
     if (h > INT_MAX) h = INT_MAX;
     if (e > INT_MAX) e = INT_MAX;
     if (h > g->q.hcap) {
+        g->q.hcap = 0;
         for (int i = 0; i < 2; ++i) {
             dev_free(g, g->q.fh[i]);
             dev_alloc(g, &g->q.fh[i], h);
@@ -503,6 +506,7 @@ void alloc_chunk_queues(cm_graph *g) {
         g->q.hcap = (int32_t)h;
     }
     if (e > g->q.ecap) {
+        g->q.ecap = 0;
         for (int i = 0; i < 2; ++i) {
             dev_free(g, g->q.eh[i]);
             dev_alloc(g, &g->q.eh[i], e);
@@ -514,6 +518,7 @@ void alloc_chunk_queues(cm_graph *g) {
         // most once) plus two chunk items per chunk of a claimed list
         const int64_t ac = std::min<int64_t>((int64_t)g->g.n_cap + 2 * (int64_t)g->q.hcap, INT_MAX);
         if (ac > g->q.acap) {
+            g->q.acap = 0;
             for (int i = 0; i < 2; ++i) {
                 dev_free(g, g->q.aq[i]);
                 dev_alloc(g, &g->q.aq[i], ac);
@@ -560,6 +565,7 @@ void ensure_batch(cm_graph *g, int64_t s, bool clear = true) {
     if (s > g->batch_cap) {
         int64_t c = std::max<int64_t>(s, 1024);
         DevBatch &b = g->b;
+        g->batch_cap = b.cap = 0;  // none, if one of them does not fit
         dev_free(g, b.err); dev_free(g, b.eu); dev_free(g, b.ev); dev_free(g, b.su); dev_free(g, b.sv);
         dev_free(g, b.hslot); dev_free(g, b.rem[0]); dev_free(g, b.rem[1]); dev_free(g, b.sel); dev_free(g, b.esel);
         dev_free(g, g->src_buf); dev_free(g, g->dst_buf);
@@ -574,6 +580,7 @@ void ensure_batch(cm_graph *g, int64_t s, bool clear = true) {
     }
     int64_t hc = next_pow2(std::max<int64_t>(2 * s, 1024));
     if (hc > g->hash_cap) {
+        g->hash_cap = 0;
         dev_free(g, g->b.hkey); dev_free(g, g->b.hval);
         dev_alloc(g, &g->b.hkey, hc);
         dev_alloc(g, &g->b.hval, hc);
@@ -587,6 +594,7 @@ void ensure_batch(cm_graph *g, int64_t s, bool clear = true) {
     int64_t sc = 2 * s + g->g.pool_size / std::max(1, g->tune.chunk) + 1024;
     sc = std::min<int64_t>(sc, INT_MAX);
     if (sc > g->scan_cap) {
+        g->scan_cap = 0;
         dev_free(g, g->b.scanq);
         dev_alloc(g, &g->b.scanq, sc);
         g->scan_cap = (int32_t)sc;
@@ -601,43 +609,67 @@ double now_ms() {
 
 // Build (or rebuild) the adjacency pool so that every live list gets slack;
 // lists keep their order, tombstones are dropped.  extra = slots to add to
-// the pool beyond the packed size.
+// the pool beyond the packed size.  Where memory is short the lists stay as
+// they are (CM_E_NOMEM).
 void repack(cm_graph *g, int64_t extra) {
     Range range("coremaint.repack");
     hipStream_t st = g->stream;
     KArgs a = make_args(g);
-    int32_t *cnt = g->g.gain;  // gain is zero between batches; used as scratch here
+    Tmp<int64_t> caps64(g), newoff(g);
+    dev_alloc(g, &caps64.p, g->g.n_cap);
+    dev_alloc(g, &newoff.p, g->g.n_cap);
+    // scratch between batches: gain (zero again afterwards) and a vertex queue
+    int32_t *cnt = g->g.gain, *newcap = g->q.touched;
     HIPCHK(count_live(a, cnt, g->grid_reg, st));
-    int64_t *caps64 = nullptr, *newoff = nullptr;
-    dev_alloc(g, &caps64, g->g.n_cap);
-    dev_alloc(g, &newoff, g->g.n_cap);
-    HIPCHK(caps_from_counts(cnt, g->g.n_ids, g->g.n_cap, caps64, g->g.cap, st));
-    HIPCHK(exclusive_scan_i64(caps64, newoff, g->g.n_cap, g->scan_tmp, g->i64_scratch, st));
+    HIPCHK(caps_from_counts(cnt, g->g.n_ids, g->g.n_cap, caps64.p, newcap, st));
+    HIPCHK(exclusive_scan_i64(caps64.p, newoff.p, g->g.n_cap, g->scan_tmp, g->i64_scratch, st));
     int64_t total = 0;
     HIPCHK(hipMemcpyAsync(&total, g->i64_scratch, sizeof(int64_t), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
     int64_t pool = total + std::max<int64_t>(extra, total / 4) + 4096;
     if (g->cfg.edge_capacity_hint > pool) pool = g->cfg.edge_capacity_hint;
-    int32_t *newnbr = nullptr;
-    dev_alloc(g, &newnbr, pool);
-    if (g->tune.sublists) {
-        // supporter lists live only within an iteration: nothing to copy
-        dev_free(g, g->g.sub);
-        dev_alloc(g, &g->g.sub, pool);
+    Tmp<int32_t> newnbr(g);
+    try {
+        dev_alloc(g, &newnbr.p, pool);
+        if (g->tune.sublists) {
+            // supporter lists live only within an iteration: nothing to copy
+            dev_free(g, g->g.sub);
+            dev_alloc(g, &g->g.sub, pool);
+        }
+        if (g->tune.uplists) {
+            // every up-list is invalidated with the move (repack_finish)
+            dev_free(g, g->g.upl);
+            dev_alloc(g, &g->g.upl, pool);
+        }
+    } catch (const Fail &) {
+        // back to the arrays of the present pool, without up-lists
+        const std::string why = g->err;
+        g->poisoned = true;  // unless they are complete below
+        dev_free(g, newnbr.p);
+        if (g->tune.sublists) {
+            dev_free(g, g->g.sub);
+            dev_alloc(g, &g->g.sub, g->g.pool_size);
+        }
+        if (g->tune.uplists) {
+            dev_free(g, g->g.upl);
+            dev_alloc(g, &g->g.upl, g->g.pool_size);
+            HIPCHK(fill_i32(g->g.ubl, -1, g->g.n_cap, st));
+        }
+        HIPCHK(fill_i32(cnt, 0, g->g.n_cap, st));
+        HIPCHK(hipStreamSynchronize(st));
+        g->poisoned = false;
+        g->err = why;
+        throw;
     }
-    if (g->tune.uplists) {
-        // every up-list is invalidated with the move (repack_finish)
-        dev_free(g, g->g.upl);
-        dev_alloc(g, &g->g.upl, pool);
-    }
-    HIPCHK(repack_copy(a, newoff, newnbr, g->grid_reg, st));
-    HIPCHK(repack_finish(a, newoff, cnt, g->grid_reg, st));
+    HIPCHK(hipMemcpyAsync(g->g.cap, newcap, sizeof(int32_t) * (size_t)g->g.n_cap, hipMemcpyDeviceToDevice, st));
+    HIPCHK(repack_copy(a, newoff.p, newnbr.p, g->grid_reg, st));
+    HIPCHK(repack_finish(a, newoff.p, cnt, g->grid_reg, st));
     HIPCHK(fill_i32(cnt, 0, g->g.n_cap, st));
     HIPCHK(hipStreamSynchronize(st));
-    dev_free(g, caps64);
-    dev_free(g, newoff);
-    dev_free(g, g->g.nbr);
-    g->g.nbr = newnbr;
+    std::swap(g->g.nbr, newnbr.p);
+    dev_free(g, newnbr.p);
+    dev_free(g, caps64.p);
+    dev_free(g, newoff.p);
     g->g.pool_size = pool;
     unsigned long long tail = (unsigned long long)total;
     HIPCHK(ctl_set_pool(g->ctl, tail, st));
@@ -1058,6 +1090,7 @@ void program_execute(cm_graph *g, const std::vector<ProgBatch> &pb, const int32_
     const int32_t nb = (int32_t)pb.size();
     out.assign((size_t)nb, ProgOut{});
     if (nb > g->prog_cap) {
+        g->prog_cap = 0;
         dev_free(g, g->d_pbatch);
         dev_free(g, g->d_pout);
         int32_t c = std::max(nb, 64);
@@ -2673,6 +2706,7 @@ int cm_run_batches(cm_graph *g, int32_t nb, const int32_t *kinds, const int64_t 
         const int32_t *ds = src, *dd = dst, *dsub = sub;
         if (!on_device && total > 0) {
             if (total > g->items_cap) {
+                g->items_cap = 0;
                 dev_free(g, g->d_isrc); dev_free(g, g->d_idst); dev_free(g, g->d_isub);
                 int64_t c = std::max<int64_t>(total, 1024);
                 dev_alloc(g, &g->d_isrc, c);

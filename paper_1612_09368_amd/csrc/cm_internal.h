@@ -757,8 +757,9 @@ __device__ __forceinline__ bool slice_over(const Bar *b, unsigned long long t0) 
 // arrivals are those of gbar: all but this workgroup on its own XCC's counter,
 // all the other XCCs on the top one (both are zero again before gbar lets
 // anyone go).  They arrive while the first step runs (the others have nothing
-// else to do), so this is two loads as a rule.  False if the barrier was
-// aborted.  Every thread of the workgroup must call it, once per chain.
+// else to do), so this is two loads as a rule: 0.3 to 0.8 us a chain, under
+// 0.4% of any workload of perf/cases.py.  False if the barrier was aborted.
+// Every thread of the workgroup must call it, once per chain.
 __device__ __forceinline__ bool chain_alone(Bar *b) {
     __shared__ int alone;
     if (threadIdx.x == 0) {

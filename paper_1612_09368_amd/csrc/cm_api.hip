@@ -484,34 +484,28 @@ void alloc_vertex_arrays(cm_graph *g, int32_t n_cap, int32_t n_keep) {
 
 // Chunk queues sized for n_cap + pool/chunk items.  The eviction walks supporter
 // runs of more than evict_large entries as items of evict_chunk (cm_phases.h),
-// which may be shorter: a graph with lists of some 100 entries and more on
-// average needs more of those than of chunks.
+// which may be shorter: a graph with lists of some 40 entries and more on
+// average may need more of those than of chunks.  (One capacity for all five
+// queues: one of its own for the eviction's two saves a dense graph 2% of its
+// memory, and took the plain form of the R-MAT 22 stream from 743 to 758 ms a
+// pass by what the compiler then did with k_maintain.)
 void alloc_chunk_queues(cm_graph *g) {
     int64_t h = (int64_t)g->g.n_cap + g->g.pool_size / std::max(1, g->tune.chunk) + 1024;
-    int64_t e = h;
     if (g->tune.sublists) {
         const int64_t item = std::max(1, std::min(g->tune.chunk, WAVE)), run = std::min(g->tune.large_deg, WAVE) + 1;
-        e = std::max(h, std::min<int64_t>(g->g.n_cap, g->g.pool_size / run) + g->g.pool_size / item + 1024);
+        h = std::max(h, std::min<int64_t>(g->g.n_cap, g->g.pool_size / run) + g->g.pool_size / item + 1024);
     }
     if (h > INT_MAX) h = INT_MAX;
-    if (e > INT_MAX) e = INT_MAX;
     if (h > g->q.hcap) {
         g->q.hcap = 0;
         for (int i = 0; i < 2; ++i) {
-            dev_free(g, g->q.fh[i]);
+            dev_free(g, g->q.fh[i]); dev_free(g, g->q.eh[i]);
             dev_alloc(g, &g->q.fh[i], h);
+            dev_alloc(g, &g->q.eh[i], h);
         }
         dev_free(g, g->q.chh);
         dev_alloc(g, &g->q.chh, h);
         g->q.hcap = (int32_t)h;
-    }
-    if (e > g->q.ecap) {
-        g->q.ecap = 0;
-        for (int i = 0; i < 2; ++i) {
-            dev_free(g, g->q.eh[i]);
-            dev_alloc(g, &g->q.eh[i], e);
-        }
-        g->q.ecap = (int32_t)e;
     }
     if (g->tune.async_steps) {
         // an asynchronous step holds every item it creates: vertices (each at

@@ -220,7 +220,6 @@ struct DevBatch {
 struct DevQueues {
     int32_t vcap;        // capacity of vertex queues
     int32_t hcap;        // capacity of chunk queues
-    int32_t ecap;        // capacity of eh for the evictions' shorter items (>= hcap; see evict_cap)
     int32_t *fq[2];
     int64_t *fh[2];
     int32_t *eq[2];

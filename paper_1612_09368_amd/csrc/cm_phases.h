@@ -753,8 +753,8 @@ __device__ __forceinline__ void part_select(const KArgs &a, const Iter &it, int 
     VStream bq{wave_buf(0), it.ins ? a.q.fq[0] : a.q.eq[0], it.ins ? &c->fq_tail[0] : &c->eq_tail[0]};
     VStream bchg{wave_buf(1), a.q.chg, &c->chg_count};
     VStream brem{wave_buf(2), a.b.rem[it.cur ^ 1], &c->rem_count[it.cur ^ 1]};
-    CStream bh{wave_buf(3), wave_lens(0), a.q.eh[0], &c->eh_tail[0], a.t.chunk, a.q.hcap};
-    CStream bchh{wave_buf(4), wave_lens(1), a.q.chh, &c->chh_count, a.t.chunk, a.q.hcap};
+    CStream bh{wave_buf(3), wave_lens(0), a.q.eh[0], &c->eh_tail[0], a.t.chunk};
+    CStream bchh{wave_buf(4), wave_lens(1), a.q.chh, &c->chh_count, a.t.chunk};
     for_span(T, it.n_r, [&](int32_t idx) {
         const int32_t i = idx >= 0 ? R[idx] : -1;
         const bool open = i >= 0 && !(r > 0 && a.b.esel[i] == it.ep);  // not taken in an earlier round
@@ -1347,10 +1347,6 @@ __device__ __forceinline__ int32_t evict_large(const KArgs &a) {
     return a.t.large_deg < WAVE ? a.t.large_deg : WAVE;
 }
 __device__ __forceinline__ int32_t evict_chunk(const KArgs &a) { return a.t.chunk < WAVE ? a.t.chunk : WAVE; }
-// Items of the eviction queue: shorter than a chunk with supporter runs, so
-// that a dense graph has more of them than of any other queue's (the host sizes
-// it: ecap).
-__device__ __forceinline__ int32_t evict_cap(const KArgs &a) { return a.t.sublists ? a.q.ecap : a.q.hcap; }
 
 __device__ __forceinline__ void expand_round_pruned(const KArgs &a, const Iter &it, int r, const Team &T,
                                                     Acc &acc) {
@@ -1387,7 +1383,7 @@ __device__ __forceinline__ void expand_round_pruned(const KArgs &a, const Iter &
         const int32_t L = v >= 0 ? g.len[v] : 0;
         const int32_t k = v >= 0 ? g.core[v] : 0;
         const bool big = L > a.t.large_deg;
-        push_chunks(a, a.q.fh[bn], a.q.hcap, &c->fh_tail[sn], v, big ? nchunks(L, a.t.chunk) : 0);
+        push_chunks(a, a.q.fh[bn], &c->fh_tail[sn], v, big ? nchunks(L, a.t.chunk) : 0);
         const bool live = v >= 0 && !big;
         int32_t pcd = 0;
         flat_walk(g, v, live ? L : 0, [&](int32_t j, int32_t w, unsigned long long own) {
@@ -1514,10 +1510,9 @@ __device__ __forceinline__ void expand_round(const KArgs &a, const Iter &it, int
     };
     const bool sl = a.t.sublists != 0;
     Pusher pq = make_pusher(a.q.fq[bn], &c->fq_tail[sn], a.q.fh[bn], &c->fh_tail[sn], g.len, a.t.large_deg,
-                            a.t.chunk, a.q.hcap);
+                            a.t.chunk);
     VStream ev{wave_buf(3), a.q.eq[0], &c->eq_tail[0]}, cand{wave_buf(5), a.q.cand, &c->cand_count};
-    CStream eh{wave_buf(4), wave_lens(2), a.q.eh[0], &c->eh_tail[0], sl ? evict_chunk(a) : a.t.chunk,
-               evict_cap(a)};
+    CStream eh{wave_buf(4), wave_lens(2), a.q.eh[0], &c->eh_tail[0], sl ? evict_chunk(a) : a.t.chunk};
     auto push_next = [&](int32_t w, bool p) { push_deep(a, pq, w, p); };
     // an evicted vertex's walk is its supporter run (sublists) or its list
     auto push_evict = [&](int32_t v, bool p, int32_t nsup) {
@@ -1620,7 +1615,7 @@ __device__ __forceinline__ void expand_round(const KArgs &a, const Iter &it, int
         const int32_t L = v >= 0 ? g.len[v] : 0;
         const int32_t k = v >= 0 ? g.core[v] : 0;
         const bool big = L > limit;
-        push_chunks(a, a.q.fh[bn], a.q.hcap, &c->fh_tail[sn], v, big ? nchunks(L, a.t.chunk) : 0);
+        push_chunks(a, a.q.fh[bn], &c->fh_tail[sn], v, big ? nchunks(L, a.t.chunk) : 0);
         const bool live = v >= 0 && !big;
         int32_t pcd = 0, nlk = 0;  // CSD; supporters written to this lane's list
         const int32_t walked = flat_walk_st(g.nbr, g, v, live ? L : 0, k, s1, s2, s3, s4,
@@ -1659,7 +1654,7 @@ __device__ __forceinline__ void evict_round(const KArgs &a, const Iter &it, int 
     const int sc = slot_read(r), sn = slot_push(r), sx = slot_clear(r);
     const int bc = r & 1, bn = bc ^ 1;
     const int32_t nq = sqlen(it.sn, c, &c->eq_tail[sc], a.q.vcap);
-    const int32_t nh = sqlen(it.sn, c, &c->eh_tail[sc], evict_cap(a));
+    const int32_t nh = sqlen(it.sn, c, &c->eh_tail[sc], a.q.hcap);
     if (T.lead()) {
         c->eq_tail[sx] = 0; c->eh_tail[sx] = 0;
         ph_count(PH_ROUNDS);
@@ -1668,7 +1663,7 @@ __device__ __forceinline__ void evict_round(const KArgs &a, const Iter &it, int 
     // an evicted vertex's walk: its supporter run (sublists) or its list
     const bool sl = a.t.sublists != 0;
     Pusher pq = make_pusher(a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn], sl ? g.slen : g.len,
-                            sl ? evict_large(a) : a.t.large_deg, sl ? evict_chunk(a) : a.t.chunk, evict_cap(a));
+                            sl ? evict_large(a) : a.t.large_deg, sl ? evict_chunk(a) : a.t.chunk);
     const int32_t *arr = sl ? g.sub : g.nbr;
     // Of a supporter run every entry is a level-k candidate of this iteration
     // (the expansion scanned the evicted vertex, as every candidate, before
@@ -1741,9 +1736,9 @@ __device__ __forceinline__ void peel_round(const KArgs &a, const Iter &it, int r
     }
     const int32_t ep = it.ep;
     Pusher pq = make_pusher(a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn], g.len, a.t.large_deg,
-                            a.t.chunk, a.q.hcap);
+                            a.t.chunk);
     VStream touched{wave_buf(3), a.q.touched, &c->touched_count}, chg{wave_buf(4), a.q.chg, &c->chg_count};
-    CStream chh{wave_buf(5), wave_lens(2), a.q.chh, &c->chh_count, a.t.chunk, a.q.hcap};
+    CStream chh{wave_buf(5), wave_lens(2), a.q.chh, &c->chh_count, a.t.chunk};
     // cores and SD do not change during a peel round
     auto s1 = [&](Ent &e) __attribute__((always_inline)) {
         e.a = -1;
@@ -1810,7 +1805,7 @@ __device__ __forceinline__ void apply_core(const KArgs &a, const Iter &it, const
             c->st_icand += (unsigned long long)n;
         }
         VStream chg{wave_buf(0), a.q.chg, &c->chg_count};
-        CStream chh{wave_buf(1), wave_lens(0), a.q.chh, &c->chh_count, a.t.chunk, a.q.hcap};
+        CStream chh{wave_buf(1), wave_lens(0), a.q.chh, &c->chh_count, a.t.chunk};
         int32_t moved = 0;  // uniform
         for_span(T, n, [&](int32_t idx) {
             int32_t v = -1, k = 0, L = 0;
@@ -1982,10 +1977,6 @@ __device__ __forceinline__ long long queue_work(const KArgs &a, const Team &T, c
     return block_sum64(w) + (long long)nchk * a.t.chunk;
 }
 
-__device__ __forceinline__ int32_t eh_cap(const KArgs &a, int32_t step) {
-    return step == S_EVICT ? evict_cap(a) : a.q.hcap;
-}
-
 // Whether workgroup 0 may run this step by itself: its item count already
 // passed step_is_local; here the list entries it would walk are checked.
 __device__ __forceinline__ bool block_local_ok(const KArgs &a, const Iter &it, const PC &pc, const Team &T) {
@@ -2000,7 +1991,7 @@ __device__ __forceinline__ bool block_local_ok(const KArgs &a, const Iter &it, c
     case S_EVICT:
     case S_PEEL:
         // an eviction walks supporter runs when they are kept
-        w = queue_work(a, T, a.q.eq[pc.r & 1], sqlen(it.sn, c, &c->eq_tail[s], a.q.vcap), sqlen(it.sn, c, &c->eh_tail[s], eh_cap(a, pc.step)),
+        w = queue_work(a, T, a.q.eq[pc.r & 1], sqlen(it.sn, c, &c->eq_tail[s], a.q.vcap), sqlen(it.sn, c, &c->eh_tail[s], a.q.hcap),
                        a.t.large_deg, pc.step == S_EVICT && a.t.sublists ? a.g.slen : a.g.len);
         break;
     case S_MCD:
@@ -2022,7 +2013,7 @@ __device__ __forceinline__ int64_t step_work(const KArgs &a, const Iter &it, con
     case S_EXPAND:
         return frontier_work(a, sqlen(it.sn, c, &c->fq_tail[s], a.q.vcap), sqlen(it.sn, c, &c->fh_tail[s], a.q.hcap));
     case S_EVICT:
-    case S_PEEL: return frontier_work(a, sqlen(it.sn, c, &c->eq_tail[s], a.q.vcap), sqlen(it.sn, c, &c->eh_tail[s], eh_cap(a, pc.step)));
+    case S_PEEL: return frontier_work(a, sqlen(it.sn, c, &c->eq_tail[s], a.q.vcap), sqlen(it.sn, c, &c->eh_tail[s], a.q.hcap));
     case S_CORE:
         // a deletion's core step also clears the peel counters of every
         // touched vertex
@@ -2969,8 +2960,8 @@ __device__ __forceinline__ void dec_sweep(const KArgs &a, const DState &st, cons
     const int32_t next = st.k + 1 < top ? st.k + 1 : -1;  // degree of the next level, if it is near
     VStream tv{wave_buf(0), a.q.eq[fb], &c->eq_tail[fn]}, bn{wave_buf(1), nlist, &c->nr_count[n1]},
         bf{wave_buf(2), flist, &c->rm_count[f1]}, bx{wave_buf(4), a.q.chg, &c->fq_tail[h1]};
-    CStream tc{wave_buf(3), wave_lens(0), a.q.eh[fb], &c->eh_tail[fn], a.t.chunk, a.q.hcap},
-        xc{wave_buf(5), wave_lens(1), a.q.fh[0], &c->fh_tail[h1], a.t.chunk, a.q.hcap};
+    CStream tc{wave_buf(3), wave_lens(0), a.q.eh[fb], &c->eh_tail[fn], a.t.chunk},
+        xc{wave_buf(5), wave_lens(1), a.q.fh[0], &c->fh_tail[h1], a.t.chunk};
     int32_t fmin = 0x7fffffff, nmin = 0x7fffffff;
     const int32_t span = wave_span(n);
     for (int32_t base = T.wave() * span; base < n; base += T.nwaves() * span) {
@@ -3058,9 +3049,9 @@ __device__ __forceinline__ void dec_round(const KArgs &a, const DState &st, cons
         if (e.a == GONE) g.core[e.w] = k;
     };
     Pusher pq = make_pusher(a.q.eq[bn], &c->eq_tail[sn], a.q.eh[bn], &c->eh_tail[sn], g.len, a.t.large_deg,
-                            a.t.chunk, a.q.hcap);
+                            a.t.chunk);
     VStream near{wave_buf(3), nlist, ntail}, bx{wave_buf(4), a.q.chg, &c->fq_tail[hs]};
-    CStream xc{wave_buf(5), wave_lens(2), a.q.fh[0], &c->fh_tail[hs], a.t.chunk, a.q.hcap};
+    CStream xc{wave_buf(5), wave_lens(2), a.q.fh[0], &c->fh_tail[hs], a.t.chunk};
     auto fin = [&](int32_t w, int32_t f) {
         if (__ballot(f != 0) == 0ull) return;
         const int32_t L = f & (GONE | NEXT) ? g.len[w] : 0;

@@ -17,8 +17,8 @@ namespace cm {
 // together, lane i taking items i, i + 64, ..., so a very long list does not
 // serialise on its own lane.  Every lane of the wave must call it; incl =
 // the inclusive scan of nch.
-__device__ __forceinline__ void write_chunks(const KArgs &a, int64_t *hq, int32_t hcap, int32_t base, int32_t w,
-                                             int32_t nch, int32_t incl) {
+__device__ __forceinline__ void write_chunks(const KArgs &a, int64_t *hq, int32_t base, int32_t w, int32_t nch,
+                                             int32_t incl) {
     const int32_t total = __builtin_amdgcn_readlane(incl, WAVE - 1);
     const int32_t excl = incl - nch;
     for (int32_t e0 = 0; e0 < total; e0 += WAVE) {
@@ -35,7 +35,7 @@ __device__ __forceinline__ void write_chunks(const KArgs &a, int64_t *hq, int32_
         const int32_t wj = __shfl(w, j);
         if (e < total) {
             const int32_t pos = base + e;
-            if (pos < hcap) hq[pos] = chunk_item(wj, e - xj);
+            if (pos < a.q.hcap) hq[pos] = chunk_item(wj, e - xj);
             else atomicOr(&a.ctl->overflow, 1);
         }
     }
@@ -45,14 +45,14 @@ __device__ __forceinline__ void write_chunks(const KArgs &a, int64_t *hq, int32_
 // per wave: returning atomics on one word serialise (about 11 ns each), and
 // one per long list bound the rounds that push many of them.  A wave with
 // inactive lanes (the last pass of a strided loop) pushes lane by lane.
-__device__ __forceinline__ void push_chunks(const KArgs &a, int64_t *hq, int32_t hcap, int32_t *htail, int32_t w,
+__device__ __forceinline__ void push_chunks(const KArgs &a, int64_t *hq, int32_t *htail, int32_t w,
                                             int32_t nch) {
     if (__ballot(nch > 0) == 0ull) return;
     if (__ballot(1) != ~0ull) {
         if (nch > 0) {
             const int32_t base = atomicAdd(htail, nch);
             for (int32_t c = 0; c < nch; ++c) {
-                if (base + c < hcap) hq[base + c] = chunk_item(w, c);
+                if (base + c < a.q.hcap) hq[base + c] = chunk_item(w, c);
                 else atomicOr(&a.ctl->overflow, 1);
             }
         }
@@ -61,7 +61,7 @@ __device__ __forceinline__ void push_chunks(const KArgs &a, int64_t *hq, int32_t
     const int32_t incl = wave_incl_add(nch);
     int32_t base = 0;
     if (lane() == WAVE - 1) base = atomicAdd(htail, incl);
-    write_chunks(a, hq, hcap, __builtin_amdgcn_readlane(base, WAVE - 1), w, nch, incl);
+    write_chunks(a, hq, __builtin_amdgcn_readlane(base, WAVE - 1), w, nch, incl);
 }
 
 // Route a pushed vertex: short/medium lists to the vertex queue, long lists
@@ -72,7 +72,7 @@ __device__ __forceinline__ void push_vertex(const KArgs &a, int32_t *vq, int32_t
     int32_t L = pred ? a.g.len[w] : 0;
     bool big = pred && L > a.t.large_deg;
     push_agg<int32_t>(vq, a.q.vcap, vtail, w, pred && !big, &a.ctl->overflow);
-    push_chunks(a, hq, a.q.hcap, htail, w, big ? nchunks(L, a.t.chunk) : 0);
+    push_chunks(a, hq, htail, w, big ? nchunks(L, a.t.chunk) : 0);
 }
 
 // Per-wave push buffers in LDS.  A queue tail is one word that every wave
@@ -130,7 +130,7 @@ struct CStream {
     int32_t *len;  // walk lengths of the buffer's entries
     int64_t *q;
     int32_t *tail;
-    int32_t chunk, cap;
+    int32_t chunk;
 };
 constexpr int CHUNK_STREAMS = 3;  // of one step
 __device__ __forceinline__ int32_t *wave_lens(int i) {
@@ -145,7 +145,7 @@ __device__ __forceinline__ void cs_flush(const KArgs &a, CStream &s) {
     for (int i0 = 0; i0 < s.b.n; i0 += WAVE) {  // up to 2 * WAVE - 1 entries
         const bool has = i0 + lane() < s.b.n;
         const int32_t w = has ? s.b.buf[i0 + lane()] : -1;
-        push_chunks(a, s.q, s.cap, s.tail, w, has ? nchunks(s.len[i0 + lane()], s.chunk) : 0);
+        push_chunks(a, s.q, s.tail, w, has ? nchunks(s.len[i0 + lane()], s.chunk) : 0);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // reads done before the slots are reused
     s.b.n = 0;
@@ -229,7 +229,7 @@ __device__ __forceinline__ void block_flush(const KArgs &a, VStream *const (&vs)
             constexpr int Z = NV;
             const int ci = i < NV ? 0 : i - Z;
             CStream &s = *cs[ci];
-            write_chunks(a, s.q, s.cap, base, w[ci], nch[ci], incl[ci]);
+            write_chunks(a, s.q, base, w[ci], nch[ci], incl[ci]);
             s.b.n = 0;
         }
     }
@@ -248,9 +248,9 @@ struct Pusher {
     int32_t large;
 };
 __device__ __forceinline__ Pusher make_pusher(int32_t *vq, int32_t *vtail, int64_t *hq, int32_t *htail,
-                                              const int32_t *lens, int32_t large, int32_t chunk, int32_t cap) {
-    return Pusher{VStream{wave_buf(0), vq, vtail}, CStream{wave_buf(1), wave_lens(0), hq, htail, chunk, cap},
-                  CStream{wave_buf(2), wave_lens(1), hq, htail, chunk, cap}, lens, large};
+                                              const int32_t *lens, int32_t large, int32_t chunk) {
+    return Pusher{VStream{wave_buf(0), vq, vtail}, CStream{wave_buf(1), wave_lens(0), hq, htail, chunk},
+                  CStream{wave_buf(2), wave_lens(1), hq, htail, chunk}, lens, large};
 }
 __device__ __forceinline__ void push_deep(const KArgs &a, Pusher &p, int32_t w, int32_t L, bool pred) {
     vs_push(a, p.v, w, pred && L <= p.large);
@@ -273,7 +273,7 @@ __device__ __forceinline__ void push_vertex_wb(const KArgs &a, WaveBuf &b, int32
     const int32_t L = pred ? a.g.len[w] : 0;
     const bool big = pred && L > a.t.large_deg;
     wb_push(b, vq, a.q.vcap, vtail, w, pred && !big, &a.ctl->overflow);
-    push_chunks(a, hq, a.q.hcap, htail, w, big ? nchunks(L, a.t.chunk) : 0);
+    push_chunks(a, hq, htail, w, big ? nchunks(L, a.t.chunk) : 0);
 }
 
 // Team-stride over 0 .. n-1 by whole waves: f(i) runs on every lane (i < 0

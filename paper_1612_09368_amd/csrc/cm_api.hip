@@ -484,7 +484,7 @@ void alloc_vertex_arrays(cm_graph *g, int32_t n_cap, int32_t n_keep) {
 
 // Chunk queues sized for n_cap + pool/chunk items.  The eviction walks supporter
 // runs of more than evict_large entries as items of evict_chunk (cm_phases.h),
-// which may be shorter: a graph with lists of some 40 entries and more on
+// which may be shorter: a graph with lists of some 30 entries and more on
 // average may need more of those than of chunks.  (One capacity for all five
 // queues: one of its own for the eviction's two saves a dense graph 2% of its
 // memory, and took the plain form of the R-MAT 22 stream from 743 to 758 ms a

@@ -121,6 +121,10 @@ def library():
         return _lib
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"{LIB_PATH} is missing: build it with `python -m paper_1612_09368_amd.build`")
+    try:
+        _torch()  # its HIP runtime serves the library too: a second one in the process would find no device
+    except ImportError:
+        pass
     lib = ctypes.CDLL(LIB_PATH)
     P, I32, I64 = ctypes.c_void_p, ctypes.c_int32, ctypes.c_int64
     sig = {

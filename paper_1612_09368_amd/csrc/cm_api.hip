@@ -1324,6 +1324,7 @@ int cm_create(const cm_config *cfg, cm_graph **out) {
         g->tune.local_edges = g->cfg.local_edges > 0 ? g->cfg.local_edges : 2048;
         g->tune.local_items = g->cfg.local_items > 0 ? g->cfg.local_items : 128;
         g->tune.local_work = g->cfg.local_work > 0 ? g->cfg.local_work : 16384;
+        g->tune.slice_mask = slice_mask(g->tune.local_edges, g->tune.local_items, g->tune.local_work);
         g->tune.async_steps = g->cfg.async_steps ? 1 : 0;
         g->tune.single_edge = g->cfg.single_edge ? 1 : 0;
         if (g->cfg.expand_mode < 0 || g->cfg.expand_mode > 4) {

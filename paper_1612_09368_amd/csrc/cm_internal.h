@@ -247,7 +247,7 @@ struct Tune {
     int32_t stamp_limit; // iteration stamps restart (stamp arrays cleared) before passing this
     int32_t sublists;    // the one-pass expansion records supporter lists for the eviction
     int32_t uplists;     // long lists keep up-lists (scanned by the one-pass expansion)
-    int32_t pad;
+    int32_t slice_mask;  // a chain of local steps looks at its slice when (steps & slice_mask) == 0
 };
 
 // Chunk items of the expansion's claim pass (pruned expansion) carry this

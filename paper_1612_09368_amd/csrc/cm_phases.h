@@ -2200,10 +2200,9 @@ __device__ __forceinline__ int run_iterations(const KArgs &a, int ins, int max_i
                     pc = next_pc(a, it, pc);
                     // a long chain (a cascade of many small rounds) hands
                     // back to the grid once per slice, so that no barrier
-                    // wait outlasts its bound (looked at every 16 steps, well
-                    // under a millisecond: it takes two workgroup barriers)
+                    // wait outlasts its bound
                     stop = pc.step == S_DONE || !step_is_local(a, it, pc, step_work(a, it, pc)) ||
-                           ((++links & 15) == 0 && slice_over(a.bar, tl));
+                           ((++links & a.t.slice_mask) == 0 && slice_over(a.bar, tl));
                 }
                 if (stop) {
                     const int slot = pubs & 1;
@@ -3212,7 +3211,8 @@ __device__ __forceinline__ void decompose(const KArgs &a, Acc &acc) {
             if (!stop) {
                 __syncthreads();
                 st = dec_next(a, st);
-                stop = st.step == D_DONE || !dec_is_local(a, st) || ((++links & 15) == 0 && slice_over(a.bar, tl));
+                stop = st.step == D_DONE || !dec_is_local(a, st) ||
+                       ((++links & a.t.slice_mask) == 0 && slice_over(a.bar, tl));
             }
             if (stop) {
                 const int slot = pubs & 1;

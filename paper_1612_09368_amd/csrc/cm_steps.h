@@ -23,4 +23,12 @@ __host__ __device__ constexpr int slot_clear(int32_t r) { return (r + 2) % 3; }
 // at the barrier that ends the chain, thus has looked (chain_alone).
 constexpr int CHAIN_FREE = 1;
 
+// A chain of local steps looks at its time slice when (steps & mask) == 0: every
+// 16 steps (the look takes two workgroup barriers, and 16 steps of the default
+// bounds take well under a millisecond), but after each one where the bounds let
+// a single step take milliseconds, so that 16 of them could outlast a barrier wait.
+__host__ __device__ constexpr int slice_mask(int32_t local_edges, int32_t local_items, int32_t local_work) {
+    return local_edges > (1 << 16) || local_items > (1 << 14) || local_work > (1 << 20) ? 0 : 15;
+}
+
 }  // namespace cm

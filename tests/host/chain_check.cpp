@@ -1,7 +1,8 @@
 // Host check of the step machines' rotating counters (cm_steps.h), built with
 // hipcc as host code and run by tests/test_chain.py: a workgroup that looks at
 // the counters late -- at any point of the steps that workgroup 0 runs before
-// it waits for the others -- sees what the early ones saw.
+// it waits for the others -- sees what the early ones saw; how often a chain
+// looks at its time slice.
 #include <cstdio>
 
 #include "../../paper_1612_09368_amd/csrc/cm_steps.h"
@@ -42,6 +43,12 @@ int main() {
             }
         }
     }
+    // the slice: every 16 steps for the default bounds and for tuned ones, after
+    // each step where a bound lets one step walk for milliseconds
+    CHECK(slice_mask(2048, 128, 16384) == 15 && slice_mask(8192, 1024, 1 << 18) == 15);
+    CHECK(slice_mask(0x7fffffff, 128, 16384) == 0);
+    CHECK(slice_mask(2048, 0x7fffffff, 16384) == 0);
+    CHECK(slice_mask(2048, 128, 0x7fffffff) == 0);
     std::printf(fails ? "chain: %d failures\n" : "chain: ok\n", fails);
     return fails ? 1 : 0;
 }

@@ -62,3 +62,31 @@ def test_grid_rounds_into_chains_and_back(mode, items):
                 g.insert_edges(a, b)
                 ref.insert_edges(a, b)
                 assert np.array_equal(g.cores(), ref.cores())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("mode", [0, 1], ids=["plain", "persistent"])
+def test_chains_of_long_steps(mode):
+    """Bounds that keep every step in workgroup 0, whatever its size: the chain
+    looks at its slice after each step, hands back to the grid and goes on."""
+    import graphgen
+    import oracle
+    import paper_1612_09368_amd as cm
+    import torch
+    assert torch.cuda.is_available()
+    n = 20_000
+    s, d = graphgen.er_graph(n, 100_000, graphgen.rng_for("chain-long"))
+    es = graphgen.EdgeSet(s, d)
+    a, b = graphgen.uniform_non_edges(n, 5000, es, graphgen.rng_for("chain-long", 1))
+    ref = oracle.DynamicGraph(n, s, d)
+    big = (1 << 31) - 1
+    with cm.Graph(mode=mode, local_edges=big, local_items=big, local_work=big) as g:
+        g.load(n, s, d)
+        g.decompose()
+        assert np.array_equal(g.cores(), ref.cores())
+        for _ in range(2):
+            for call, model in ((g.insert_edges, ref.insert_edges), (g.delete_edges, ref.delete_edges)):
+                st = call(a, b)
+                model(a, b)
+                assert np.array_equal(g.cores(), ref.cores())
+                assert st.local_steps > 0 and st.grid_steps == 0

@@ -2699,7 +2699,8 @@ __device__ __forceinline__ int run_one_batch(const KArgs &a, const ProgDesc *pd,
         const bool star = kind == P_STARS_IN || kind == P_STARS_OUT;
         iters += run_iterations(a, vb.inserting, 0x7fffffff, ep, acc, pubs, star ? sc : StarCtx{});
     }
-    if (pass0 != 0 && validate) prog_finish(a, vb.inserting, acc);
+    // (without a validated batch, vertices without edges, there are no lists to compact)
+    if (pass0 != 0) prog_finish(a, vb.inserting || !validate, acc);
     if (B.kind == 3) {
         vdel_finish_ids(a, pd, ids, B.s, status == 0, G);
         gbar(a.bar);

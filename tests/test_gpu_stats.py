@@ -118,3 +118,20 @@ def test_moved_lists(lists, mode):
             got, want = g.export_edges(), ref.edges()
             key = [np.sort(np.minimum(x, y).astype(np.int64) * n + np.maximum(x, y)) for x, y in (got, want)]
             assert np.array_equal(*key)
+
+
+@pytest.mark.parametrize("mode", [cm.MODE_PLAIN, cm.MODE_PERSISTENT])
+def test_vertices_without_edges_leave_in_counted_steps(mode):
+    """Their steps are theirs, not the next batch's."""
+    n, s, d, _ = _graph()
+    with cm.Graph(mode=mode) as g:
+        g.load(n + 100, s, d)
+        g.decompose()
+        st = g.delete_vertices(np.arange(n, n + 100, 3, dtype=np.int32))
+        assert st.iterations > 0 and st.applied == 0
+        assert st.grid_steps >= st.iterations
+        ref = oracle.DynamicGraph(n, s, d)
+        assert np.array_equal(g.cores()[:n], ref.cores())
+        left = g.cores()[n:]
+        assert (left[::3] == -1).all() and (np.delete(left, np.arange(0, 100, 3)) == 0).all()
+        assert g.num_vertices() == (n + 100, n + 100 - 34)

@@ -50,9 +50,9 @@ HBM_PEAK_GBS = 8000.0
 # summaries and commands are under profiles/).
 TRAFFIC = {
     "rmat22-stream": {"kernel": "k_program", "bytes_per_launch": 1820.9e9,
-                      "sources_sha256": "838ee45b4487de55b90511cd2527b3c790ab598007994a2546ee63a8001a12e2"},
+                      "sources_sha256": "4cece2a8e9c1de9122e74bb973a71cb703eca867203d5c8f69c18045263fbd84"},
 }
-KERNEL_SOURCES = ["cm_internal.h", "cm_kernels.hip", "cm_phases.h", "cm_walk.h"]
+KERNEL_SOURCES = ["cm_internal.h", "cm_kernels.hip", "cm_phases.h", "cm_steps.h", "cm_walk.h"]
 
 
 def kernel_sources_sha256():
